@@ -2,6 +2,7 @@
 // Kept in a file of its own so that its source fingerprint names exactly the code a
 // profile of it measured.
 #pragma once
+#include "fft.h"
 #include "vsp_internal.h"
 
 namespace vsp {
@@ -10,65 +11,117 @@ namespace vsp {
 // lanes 32-63; coefficient l + 32 t belongs to lane l). ACC starts as (0, X^{-bbar} tv) with
 // tv = mu everywhere; step i adds BK_i (ext) (X^{abar_i} ACC - ACC) (a CMUX between ACC and
 // its rotation selected by the key bit s0_i); a step with abar_i = 0 has a zero difference,
-// hence a zero product, and is skipped. LDS per workgroup: the twiddle tables, then per wave
-// the accumulator (2 x 1024 u32) and the two transpose regions.
-constexpr int BR_WAVE_U32 = 2 * RING_N + WAVE_T_U32;
+// hence a zero product, and is skipped. LDS per workgroup: the lane tables, then per wave
+// the accumulator (2 x 1024 u32) and the two exchange regions.
+constexpr int BR_WAVE_U32 = 2 * RING_N + 2 * FFT_WAVE_F64;
 
-constexpr size_t br_lds_bytes(int waves) { return 2048 * 8 + (size_t)waves * BR_WAVE_U32 * 4; }
+constexpr size_t br_lds_bytes(int waves, bool shared) {
+  return FFT_TAB_C64 * 16 + (shared ? 2 * FFT_PIECE_C64 * 16 : 0) + (size_t)waves * BR_WAVE_U32 * 4;
+}
 
-// With keytab non-NULL gate g uses the bootstrapping key keytab[kid[g]] (clients with their
-// own keys in one launch), else bkn.
+// The key shared by a workgroup's gates, streamed through LDS in pieces of one slot pair (6 KiB, in
+// the order of use over all steps): two LDS slots, each thread carrying its share of the next two
+// pieces in registers. While a piece is used, the next one is written to the other slot and the load
+// of the one three on is issued; one barrier per piece. A wave alone would read the whole
+// transformed key, 147 KB a step, through the vector cache for every gate. The threads past a
+// piece's 384 entries load and write the first ones a second time (the same values): waves that
+// branch around it cost more.
 template <int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_blind_rotate(const u64* __restrict__ bkn, const u64* __restrict__ tw,
+struct SharedKey {
+  static constexpr int PER = (FFT_PIECE_C64 + WAVES * 64 - 1) / (WAVES * 64);  // 16-byte entries per thread
+  gkey src;    // start of the next piece to load
+  c64* ring;   // [2][FFT_PIECE_C64]
+  int left;    // pieces still to load
+  c64 r[2][PER];  // piece n in r[n mod 2]
+  __device__ __forceinline__ int entry(int q) const {
+    const int i = (int)threadIdx.x + q * WAVES * 64;
+    return i < FFT_PIECE_C64 ? i : i - FFT_PIECE_C64;
+  }
+  __device__ __forceinline__ void load(c64 (&x)[PER]) {
+#pragma unroll
+    for (int q = 0; q < PER; q++) x[q] = gkey_load(src + entry(q));
+    if (--left > 0) src += FFT_PIECE_C64;  // past the end the last piece is loaded again, unused
+  }
+  __device__ __forceinline__ void store(int slot, const c64 (&x)[PER]) {
+#pragma unroll
+    for (int q = 0; q < PER; q++) ring[slot * FFT_PIECE_C64 + entry(q)] = x[q];
+  }
+  __device__ __forceinline__ void start(gkey key, c64* lds) {
+    src = key;
+    ring = lds;
+    left = LWE_N * FFT_PIECES;
+    load(r[0]);
+    store(0, r[0]);
+    load(r[1]);
+    load(r[0]);
+  }
+  __device__ __forceinline__ void half(int, int p, int e, c64 (&v)[FFT_PRODUCTS]) {
+    const c64* s = ring + (p & 1) * FFT_PIECE_C64 + e * FFT_HALF_C64 + (threadIdx.x & 63);
+#pragma unroll
+    for (int q = 0; q < FFT_PRODUCTS; q++) v[q] = s[q * 64];
+    if (e == 0) return;
+    store((p + 1) & 1, r[(p + 1) & 1]);
+    load(r[(p + 1) & 1]);
+  }
+  __device__ __forceinline__ void meet() { __syncthreads(); }
+};
+
+// SHARED: every gate uses the key bkf, which the workgroup streams through LDS; its waves meet at
+// every piece, so a wave without a gate takes part as well (on a zero accumulator). Otherwise gate g
+// reads the key keytab[kid[g]] by itself (clients with their own keys in one launch), or bkf with
+// keytab NULL, and steps whose difference is zero are skipped.
+template <int WAVES, int PER_SIMD, bool SHARED>
+__global__ __launch_bounds__(WAVES * 64, PER_SIMD) void k_blind_rotate(const c64* __restrict__ bkf, const c64* __restrict__ tab,
                                                              const uint8_t* __restrict__ ops,
                                                              const u32* __restrict__ abar, u32* __restrict__ tlwe1,
                                                              u32* __restrict__ trlwe, uint64_t B,
-                                                             const u64* const* __restrict__ keytab,
+                                                             const c64* const* __restrict__ keytab,
                                                              const uint16_t* __restrict__ kid) {
-  extern __shared__ u64 lds[];
-  u64* tws = lds;
-  for (int i = threadIdx.x; i < 2048; i += WAVES * 64) tws[i] = tw[i];
+  extern __shared__ c64 lds[];
+  c64* tabs = lds;
+  c64* ring = lds + FFT_TAB_C64;
+  for (int i = threadIdx.x; i < FFT_TAB_C64; i += WAVES * 64) tabs[i] = tab[i];
+  SharedKey<WAVES> shared;
+  if (SHARED) shared.start((gkey)bkf, ring);
   __syncthreads();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t g = (uint64_t)blockIdx.x * WAVES + wave;
-  if (g >= B) return;
-  if (ops && !op_bootstraps(ops[g])) return;
-  if (keytab) bkn = keytab[__builtin_amdgcn_readfirstlane(kid[g])];
+  const bool live = g < B && (!ops || op_bootstraps(ops[g]));
+  if (!SHARED && !live) return;
+  if (!SHARED && keytab) bkf = keytab[__builtin_amdgcn_readfirstlane(kid[g])];
   const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
-  u32* wbase = reinterpret_cast<u32*>(lds + 2048) + wave * BR_WAVE_U32;
-  const u32* ab = abar + g * TLWE0;
-  const int bbar = (int)ab[LWE_N];
-  const int k0 = (2 * RING_N - bbar) & (2 * RING_N - 1);
+  u32* wbase = reinterpret_cast<u32*>(ring + (SHARED ? 2 * FFT_PIECE_C64 : 0)) + wave * BR_WAVE_U32;
+  const u32* ab = abar + (live ? g : 0) * TLWE0;
   {
+    const int k0 = (2 * RING_N - (int)ab[LWE_N]) & (2 * RING_N - 1);
     u32* accs = wbase + h * RING_N;
 #pragma unroll
-    for (int t = 0; t < 32; t++) accs[l + 32 * t] = h ? rotated_testvector(l + 32 * t, k0) : 0u;
+    for (int t = 0; t < 32; t++) accs[l + 32 * t] = (h && live) ? rotated_testvector(l + 32 * t, k0) : 0u;
   }
   wave_lds_sync();
   for (int i = 0; i < LWE_N; i++) {
     const int a = (int)__builtin_amdgcn_readfirstlane(ab[i]);
-    if (a == 0) continue;
+    if (!SHARED && a == 0) continue;
     const int ln = opaque_lane(lane);
     const int li = ln & 31, hi = ln >> 5;
     u32* accs = wbase + hi * RING_N;
-    u32* treg = wbase + 2 * RING_N + hi * TREGION;
-    // digits of X^a ACC - ACC, recomputed from the LDS accumulator in every round
-    auto digits = [&](int sh, u64 (&x)[32]) {
-#pragma unroll
-      for (int t = 0; t < 32; t++) {
-        const int idx = (li + 32 * t - a) & (2 * RING_N - 1);
-        u32 r = accs[idx & (RING_N - 1)];
-        if (idx & RING_N) r = 0u - r;
-        x[t] = gadget_digit(r - accs[li + 32 * t], sh);
-      }
-    };
+    double* reg = reinterpret_cast<double*>(wbase + 2 * RING_N) + hi * FFT_REGION;
+    const int bt = 4 * (li - a);
+    auto word = [&](int t) { return rotated_word(accs, bt + 128 * t, accs[li + 32 * t]); };
     u32 z[32];
-    external_product(digits, bkn + (size_t)i * TRGSW_NTT_U64, tws, tws + 1024, treg, ln, z);
+    if constexpr (SHARED) {
+      fft_external_product(word, shared, tabs, reg, ln, z);
+    } else {
+      GlobalKey key;
+      key.base = (gkey)bkf + (size_t)i * TRGSW_FFT_C64 + ln;
+      fft_external_product(word, key, tabs, reg, ln, z);
+    }
 #pragma unroll
     for (int t = 0; t < 32; t++)
       __hip_atomic_fetch_add(&accs[li + 32 * t], z[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     wave_lds_sync();
   }
+  if (!live) return;
   const u32* accs = wbase + h * RING_N;
   if (trlwe) {
     u32* o = trlwe + g * 2 * RING_N + h * RING_N;

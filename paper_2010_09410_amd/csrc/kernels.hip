@@ -43,6 +43,40 @@ hipError_t launch_trgsw_to_ntt(const vsp_context* ctx, const uint32_t* src, uint
   return hipGetLastError();
 }
 
+// One wave per (item, round k, product q): lanes 0-31 transform that product's key polynomial of
+// TRGSW row k, lanes 32-63 of row k + 3; results land in the key layout of fft.h.
+__global__ __launch_bounds__(256) void k_trgsw_to_fft(const u32* __restrict__ src, c64* __restrict__ dst,
+                                                      const c64* __restrict__ tab, uint64_t jobs) {
+  __shared__ double lds[4 * FFT_WAVE_F64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t job = (uint64_t)blockIdx.x * 4 + wave;
+  if (job >= jobs) return;
+  const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
+  const uint64_t item = job / (GADGET_L * FFT_PRODUCTS);
+  const int rem = (int)(job % (GADGET_L * FFT_PRODUCTS)), k = rem / FFT_PRODUCTS, q = rem % FFT_PRODUCTS;
+  const u32* a = src + (item * 2 * GADGET_L + k + GADGET_L * h) * 2 * RING_N;
+  const u32* b = a + RING_N;
+  double re[16], im[16];
+#pragma unroll
+  for (int t = 0; t < 16; t++) {
+    const int j = l + 32 * t;
+    re[t] = (double)fft_key_int(a[j], b[j], q);
+    im[t] = (double)fft_key_int(a[j + RING_N / 2], b[j + RING_N / 2], q);
+  }
+  fft_forward(re, im, tab, lds + wave * FFT_WAVE_F64 + h * FFT_REGION, l);
+  c64* out = dst + item * TRGSW_FFT_C64 + (size_t)k * 8 * FFT_PIECE_C64 + h * FFT_HALF_C64 + q * 64 + l;
+#pragma unroll
+  for (int s = 0; s < 16; s++)  // the inverse's factor 512 is taken off here (exactly)
+    out[(s & 7) * FFT_PIECE_C64 + 32 * (s >> 3)] = make_double2(re[s] * 0x1p-9, im[s] * 0x1p-9);
+}
+
+hipError_t launch_trgsw_to_fft(const vsp_context* ctx, const uint32_t* src, c64* dst, uint64_t count, hipStream_t st) {
+  if (count == 0) return hipSuccess;
+  const uint64_t jobs = count * GADGET_L * FFT_PRODUCTS;
+  hipLaunchKernelGGL(k_trgsw_to_fft, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, st, src, dst, ctx->ftab, jobs);
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ gate prologue
 // Linear combination of a homomorphic gate on the +-1/8 encoding (standard TFHE gates),
 // then modulus switch of every coefficient to Z/2N: round(x 2N / 2^32).
@@ -163,23 +197,27 @@ hipError_t launch_mux_combine(uint32_t* t, uint64_t B, hipStream_t st) {
 // Raises the dynamic-LDS limit of the kernels that use more than 64 KiB (once, at context
 // creation, outside any stream capture).
 hipError_t init_kernel_attributes() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_blind_rotate<4>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)br_lds_bytes(4));
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_blind_rotate<8>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)br_lds_bytes(8));
-  return e;
+  const struct {
+    const void* fn;
+    size_t lds;
+  } k[] = {{reinterpret_cast<const void*>(&k_blind_rotate<4, 1, true>), br_lds_bytes(4, true)},
+           {reinterpret_cast<const void*>(&k_blind_rotate<8, 2, true>), br_lds_bytes(8, true)},
+           {reinterpret_cast<const void*>(&k_blind_rotate<8, 2, false>), br_lds_bytes(8, false)},
+           {reinterpret_cast<const void*>(&k_blind_rotate_wide), brw_lds_bytes()}};
+  for (const auto& x : k)
+    if (hipError_t e = hipFuncSetAttribute(x.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)x.lds)) return e;
+  return hipSuccess;
 }
 
 hipError_t blind_rotate_capacity(int device, uint64_t (&cap)[kBrShapes]) {
   int cus = 0, n4 = 0, n8 = 0, nw = 0;
   hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n4, reinterpret_cast<const void*>(&k_blind_rotate<4>), 256,
-                                                     br_lds_bytes(4));
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n4, reinterpret_cast<const void*>(&k_blind_rotate<4, 1, true>), 256,
+                                                     br_lds_bytes(4, true));
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n8, reinterpret_cast<const void*>(&k_blind_rotate<8>), 512,
-                                                     br_lds_bytes(8));
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n8, reinterpret_cast<const void*>(&k_blind_rotate<8, 2, true>), 512,
+                                                     br_lds_bytes(8, true));
   if (e == hipSuccess)
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nw, reinterpret_cast<const void*>(&k_blind_rotate_wide),
                                                      BRW_WAVES * 64, brw_lds_bytes());
@@ -198,14 +236,14 @@ hipError_t blind_rotate_capacity(int device, uint64_t (&cap)[kBrShapes]) {
 }
 
 hipError_t launch_blind_rotate(const vsp_context* ctx, const uint8_t* ops, const uint32_t* abar, uint32_t* tlwe1,
-                               uint32_t* trlwe, uint64_t B, int waves, hipStream_t st, const uint64_t* bkn,
-                               const uint64_t* const* keytab, const uint16_t* kid, void* mf_work, bool instrument,
+                               uint32_t* trlwe, uint64_t B, int waves, hipStream_t st, const c64* bkf,
+                               const c64* const* keytab, const uint16_t* kid, void* mf_work, bool instrument,
                                const int8_t* const* tile_mfkeys) {
   if (B == 0) return hipSuccess;
-  if (bkn == nullptr) bkn = ctx->bkn;
+  if (bkf == nullptr) bkf = ctx->bkf;
   if (waves <= 0) waves = ctx->tune.br_waves(B);
   if (br_matrix_form(waves)) {
-    const bool own = keytab == nullptr && bkn == ctx->bkn && ctx->mf_key != nullptr;
+    const bool own = keytab == nullptr && bkf == ctx->bkf && ctx->mf_key != nullptr;
     if (mf_work != nullptr && (own || tile_mfkeys != nullptr))
       return waves == 32 ? launch_blind_rotate_mfma(ctx, ops, abar, tlwe1, trlwe, B, mf_work, st, instrument, tile_mfkeys)
                          : launch_blind_rotate_mfsplit(ctx, ops, abar, tlwe1, trlwe, B, mf_work,
@@ -214,14 +252,14 @@ hipError_t launch_blind_rotate(const vsp_context* ctx, const uint8_t* ops, const
     waves = ctx->tune.br_waves(B, true);
   }
   if (waves == 3) {
-    hipLaunchKernelGGL(k_blind_rotate_wide, dim3((unsigned)B), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, bkn,
-                       ctx->tw, ops, abar, tlwe1, trlwe, B, keytab, kid);
-  } else if (waves == 4) {
-    hipLaunchKernelGGL(k_blind_rotate<4>, dim3((unsigned)((B + 3) / 4)), dim3(256), br_lds_bytes(4), st, bkn,
-                       ctx->tw, ops, abar, tlwe1, trlwe, B, keytab, kid);
+    hipLaunchKernelGGL(k_blind_rotate_wide, dim3((unsigned)B), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, bkf,
+                       ctx->ftab, ops, abar, tlwe1, trlwe, B, keytab, kid);
   } else {
-    hipLaunchKernelGGL(k_blind_rotate<8>, dim3((unsigned)((B + 7) / 8)), dim3(512), br_lds_bytes(8), st, bkn,
-                       ctx->tw, ops, abar, tlwe1, trlwe, B, keytab, kid);
+    // one key for all gates: the workgroup shares it; per-gate keys: each wave reads its own
+    auto* kern = keytab ? &k_blind_rotate<8, 2, false> : waves == 4 ? &k_blind_rotate<4, 1, true> : &k_blind_rotate<8, 2, true>;
+    const int w = keytab == nullptr && waves == 4 ? 4 : 8;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((B + w - 1) / w)), dim3(64 * w), br_lds_bytes(w, keytab == nullptr), st, bkf,
+                       ctx->ftab, ops, abar, tlwe1, trlwe, B, keytab, kid);
   }
   return hipGetLastError();
 }

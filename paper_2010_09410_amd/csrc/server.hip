@@ -46,11 +46,11 @@ struct Slot {  // one in-flight batch
   uint8_t* h_ops = nullptr;
   uint32_t* h_idx = nullptr;
   uint16_t* h_kid = nullptr;
-  const uint64_t** h_keytab = nullptr;
+  const c64** h_keytab = nullptr;
   uint8_t* d_ops = nullptr;
   uint32_t* d_idx = nullptr;
   uint16_t* d_kid = nullptr;
-  const uint64_t** d_keytab = nullptr;
+  const c64** d_keytab = nullptr;
   const int8_t** h_tilekeys = nullptr;  // matrix-core key of each tile of a padded batch
   const int8_t** d_tilekeys = nullptr;
   uint32_t* d_abar = nullptr;
@@ -260,7 +260,7 @@ void worker_loop(vsp_server* s) {
           sl.h_kid[i] = (uint16_t)k;
           sl.h_idx[i] = sl.h_idx[M + i] = sl.h_idx[2 * M + i] = 0;
         }
-        sl.h_keytab[k] = kset[k] ? kset[k]->bkn : s->ctx->bkn;
+        sl.h_keytab[k] = kset[k] ? kset[k]->bkf : s->ctx->bkf;
         if (padded)
           for (uint64_t t = start[k] / MF_TILE; t < start[k + 1] / MF_TILE; t++)
             sl.h_tilekeys[t] = kset[k] ? kset[k]->mf_key : s->ctx->mf_key;

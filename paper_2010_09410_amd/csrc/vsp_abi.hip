@@ -1,6 +1,7 @@
 // C ABI of libvsp: status codes, the context, batched / per-gate homomorphic gates,
 // TRLWE-output bootstrapping and the test entry points. CMUX memory, circuits and the
 // server have their own files.
+#include <cmath>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -135,15 +136,34 @@ static bool make_tables(std::vector<u64>& tw) {
   return true;
 }
 
-vsp_status upload_keys(const vsp_context* ctx, const uint32_t* bk_host, const uint32_t* ksk_host, uint64_t** bkn,
+// Lane tables of the complex transform (fft.h): lane (u, c) holds residue u's half c, whose root
+// has the angle beta = angle(z_u) / 2 + c / 2 turns; entry e of pass 2 has the angle
+// beta / 2^(s+1) + f, and entry 8 is sqrt(z_u).
+static std::vector<c64> make_fft_tables() {
+  const long double twopi = 6.283185307179586476925286766559005768L;
+  static const struct { int s; long double f; } kEntry[8] = {{0, 0.0L},      {1, 0.0L},      {2, 0.0L},       {2, 1 / 8.0L},
+                                                             {3, 0.0L},      {3, 1 / 8.0L},  {3, 1 / 16.0L},  {3, 3 / 16.0L}};
+  std::vector<c64> t(FFT_TAB_C64);
+  for (int l = 0; l < 32; l++) {
+    const long double half = fft_node(4, l & 15) / 128.0L, beta = half + (l >> 4) / 2.0L;
+    for (int e = 0; e < FFT_TAB; e++) {
+      const long double a = twopi * (e < 8 ? beta / (2 << kEntry[e].s) + kEntry[e].f : half);
+      t[e * 32 + l].x = (double)cosl(a);
+      t[e * 32 + l].y = (double)sinl(a);
+    }
+  }
+  return t;
+}
+
+vsp_status upload_keys(const vsp_context* ctx, const uint32_t* bk_host, const uint32_t* ksk_host, c64** bkf,
                        uint32_t** ksk, int8_t** mf_key, int8_t** ks_mf) {
-  *bkn = nullptr;
+  *bkf = nullptr;
   *ksk = nullptr;
   if (mf_key) *mf_key = nullptr;
   if (ks_mf) *ks_mf = nullptr;
   const size_t bk_words = (size_t)LWE_N * 2 * GADGET_L * 2 * RING_N;
   const size_t ksk_rows = (size_t)RING_N * KS_T * 4;
-  uint64_t* b = nullptr;
+  c64* b = nullptr;
   uint32_t* k = nullptr;
   uint32_t* tmp = nullptr;
   int8_t* E = nullptr;
@@ -154,12 +174,12 @@ vsp_status upload_keys(const vsp_context* ctx, const uint32_t* bk_host, const ui
     return st;
   };
   hipError_t e;
-  if ((e = hipMalloc(&b, (size_t)LWE_N * TRGSW_NTT_U64 * 8)) != hipSuccess) return undo(hip_fail(e, "hipMalloc(bk)"));
+  if ((e = hipMalloc(&b, (size_t)LWE_N * TRGSW_FFT_C64 * sizeof(c64))) != hipSuccess) return undo(hip_fail(e, "hipMalloc(bk)"));
   if ((e = hipMalloc(&k, ksk_rows * (LWE_N + 1) * 4)) != hipSuccess) return undo(hip_fail(e, "hipMalloc(ksk)"));
-  // Bootstrapping key: torus -> NTT domain on the device.
+  // Bootstrapping key: torus -> transform domain on the device.
   if ((e = hipMalloc(&tmp, bk_words * 4)) != hipSuccess) return undo(hip_fail(e, "hipMalloc(bk staging)"));
   e = hipMemcpy(tmp, bk_host, bk_words * 4, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = launch_trgsw_to_ntt(ctx, tmp, b, LWE_N, nullptr);
+  if (e == hipSuccess) e = launch_trgsw_to_fft(ctx, tmp, b, LWE_N, nullptr);
   if (e == hipSuccess && mf_key) {
     e = hipMalloc(&E, mf_key_bytes());
     if (e == hipSuccess) e = launch_mf_key(tmp, E, nullptr);
@@ -180,7 +200,7 @@ vsp_status upload_keys(const vsp_context* ctx, const uint32_t* bk_host, const ui
     if ((e = launch_ks_mfkey(k, KM, nullptr)) != hipSuccess || (e = hipDeviceSynchronize()) != hipSuccess)
       return undo(hip_fail(e, "key-switching key conversion"));
   }
-  *bkn = b;
+  *bkf = b;
   *ksk = k;
   if (mf_key) *mf_key = E;
   if (ks_mf) *ks_mf = KM;
@@ -277,11 +297,15 @@ vsp_status vsp_context_create(const vsp_params* params, const uint32_t* bk_host,
   }
   hipError_t e;
   if ((e = hipMalloc(&ctx->tw, tw.size() * 8)) != hipSuccess) return cleanup(hip_fail(e, "hipMalloc(tw)"));
+  const std::vector<c64> ft = make_fft_tables();
+  if ((e = hipMalloc(&ctx->ftab, ft.size() * sizeof(c64))) != hipSuccess) return cleanup(hip_fail(e, "hipMalloc(tables)"));
+  if ((e = hipMemcpy(ctx->ftab, ft.data(), ft.size() * sizeof(c64), hipMemcpyHostToDevice)) != hipSuccess)
+    return cleanup(hip_fail(e, "upload tables"));
   if ((e = hipMalloc(&ctx->dev_err, 256)) != hipSuccess) return cleanup(hip_fail(e, "hipMalloc(err)"));
   if ((e = hipMemcpy(ctx->tw, tw.data(), tw.size() * 8, hipMemcpyHostToDevice)) != hipSuccess)
     return cleanup(hip_fail(e, "upload twiddles"));
   if ((e = hipMemset(ctx->dev_err, 0, 256)) != hipSuccess) return cleanup(hip_fail(e, "clear flags"));
-  if (vsp_status st = upload_keys(ctx, bk_host, ksk_host, &ctx->bkn, &ctx->ksk, &ctx->mf_key, &ctx->ks_mf))
+  if (vsp_status st = upload_keys(ctx, bk_host, ksk_host, &ctx->bkf, &ctx->ksk, &ctx->mf_key, &ctx->ks_mf))
     return cleanup(st);
   *out = ctx;
   return VSP_OK;
@@ -292,7 +316,7 @@ vsp_status vsp_context_destroy(vsp_context* ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipDeviceSynchronize();
   profile_clear(ctx);
-  for (void* p : {(void*)ctx->bkn, (void*)ctx->ksk, (void*)ctx->mf_key, (void*)ctx->ks_mf, (void*)ctx->tw,
+  for (void* p : {(void*)ctx->bkf, (void*)ctx->ftab, (void*)ctx->ksk, (void*)ctx->mf_key, (void*)ctx->ks_mf, (void*)ctx->tw,
                   (void*)ctx->dev_err,
                   ctx->abar.ptr, ctx->tlwe1.ptr, ctx->ntt_sel.ptr, ctx->mem_a.ptr, ctx->mem_b.ptr, ctx->mem_c.ptr,
                   ctx->mem_d.ptr, ctx->mf_work.ptr})
@@ -444,7 +468,7 @@ vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const ui
   if (B == 0) return VSP_OK;
   VSP_HIP(hipSetDevice(ctx->device));
   if ((s = check_gate_args(ctx, d_ops, d_in0, d_in1, d_out, B, VSP_BATCHED, false))) return s;
-  const size_t key_bytes = (size_t)LWE_N * TRGSW_NTT_U64 * 8;
+  const size_t key_bytes = (size_t)LWE_N * TRGSW_FFT_C64 * sizeof(c64);
   const size_t copy_bytes = copies > 1 ? (size_t)copies * key_bytes : 0;
   size_t free_b = 0, total_b = 0;
   VSP_HIP(hipMemGetInfo(&free_b, &total_b));
@@ -454,8 +478,8 @@ vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const ui
   if ((s = scratch_reserve(ctx, ctx->abar, B * (LWE_N + 1) * 4))) return s;
   if ((s = scratch_reserve(ctx, ctx->tlwe1, B * (RING_N + 1) * 4))) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  uint64_t* keys = nullptr;
-  const uint64_t** d_tab = nullptr;
+  c64* keys = nullptr;
+  const c64** d_tab = nullptr;
   uint16_t* d_kid = nullptr;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   auto undo = [&](vsp_status r) {
@@ -468,12 +492,12 @@ vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const ui
     return r;
   };
   hipError_t e;
-  std::vector<const uint64_t*> tab(copies, ctx->bkn);
+  std::vector<const c64*> tab(copies, ctx->bkf);
   if (copies > 1) {
     if ((e = hipMalloc(&keys, copy_bytes)) != hipSuccess) return undo(hip_fail(e, "hipMalloc(key copies)"));
     for (uint32_t c = 0; c < copies; c++) {
-      tab[c] = keys + (size_t)c * LWE_N * TRGSW_NTT_U64;
-      if ((e = hipMemcpyAsync(keys + (size_t)c * LWE_N * TRGSW_NTT_U64, ctx->bkn, key_bytes, hipMemcpyDeviceToDevice,
+      tab[c] = keys + (size_t)c * LWE_N * TRGSW_FFT_C64;
+      if ((e = hipMemcpyAsync(keys + (size_t)c * LWE_N * TRGSW_FFT_C64, ctx->bkf, key_bytes, hipMemcpyDeviceToDevice,
                               st)) != hipSuccess)
         return undo(hip_fail(e, "key copy"));
     }
@@ -513,7 +537,7 @@ vsp_status vsp_keyset_create(vsp_context* ctx, const uint32_t* bk_host, const ui
   VSP_HIP(hipSetDevice(ctx->device));
   auto* k = new vsp_keyset();
   k->ctx = ctx;
-  if ((s = upload_keys(ctx, bk_host, ksk_host, &k->bkn, &k->ksk, &k->mf_key, &k->ks_mf))) {
+  if ((s = upload_keys(ctx, bk_host, ksk_host, &k->bkf, &k->ksk, &k->mf_key, &k->ks_mf))) {
     delete k;
     return s;
   }
@@ -525,7 +549,7 @@ vsp_status vsp_keyset_destroy(vsp_keyset* k) {
   if (k == nullptr) return VSP_OK;
   (void)hipSetDevice(k->ctx->device);
   (void)hipDeviceSynchronize();
-  for (void* p : {(void*)k->bkn, (void*)k->ksk, (void*)k->mf_key, (void*)k->ks_mf})
+  for (void* p : {(void*)k->bkf, (void*)k->ksk, (void*)k->mf_key, (void*)k->ks_mf})
     if (p) (void)hipFree(p);
   delete k;
   return VSP_OK;

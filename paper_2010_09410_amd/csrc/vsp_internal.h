@@ -10,7 +10,7 @@
 #include <vector>
 
 #include "../../include/vsp.h"
-#include "ntt.h"
+#include "fft.h"
 
 namespace vsp {
 
@@ -89,12 +89,11 @@ constexpr uint64_t kSplitAt[kSplitPts] = {1, 16, 64, 256, 512, 768, 1024, 1280, 
 //    key's byte planes).
 struct Tuning {
   uint64_t br_cap[kBrShapes] = {1024, 2048, 512, 4096, MF_TILE};
-  float br_round_ms[kBrShapes] = {1.0f, 1.482f, 0.75f, 2.33f, 0.337f};
+  float br_round_ms[kBrShapes] = {10.1f, 14.7f, 7.1f, 82.0f, 4.2f};
   // split form, at the sizes kSplitAt: time in the same units as br_round_ms, and row groups
-  // (0: the count that fills the chip, mf_split_groups). The defaults are relative times
-  // measured on an MI355X (one 4-gate-workgroup round = 1).
-  float split_ms[kSplitPts] = {0.114f, 0.190f, 0.246f, 0.355f, 0.505f, 0.670f, 0.857f, 0.916f, 1.253f, 1.333f, 1.399f,
-                               2.180f, 2.530f};
+  // (0: the count that fills the chip, mf_split_groups). The defaults are milliseconds measured
+  // on an MI355X.
+  float split_ms[kSplitPts] = {4.1f, 6.9f, 8.9f, 12.7f, 18.3f, 24.3f, 31.1f, 33.2f, 45.5f, 48.4f, 50.8f, 79.1f, 91.8f};
   int split_groups[kSplitPts] = {24, 12, -6, -6, -2, -3, -2, -1, -2, -2, -2, -2, 1};
   int br_force[kTuneBuckets] = {0, 0, 0, 0, 0, 0, 0};
   int ks_form[kTuneBuckets] = {2, 2, 2, 2, 3, 3, 3};
@@ -168,11 +167,11 @@ struct Profile {
 
 }  // namespace vsp
 
-// A client's key set converted for the device: bootstrapping key in the NTT domain and the
+// A client's key set converted for the device: bootstrapping key in the transform domain and the
 // key-switching key with zero rows (layouts as in vsp_context).
 struct vsp_keyset {
   vsp_context* ctx = nullptr;
-  uint64_t* bkn = nullptr;
+  vsp::c64* bkf = nullptr;
   uint32_t* ksk = nullptr;
   int8_t* mf_key = nullptr;  // byte-plane forms for the matrix-core blind rotation and key switch
   int8_t* ks_mf = nullptr;
@@ -183,8 +182,9 @@ struct vsp_context {
   int cus = 1;                    // compute units of the device
   int8_t* mf_key = nullptr;       // bootstrapping key as balanced-byte Toeplitz rows (matrix-core form)
   int8_t* ks_mf = nullptr;        // key-switching key as balanced bytes in MFMA operand order (key-switch form 3)
-  uint64_t* bkn = nullptr;        // bootstrapping key, NTT domain: [n][TRGSW_NTT_U64]
+  vsp::c64* bkf = nullptr;        // bootstrapping key, transform domain: [n][TRGSW_FFT_C64]
   uint32_t* ksk = nullptr;        // key-switching key [N][t][4][n+1]; digit value 0 points at a zero row
+  vsp::c64* ftab = nullptr;       // lane tables of the complex transform (fft.h)
   uint64_t* tw = nullptr;         // psi_u^j [32][32] then psi_u^-j [32][32]
   int* dev_err = nullptr;         // device error flags
   vsp::Scratch abar, tlwe1, ntt_sel, mem_a, mem_b, mem_c, mem_d, mf_work;
@@ -210,7 +210,7 @@ vsp_status check_no_overlap(const void* a, size_t abytes, const void* b, size_t 
 
 // Converts host keys (BK torus [n][2l][2][N], KSK [N][t][3][n+1]) into freshly allocated device
 // buffers in the kernels' layouts; on failure nothing stays allocated.
-vsp_status upload_keys(const vsp_context* ctx, const uint32_t* bk_host, const uint32_t* ksk_host, uint64_t** bkn,
+vsp_status upload_keys(const vsp_context* ctx, const uint32_t* bk_host, const uint32_t* ksk_host, c64** bkf,
                        uint32_t** ksk, int8_t** mf_key = nullptr, int8_t** ks_mf = nullptr);
 
 // Grows a scratch buffer to at least `bytes` (synchronising the device before freeing).
@@ -234,6 +234,8 @@ hipError_t blind_rotate_capacity(int device, uint64_t (&cap)[kBrShapes]);
 // Torus TRGSW [count][2l][2][N] -> key layout [count][TRGSW_NTT_U64], scaled by 1/N.
 hipError_t launch_trgsw_to_ntt(const vsp_context* ctx, const uint32_t* src, uint64_t* dst, uint64_t count,
                                hipStream_t st);
+// Torus TRGSW [count][2l][2][N] -> the complex transform's key layout [count][TRGSW_FFT_C64].
+hipError_t launch_trgsw_to_fft(const vsp_context* ctx, const uint32_t* src, c64* dst, uint64_t count, hipStream_t st);
 // Gate linear combination + modulus switch (abar [B][n+1]); NOT / invalid ops write out directly.
 // idx0/idx1/idxo (optional) gather inputs and scatter outputs by wire id (stride n+1).
 // With allow_not false, NOT is reported as an invalid opcode (TRLWE-output bootstrapping).
@@ -250,7 +252,7 @@ hipError_t launch_mux_prologue(const uint32_t* sel, const uint32_t* in1, const u
 hipError_t launch_mux_combine(uint32_t* t, uint64_t B, hipStream_t st);
 // Blind rotation of B gates (abar from the prologue). Writes SE_0 (TLWE1 [B][N+1]) and/or
 // the accumulator (TRLWE [B][2][N]). waves: a shape of kBrWaveChoices, <= 0 the tuned choice.
-// bkn: the bootstrapping key to use (NULL: the context's); with keytab non-NULL gate g uses
+// bkf: the bootstrapping key to use (NULL: the context's); with keytab non-NULL gate g uses
 // keytab[kid[g]] instead (device arrays). The matrix-core forms (waves 32 and 33) need the
 // context's own key and a workspace of mf_work_bytes(B, trlwe == NULL) bytes in mf_work;
 // without them the best NTT form for B runs instead.
@@ -258,8 +260,8 @@ hipError_t launch_mux_combine(uint32_t* t, uint64_t B, hipStream_t st);
 // key of each tile's key set, for batches whose key-set ranges start on tile boundaries; with
 // it the matrix-core forms also run batches of other key sets.
 hipError_t launch_blind_rotate(const vsp_context* ctx, const uint8_t* ops, const uint32_t* abar, uint32_t* tlwe1,
-                               uint32_t* trlwe, uint64_t B, int waves, hipStream_t st, const uint64_t* bkn = nullptr,
-                               const uint64_t* const* keytab = nullptr, const uint16_t* kid = nullptr,
+                               uint32_t* trlwe, uint64_t B, int waves, hipStream_t st, const c64* bkf = nullptr,
+                               const c64* const* keytab = nullptr, const uint16_t* kid = nullptr,
                                void* mf_work = nullptr, bool instrument = false,
                                const int8_t* const* tile_mfkeys = nullptr);
 // Matrix-core form (blind_rotate_mfma.hip): key bytes, workspace bytes, key conversion from

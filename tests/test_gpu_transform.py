@@ -1,0 +1,67 @@
+"""The complex float64 transform of the blind rotation: every form returns the exact integers, also for keys whose
+words sit at the ends of their range in patterns that pile up in single transform slots. Tolerance: zero bits (the
+rounding error is proven to stay below one half)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from paper_2010_09410_amd import client
+from paper_2010_09410_amd.device import Context, to_host
+
+pytestmark = pytest.mark.gpu
+N = 1024
+
+
+def extreme_key(pattern):
+    """A bootstrapping key [630][6][2][N] (no encryption of anything) of extreme words."""
+    g = W.rng(77)
+    j = np.arange(N)
+    if pattern == "constant":           # the limb split's largest magnitudes, one sign
+        row = np.full(N, 0x80000000, np.uint32)
+    elif pattern == "alternating":
+        row = np.where(j % 2 == 0, 0x80000000, 0x7FFFFFF7).astype(np.uint32)
+    elif pattern == "wave":             # square wave of the slowest transform frequency
+        row = np.where(np.cos(np.pi * (j + 0.5) / N) >= 0, 0x7FFFFFFF, 0x80000008).astype(np.uint32)
+    else:                               # both ends at random
+        return g.choice(np.array([0x7FFFFFFF, 0x80000000, 0x7FFFFFF8, 0x80000007], np.uint32), size=(630, 6, 2, N))
+    return np.broadcast_to(row, (630, 6, 2, N)).copy()
+
+
+@pytest.mark.parametrize("pattern", ["constant", "alternating", "wave", "random"])
+def test_extreme_keys_equal_oracle_in_every_form(keys, pattern):
+    bk = extreme_key(pattern)
+    g = W.rng(78)
+    B = 3
+    ops = np.array([W.NAND, W.XOR, W.ORNOT], np.uint8)
+    enc = W.tlwe_draws(g, 2 * B)
+    x = client.tlwe_encrypt_bits(keys["s0"], g.integers(0, 2, 2 * B), *enc)
+    ref = oracle.gates(bk, keys["ksk"], ops, x[:B], x[B:])
+    with Context(bk, keys["ksk"]) as ctx:
+        d = ctx.tensor(ops), ctx.tensor(x[:B]), ctx.tensor(x[B:])
+        for form in (3, 4, 8):
+            ctx.set_tuning(B, form, 2)
+            np.testing.assert_array_equal(to_host(ctx.gates(*d)), ref, err_msg=f"{pattern}, form {form}")
+        out, _ = ctx.gates_key_copies(*d, waves=8, copies=2)    # per-gate keys
+        np.testing.assert_array_equal(to_host(out), ref, err_msg=f"{pattern}, key copies")
+        ctx.sync()
+
+
+@pytest.mark.parametrize("B", [1, 3, 4, 5, 8, 9, 13])
+def test_shared_key_workgroups_with_idle_waves(gpu, keys, B):
+    """Batches that leave waves of a workgroup without a gate, and gates that do not bootstrap, in the forms whose
+    workgroups stream the key together."""
+    g = W.rng(79 + B)
+    ops = g.choice(np.array([W.NAND, W.NOT, W.XNOR, W.AND], np.uint8), size=B)
+    x = client.tlwe_encrypt_bits(keys["s0"], g.integers(0, 2, 2 * B), *W.tlwe_draws(g, 2 * B))
+    d = gpu.tensor(ops), gpu.tensor(x[:B]), gpu.tensor(x[B:])
+    _, ks = gpu.tuning(B)
+    outs = []
+    try:
+        for form in (33, 3, 4, 8):
+            gpu.set_tuning(B, form, ks)
+            outs.append(to_host(gpu.gates(*d)))
+    finally:
+        gpu.set_tuning(B, 0, ks)
+    for o in outs[1:]:
+        np.testing.assert_array_equal(o, outs[0])
