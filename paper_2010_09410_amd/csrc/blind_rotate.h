@@ -70,8 +70,8 @@ struct SharedKey {
 // every piece, so a wave without a gate takes part as well (on a zero accumulator). Otherwise gate g
 // reads the key keytab[kid[g]] by itself (clients with their own keys in one launch), or bkf with
 // keytab NULL, and steps whose difference is zero are skipped.
-template <int WAVES, int PER_SIMD, bool SHARED>
-__global__ __launch_bounds__(WAVES * 64, PER_SIMD) void k_blind_rotate(const c64* __restrict__ bkf, const c64* __restrict__ tab,
+template <int WAVES, bool SHARED>
+__global__ __launch_bounds__(WAVES * 64) void k_blind_rotate(const c64* __restrict__ bkf, const c64* __restrict__ tab,
                                                              const uint8_t* __restrict__ ops,
                                                              const u32* __restrict__ abar, u32* __restrict__ tlwe1,
                                                              u32* __restrict__ trlwe, uint64_t B,

@@ -90,7 +90,7 @@ __host__ __device__ constexpr int fft_node(int s, int b) {
   return s == 0 ? 16 : fft_node(s - 1, b >> 1) / 2 + 32 * (b & 1);
 }
 
-// Sixteen coefficients modulo Y^16 - r take four splittings. Block b of splitting s uses the
+// Sixteen coefficients modulo Y^16 - r take four splittings (eight modulo Y^8 - r the first three). Block b of splitting s uses the
 // constant e = (2^s >> 1) + (b >> 1), times i when b is odd (the roots of sibling blocks are a
 // quarter turn apart), so eight constants serve the fifteen blocks. In pass 1, r = i:
 struct FftPass1 {
@@ -132,11 +132,11 @@ __device__ __forceinline__ void fft_join(double& sr, double& si, double& dr, dou
   di = __builtin_fma(wr, ti, -(wi * tr));
 }
 
-template <class W>
-__device__ __forceinline__ void fft_pass(double (&re)[16], double (&im)[16], W constants) {
+template <int M, class W>
+__device__ __forceinline__ void fft_pass(double (&re)[M], double (&im)[M], W constants) {
 #pragma unroll
-  for (int s = 0; s < 4; s++) {
-    const int H = 8 >> s;
+  for (int s = 0; (1 << s) < M; s++) {
+    const int H = (M / 2) >> s;
 #pragma unroll
     for (int b = 0; b < (1 << s); b++) {
       const c64 w = constants(((1 << s) >> 1) + (b >> 1));
@@ -151,11 +151,11 @@ __device__ __forceinline__ void fft_pass(double (&re)[16], double (&im)[16], W c
     }
   }
 }
-template <class W>
-__device__ __forceinline__ void fft_pass_inverse(double (&re)[16], double (&im)[16], W constants) {
+template <int M, class W>
+__device__ __forceinline__ void fft_pass_inverse(double (&re)[M], double (&im)[M], W constants) {
 #pragma unroll
-  for (int s = 3; s >= 0; s--) {
-    const int H = 8 >> s;
+  for (int s = (M == 16 ? 3 : 2); s >= 0; s--) {
+    const int H = (M / 2) >> s;
 #pragma unroll
     for (int b = 0; b < (1 << s); b++) {
       const c64 w = constants(((1 << s) >> 1) + (b >> 1));
@@ -246,6 +246,89 @@ __device__ __forceinline__ void fft_inverse(double (&re)[16], double (&im)[16], 
   for (int q = 0; q < 8; q++) fft_join(re[q], im[q], re[8 + q], im[8 + q], w.x, w.y);
   fft_exchange_inverse(re, reg, l);
   fft_exchange_inverse(im, reg, l);
+  fft_pass_inverse(re, im, FftConst{});
+}
+
+// ------------------------------------------------------------------ one polynomial per wave
+// The same transform on all 64 lanes, for the latency form: lane L holds the coefficients L + 64 t
+// (t = 0..7). Three passes of three splittings each: with Z = X^64 modulo Z^8 - i (constants of
+// pass 1 above), with Y = X^8 modulo Y^8 - z_u, and modulo X^8 - z_{u,u'}; the exchanges give lane
+// 8 u + v the coefficients v + 8 s of residue u, then lane 8 u + u' the eight coefficients of residue
+// (u, u'). The nine splittings are those of the half-wave layout, so a value's place there follows
+// from the path of its splittings: slot s of lane L is entry fft_half_lane(L) of slot pair s.
+// Both exchanges go through 8 KiB of LDS, in words of one complex number placed so that the sixteen
+// lanes of an access phase hit all banks.
+constexpr int FFT8_TAB = 8;                    // lane table: entries 0-3 of pass 2, 4-7 of pass 3
+constexpr int FFT8_TAB_C64 = FFT8_TAB * 64;
+constexpr int FFT8_REGION_C64 = 512;
+__host__ __device__ constexpr int fft_half_lane(int L) { return (L >> 2) + 16 * ((L >> 1) & 1) + 32 * (L & 1); }
+
+struct Fft8Lane {  // a lane's constants of both passes
+  c64 w[FFT8_TAB];
+  __device__ __forceinline__ void load(const c64* tab, int lane) {
+#pragma unroll
+    for (int e = 0; e < FFT8_TAB; e++) w[e] = tab[e * 64 + lane];
+  }
+};
+struct Fft8Pass {
+  const c64* w;
+  __device__ __forceinline__ c64 operator()(int e) const { return w[e]; }
+};
+
+// Register u of lane L -> register s of lane (u, v): place u 64 + (j ^ 8 (u & 1)) for coefficient j.
+__device__ __forceinline__ void fft8_to_rows(double (&re)[8], double (&im)[8], c64* reg, int lane) {
+#pragma unroll
+  for (int u = 0; u < 8; u++) reg[u * 64 + (lane ^ (8 * (u & 1)))] = make_double2(re[u], im[u]);
+  wave_lds_sync();
+  const int u = lane >> 3, v = lane & 7;
+#pragma unroll
+  for (int s = 0; s < 8; s++) {
+    const c64 x = reg[u * 64 + ((v + 8 * s) ^ (8 * (u & 1)))];
+    re[s] = x.x;
+    im[s] = x.y;
+  }
+  wave_lds_sync();
+}
+__device__ __forceinline__ void fft8_from_rows(double (&re)[8], double (&im)[8], c64* reg, int lane) {
+  const int u = lane >> 3, v = lane & 7;
+#pragma unroll
+  for (int s = 0; s < 8; s++) reg[u * 64 + ((v + 8 * s) ^ (8 * (u & 1)))] = make_double2(re[s], im[s]);
+  wave_lds_sync();
+#pragma unroll
+  for (int t = 0; t < 8; t++) {
+    const c64 x = reg[t * 64 + (lane ^ (8 * (t & 1)))];
+    re[t] = x.x;
+    im[t] = x.y;
+  }
+  wave_lds_sync();
+}
+// Within residue u: register a of lane (u, b) -> register b of lane (u, a) (its own inverse): place
+// u 64 + ((8 a + (b ^ a)) ^ 8 (u & 1)).
+__device__ __forceinline__ void fft8_transpose(double (&re)[8], double (&im)[8], c64* reg, int lane) {
+  const int u = lane >> 3, v = lane & 7;
+#pragma unroll
+  for (int a = 0; a < 8; a++) reg[u * 64 + ((8 * a + (v ^ a)) ^ (8 * (u & 1)))] = make_double2(re[a], im[a]);
+  wave_lds_sync();
+#pragma unroll
+  for (int b = 0; b < 8; b++) {
+    const c64 x = reg[u * 64 + ((8 * v + (b ^ v)) ^ (8 * (u & 1)))];
+    re[b] = x.x;
+    im[b] = x.y;
+  }
+  wave_lds_sync();
+}
+__device__ __forceinline__ void fft8_forward(double (&re)[8], double (&im)[8], const Fft8Lane& tab, c64* reg, int lane) {
+  fft_pass(re, im, FftConst{});
+  fft8_to_rows(re, im, reg, lane);
+  fft_pass(re, im, Fft8Pass{tab.w});
+  fft8_transpose(re, im, reg, lane);
+  fft_pass(re, im, Fft8Pass{tab.w + 4});
+}
+__device__ __forceinline__ void fft8_inverse(double (&re)[8], double (&im)[8], const Fft8Lane& tab, c64* reg, int lane) {
+  fft_pass_inverse(re, im, Fft8Pass{tab.w + 4});
+  fft8_transpose(re, im, reg, lane);
+  fft_pass_inverse(re, im, Fft8Pass{tab.w});
+  fft8_from_rows(re, im, reg, lane);
   fft_pass_inverse(re, im, FftConst{});
 }
 
@@ -371,14 +454,20 @@ __device__ __forceinline__ void fft_take_lo(const FftSum& sum, double (&re)[16],
     swap32(im[p], im[p + 8]);
   }
 }
+// The two small products of a packed coefficient: x = lo(a) + 2^22 lo(b) after rounding. Adding
+// 1.5 x 2^52 leaves the bits of the word 0x433 2^52 + 2^51 + lo(a) + 2^22 lo(b); rounding up by half of
+// 2^22 and shifting leaves lo(b) - 2^29 in the low 32 bits.
+__device__ __forceinline__ void fft_unpack(double x, u32& lo_a, u32& lo_b) {
+  const u64 v = __builtin_bit_cast(u64, x + 0x1.8p+52);
+  lo_a = (u32)((int)((u32)v << (32 - FFT_PACK_BITS)) >> (32 - FFT_PACK_BITS));
+  lo_b = (u32)((v + (1u << (FFT_PACK_BITS - 1))) >> FFT_PACK_BITS) + (1u << 29);
+}
+
 // Output coefficient of this half from its own K_hi product hi and the packed product lo (lower
-// lanes): 16 hi + lo(a) in the lower lanes, 16 hi + lo(b) in the upper ones. After adding 1.5 x 2^52 the
-// bits of lo are the word 0x433 2^52 + 2^51 + lo(a) + 2^22 lo(b); rounding up by half of 2^22 and
-// shifting leaves lo(b) - 2^29 in the low 32 bits.
+// lanes): 16 hi + lo(a) in the lower lanes, 16 hi + lo(b) in the upper ones.
 __device__ __forceinline__ u32 fft_combine(u32 hi, double lo) {
-  const u64 v = __builtin_bit_cast(u64, lo + 0x1.8p+52);
-  const u32 a = (u32)((int)((u32)v << (32 - FFT_PACK_BITS)) >> (32 - FFT_PACK_BITS));
-  const u32 b = (u32)((v + (1u << (FFT_PACK_BITS - 1))) >> FFT_PACK_BITS) + (1u << 29);
+  u32 a, b;
+  fft_unpack(lo, a, b);
   const auto own = __builtin_amdgcn_permlane32_swap(a, b, false, false);
   return (hi << FFT_LO_BITS) + own[0];
 }

@@ -200,10 +200,10 @@ hipError_t init_kernel_attributes() {
   const struct {
     const void* fn;
     size_t lds;
-  } k[] = {{reinterpret_cast<const void*>(&k_blind_rotate<4, 1, true>), br_lds_bytes(4, true)},
-           {reinterpret_cast<const void*>(&k_blind_rotate<8, 2, true>), br_lds_bytes(8, true)},
-           {reinterpret_cast<const void*>(&k_blind_rotate<8, 2, false>), br_lds_bytes(8, false)},
-           {reinterpret_cast<const void*>(&k_blind_rotate_wide), brw_lds_bytes()}};
+  } k[] = {{reinterpret_cast<const void*>(&k_blind_rotate<8, true>), br_lds_bytes(8, true)},
+           {reinterpret_cast<const void*>(&k_blind_rotate<8, false>), br_lds_bytes(8, false)},
+           {reinterpret_cast<const void*>(&k_blind_rotate_wide<1, 4>), brw_lds_bytes()},
+           {reinterpret_cast<const void*>(&k_blind_rotate_wide<6, 2>), brw_lds_bytes()}};
   for (const auto& x : k)
     if (hipError_t e = hipFuncSetAttribute(x.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)x.lds)) return e;
   return hipSuccess;
@@ -213,19 +213,19 @@ hipError_t blind_rotate_capacity(int device, uint64_t (&cap)[kBrShapes]) {
   int cus = 0, n4 = 0, n8 = 0, nw = 0;
   hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n4, reinterpret_cast<const void*>(&k_blind_rotate<4, 1, true>), 256,
-                                                     br_lds_bytes(4, true));
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n4, reinterpret_cast<const void*>(&k_blind_rotate_wide<1, 4>),
+                                                     BRW_WAVES * 64, brw_lds_bytes());
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n8, reinterpret_cast<const void*>(&k_blind_rotate<8, 2, true>), 512,
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n8, reinterpret_cast<const void*>(&k_blind_rotate<8, true>), 512,
                                                      br_lds_bytes(8, true));
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nw, reinterpret_cast<const void*>(&k_blind_rotate_wide),
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nw, reinterpret_cast<const void*>(&k_blind_rotate_wide<6, 2>),
                                                      BRW_WAVES * 64, brw_lds_bytes());
   if (e != hipSuccess) return e;
   static_assert(kBrWaveChoices[0] == 4 && kBrWaveChoices[1] == 8 && kBrWaveChoices[2] == 3 && kBrWaveChoices[3] == 32 &&
                     kBrWaveChoices[4] == 33,
                 "shape order");
-  cap[0] = (uint64_t)(n4 > 0 ? n4 : 1) * (uint64_t)cus * 4;
+  cap[0] = (uint64_t)(n4 > 0 ? n4 : 1) * (uint64_t)cus;
   cap[1] = (uint64_t)(n8 > 0 ? n8 : 1) * (uint64_t)cus * 8;
   cap[2] = (uint64_t)(nw > 0 ? nw : 1) * (uint64_t)cus;
   // matrix-core form: one workgroup per compute unit holds half a tile of MF_TILE gates
@@ -251,14 +251,14 @@ hipError_t launch_blind_rotate(const vsp_context* ctx, const uint8_t* ops, const
                                                        tile_mfkeys);
     waves = ctx->tune.br_waves(B, true);
   }
-  if (waves == 3) {
-    hipLaunchKernelGGL(k_blind_rotate_wide, dim3((unsigned)B), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, bkf,
-                       ctx->ftab, ops, abar, tlwe1, trlwe, B, keytab, kid);
+  if (waves == 3 || waves == 4) {
+    auto* kern = waves == 3 ? &k_blind_rotate_wide<6, 2> : &k_blind_rotate_wide<1, 4>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, bkf,
+                       ctx->ftab + FFT_TAB_C64, ops, abar, tlwe1, trlwe, B, keytab, kid);
   } else {
     // one key for all gates: the workgroup shares it; per-gate keys: each wave reads its own
-    auto* kern = keytab ? &k_blind_rotate<8, 2, false> : waves == 4 ? &k_blind_rotate<4, 1, true> : &k_blind_rotate<8, 2, true>;
-    const int w = keytab == nullptr && waves == 4 ? 4 : 8;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((B + w - 1) / w)), dim3(64 * w), br_lds_bytes(w, keytab == nullptr), st, bkf,
+    auto* kern = keytab ? &k_blind_rotate<8, false> : &k_blind_rotate<8, true>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((B + 7) / 8)), dim3(512), br_lds_bytes(8, keytab == nullptr), st, bkf,
                        ctx->ftab, ops, abar, tlwe1, trlwe, B, keytab, kid);
   }
   return hipGetLastError();

@@ -136,20 +136,32 @@ static bool make_tables(std::vector<u64>& tw) {
   return true;
 }
 
-// Lane tables of the complex transform (fft.h): lane (u, c) holds residue u's half c, whose root
-// has the angle beta = angle(z_u) / 2 + c / 2 turns; entry e of pass 2 has the angle
-// beta / 2^(s+1) + f, and entry 8 is sqrt(z_u).
+// Lane tables of the complex transform (fft.h). A pass modulo Y^M - r, r at the angle a (in turns),
+// uses the angles a / 2^(s+1) + f; block b after s splittings has the root at fft_leaf(a, s, b).
+// Half-wave layout: lane (u, c) holds half c of residue u, entries 0-7 its pass 2 and 8 sqrt(z_u). Whole-wave
+// layout (after it): lane 8 u + u' holds residue u, then residue (u, u'), four entries each.
+static long double fft_leaf(long double a, int s, int b) {
+  return s == 0 ? a : fft_leaf(a, s - 1, b >> 1) / 2 + (b & 1) * 0.5L;
+}
 static std::vector<c64> make_fft_tables() {
-  const long double twopi = 6.283185307179586476925286766559005768L;
   static const struct { int s; long double f; } kEntry[8] = {{0, 0.0L},      {1, 0.0L},      {2, 0.0L},       {2, 1 / 8.0L},
                                                              {3, 0.0L},      {3, 1 / 8.0L},  {3, 1 / 16.0L},  {3, 3 / 16.0L}};
-  std::vector<c64> t(FFT_TAB_C64);
+  auto unit = [](long double turns) {
+    const long double t = 6.283185307179586476925286766559005768L * turns;
+    return make_double2((double)cosl(t), (double)sinl(t));
+  };
+  auto entry = [&](long double a, int e) { return unit(a / (2 << kEntry[e].s) + kEntry[e].f); };
+  std::vector<c64> t(FFT_TAB_C64 + FFT8_TAB_C64);
   for (int l = 0; l < 32; l++) {
-    const long double half = fft_node(4, l & 15) / 128.0L, beta = half + (l >> 4) / 2.0L;
-    for (int e = 0; e < FFT_TAB; e++) {
-      const long double a = twopi * (e < 8 ? beta / (2 << kEntry[e].s) + kEntry[e].f : half);
-      t[e * 32 + l].x = (double)cosl(a);
-      t[e * 32 + l].y = (double)sinl(a);
+    const long double zu = fft_leaf(0.25L, 4, l & 15);
+    for (int e = 0; e < 8; e++) t[e * 32 + l] = entry(zu / 2 + (l >> 4) * 0.5L, e);
+    t[8 * 32 + l] = unit(zu / 2);
+  }
+  for (int L = 0; L < 64; L++) {
+    const long double zu = fft_leaf(0.25L, 3, L >> 3), zuu = fft_leaf(zu, 3, L & 7);
+    for (int e = 0; e < 4; e++) {
+      t[FFT_TAB_C64 + e * 64 + L] = entry(zu, e);
+      t[FFT_TAB_C64 + (4 + e) * 64 + L] = entry(zuu, e);
     }
   }
   return t;

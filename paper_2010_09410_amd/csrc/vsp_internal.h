@@ -32,12 +32,12 @@ __host__ __device__ inline bool op_bootstraps(uint32_t op) { return op < 8 || op
 // Device-side error flags (bits), read back by vsp_context_sync.
 constexpr int DEVERR_BAD_OP = 1;
 
-// Blind-rotation forms: 4 or 8 gates per workgroup at one wave per gate, 3 for one gate per
-// workgroup on three waves (the latency form), 32 for the matrix-core form (int8 MFMA products
-// over tiles of MF_TILE gates, one workgroup per tile and output polynomial, one launch per
-// step), and 33 for its split form (the products of a step cut into workgroups per tile,
-// output polynomial, sub-product and group of TRGSW rows, and for single rows also per range
-// of byte planes, for batches too small to fill the chip; two launches per step).
+// Blind-rotation forms: 8 for one wave per gate, eight gates per workgroup and compute unit; 3 and 4
+// for one workgroup of eight waves per gate, one (3) or two (4) of them per compute unit (the
+// latency forms); 32 for the matrix-core form (int8 MFMA products over tiles of MF_TILE gates, one
+// workgroup per tile and output polynomial, one launch per step), and 33 for its split form (the
+// products of a step cut into workgroups per tile, output polynomial, sub-product and group of
+// TRGSW rows, and for single rows also per range of byte planes; two launches per step).
 constexpr int kBrShapes = 5;
 constexpr int kBrWaveChoices[kBrShapes] = {4, 8, 3, 32, 33};
 constexpr int MF_TILE = 32;
@@ -88,8 +88,8 @@ constexpr uint64_t kSplitAt[kSplitPts] = {1, 16, 64, 256, 512, 768, 1024, 1280, 
 //    the j range over workgroups, 3 runs on the matrix cores (one-hot digit rows times the
 //    key's byte planes).
 struct Tuning {
-  uint64_t br_cap[kBrShapes] = {1024, 2048, 512, 4096, MF_TILE};
-  float br_round_ms[kBrShapes] = {10.1f, 14.7f, 7.1f, 82.0f, 4.2f};
+  uint64_t br_cap[kBrShapes] = {512, 2048, 256, 4096, MF_TILE};
+  float br_round_ms[kBrShapes] = {4.95f, 14.7f, 3.6f, 82.0f, 4.2f};
   // split form, at the sizes kSplitAt: time in the same units as br_round_ms, and row groups
   // (0: the count that fills the chip, mf_split_groups). The defaults are milliseconds measured
   // on an MI355X.
