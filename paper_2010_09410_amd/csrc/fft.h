@@ -518,4 +518,51 @@ struct GlobalKey {
   __device__ __forceinline__ void meet() {}
 };
 
+// A key shared by a workgroup's waves, streamed through LDS in pieces of one slot pair (6 KiB, in the
+// order of use over all its TRGSWs): two LDS slots, each thread carrying its share of the next two
+// pieces in registers. While a piece is used, the next one is written to the other slot and the load
+// of the one three on is issued; one barrier per piece. A wave alone would read the whole
+// transformed key, 147 KB a step, through the vector cache for every gate. The threads past a
+// piece's 384 entries load and write the first ones a second time (the same values): waves that
+// branch around it cost more.
+template <int WAVES>
+struct SharedKey {
+  static constexpr int PER = (FFT_PIECE_C64 + WAVES * 64 - 1) / (WAVES * 64);  // 16-byte entries per thread
+  gkey src;    // start of the next piece to load
+  c64* ring;   // [2][FFT_PIECE_C64]
+  int left;    // pieces still to load
+  c64 r[2][PER];  // piece n in r[n mod 2]
+  __device__ __forceinline__ int entry(int q) const {
+    const int i = (int)threadIdx.x + q * WAVES * 64;
+    return i < FFT_PIECE_C64 ? i : i - FFT_PIECE_C64;
+  }
+  __device__ __forceinline__ void load(c64 (&x)[PER]) {
+#pragma unroll
+    for (int q = 0; q < PER; q++) x[q] = gkey_load(src + entry(q));
+    if (--left > 0) src += FFT_PIECE_C64;  // past the end the last piece is loaded again, unused
+  }
+  __device__ __forceinline__ void store(int slot, const c64 (&x)[PER]) {
+#pragma unroll
+    for (int q = 0; q < PER; q++) ring[slot * FFT_PIECE_C64 + entry(q)] = x[q];
+  }
+  __device__ __forceinline__ void start(gkey key, c64* lds, int pieces) {
+    src = key;
+    ring = lds;
+    left = pieces;
+    load(r[0]);
+    store(0, r[0]);
+    load(r[1]);
+    load(r[0]);
+  }
+  __device__ __forceinline__ void half(int, int p, int e, c64 (&v)[FFT_PRODUCTS]) {
+    const c64* s = ring + (p & 1) * FFT_PIECE_C64 + e * FFT_HALF_C64 + (threadIdx.x & 63);
+#pragma unroll
+    for (int q = 0; q < FFT_PRODUCTS; q++) v[q] = s[q * 64];
+    if (e == 0) return;
+    store((p + 1) & 1, r[(p + 1) & 1]);
+    load(r[(p + 1) & 1]);
+  }
+  __device__ __forceinline__ void meet() { __syncthreads(); }
+};
+
 }  // namespace vsp

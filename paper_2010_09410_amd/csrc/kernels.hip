@@ -1,4 +1,4 @@
-// Gate-bootstrapping kernels for gfx950: key conversion to the NTT domain, the gate
+// Gate-bootstrapping kernels for gfx950: key conversion to the transform domain, the gate
 // prologue (linear combination + modulus switch), blind rotation with SampleExtract,
 // identity key switching, and test kernels for the external product and polynomial product.
 #include "vsp_internal.h"
@@ -8,41 +8,6 @@
 namespace vsp {
 
 // ------------------------------------------------------------------ key conversion
-// One wave per (item, round k, output polynomial c): lanes 0-31 transform TRGSW row k,
-// lanes 32-63 row k + 3, both taking column c; results land in the key layout of ntt.h.
-__global__ __launch_bounds__(256) void k_trgsw_to_ntt(const u32* __restrict__ src, u64* __restrict__ dst,
-                                                      const u64* __restrict__ tw, u64 ninv, uint64_t jobs) {
-  __shared__ u32 lds[4 * WAVE_T_U32];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint64_t job = (uint64_t)blockIdx.x * 4 + wave;
-  if (job >= jobs) return;
-  const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
-  const uint64_t item = job / 6;
-  const int rem = (int)(job % 6), k = rem >> 1, c = rem & 1;
-  const int row = k + GADGET_L * h;
-  const u32* poly = src + ((item * 2 * GADGET_L + row) * 2 + c) * RING_N;
-  u64 v[32];
-#pragma unroll
-  for (int t = 0; t < 32; t++) v[t] = poly[l + 32 * t];
-  u32* reg = lds + wave * WAVE_T_U32 + h * TREGION;
-  ntt_forward(v, tw, reg, l);
-  // lanes 0-31 hold row k, lanes 32-63 row k + 3, both for output polynomial c: they become
-  // entries 0 and 1 of lane l + 32 c
-  u64* out = dst + item * TRGSW_NTT_U64 + (size_t)k * 32 * 64 * 2;
-#pragma unroll
-  for (int s = 0; s < 32; s++) out[((size_t)s * 64 + l + 32 * c) * 2 + h] = gl_canon(gl_mul(v[s], ninv));
-}
-
-hipError_t launch_trgsw_to_ntt(const vsp_context* ctx, const uint32_t* src, uint64_t* dst, uint64_t count,
-                               hipStream_t st) {
-  if (count == 0) return hipSuccess;
-  const uint64_t jobs = count * 6;
-  const u64 ninv = gl_powmod_const(RING_N, GL_P - 2);
-  hipLaunchKernelGGL(k_trgsw_to_ntt, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, st, src, dst, ctx->tw, ninv,
-                     jobs);
-  return hipGetLastError();
-}
-
 // One wave per (item, round k, product q): lanes 0-31 transform that product's key polynomial of
 // TRGSW row k, lanes 32-63 of row k + 3; results land in the key layout of fft.h.
 __global__ __launch_bounds__(256) void k_trgsw_to_fft(const u32* __restrict__ src, c64* __restrict__ dst,
@@ -508,28 +473,28 @@ hipError_t launch_keyswitch(const vsp_context* ctx, const uint8_t* ops, const ui
 }
 
 // ------------------------------------------------------------------ test kernels
-__global__ __launch_bounds__(256) void k_ext_product(const u64* __restrict__ Cn, const u32* __restrict__ x,
-                                                     u32* __restrict__ out, const u64* __restrict__ tw, uint64_t J) {
-  __shared__ u32 lds[4 * WAVE_T_U32];
+__global__ __launch_bounds__(256) void k_ext_product(const c64* __restrict__ C, const u32* __restrict__ x,
+                                                     u32* __restrict__ out, const c64* __restrict__ tab, uint64_t J) {
+  __shared__ double lds[4 * FFT_WAVE_F64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t j = (uint64_t)blockIdx.x * 4 + wave;
   if (j >= J) return;
   const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
-  u32* reg = lds + wave * WAVE_T_U32 + h * TREGION;
-  const u32* xp = x + j * 2 * RING_N + h * RING_N;
-  u32 D[32], acc[32];
+  const u32* xp = x + j * 2 * RING_N + h * RING_N + l;
+  GlobalKey key;
+  key.base = (gkey)C + j * TRGSW_FFT_C64 + lane;
+  u32 z[32];
+  fft_external_product([&](int t) { return digit_word(xp[32 * t]); }, key, tab, lds + wave * FFT_WAVE_F64 + h * FFT_REGION,
+                       lane, z);
+  u32* o = out + j * 2 * RING_N + h * RING_N + l;
 #pragma unroll
-  for (int t = 0; t < 32; t++) D[t] = xp[l + 32 * t];
-  external_product(OperandDigits{D}, Cn + j * TRGSW_NTT_U64, tw, tw + 1024, reg, lane, acc);
-  u32* o = out + j * 2 * RING_N + h * RING_N;
-#pragma unroll
-  for (int t = 0; t < 32; t++) o[l + 32 * t] = acc[t];
+  for (int t = 0; t < 32; t++) o[32 * t] = z[t];
 }
 
-hipError_t launch_ext_product(const vsp_context* ctx, const uint64_t* Cn, const uint32_t* x, uint32_t* out, uint64_t J,
+hipError_t launch_ext_product(const vsp_context* ctx, const c64* C, const uint32_t* x, uint32_t* out, uint64_t J,
                               hipStream_t st) {
   if (J == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_ext_product, dim3((unsigned)((J + 3) / 4)), dim3(256), 0, st, Cn, x, out, ctx->tw, J);
+  hipLaunchKernelGGL(k_ext_product, dim3((unsigned)((J + 3) / 4)), dim3(256), 0, st, C, x, out, ctx->ftab, J);
   return hipGetLastError();
 }
 

@@ -1,6 +1,8 @@
 // CMUX Memory (Sec. 8): ROM reads by a packed LUT (CMUX tree + rotation CMUXes), RAM reads
 // by per-bit CMUX trees, and the RAM write (read unit, control unit, write bars, refresh).
 
+#include <algorithm>
+
 #include "vsp_internal.h"
 
 namespace vsp {
@@ -10,153 +12,103 @@ constexpr int TRGSW_WORDS = 2 * GADGET_L * 2 * RING_N;
 
 // ------------------------------------------------------------------ kernels
 // The CMUX kernels run one CMUX chain per wave, WAVES waves per workgroup. The workgroup's
-// LDS holds the twiddle tables, then per wave a polynomial pair (2N u32: lanes 0-31 own the
-// a polynomial, lanes 32-63 the b polynomial, coefficient l + 32 t in lane l) and the wave's
-// two transpose regions. Keeping the pair in LDS instead of registers and reading the
-// gadget digits from it in every round leaves the external product within 256 VGPRs, so a
-// SIMD runs two waves.
-constexpr int MEM_WAVE_U32 = 2 * RING_N + WAVE_T_U32;
-constexpr size_t mem_lds_bytes(int waves) { return 2048 * 8 + (size_t)waves * MEM_WAVE_U32 * 4; }
-
-template <int WAVES>
-__device__ __forceinline__ void stage_twiddles(u64* tws, const u64* __restrict__ tw) {
-  for (int i = threadIdx.x; i < 2048; i += WAVES * 64) tws[i] = tw[i];
-  __syncthreads();
+// LDS holds the transform's lane tables, with SHARED the key ring (fft.h), then per wave the two
+// exchange regions and, for the rotation, a polynomial pair (lanes 0-31 own the a polynomial, lanes
+// 32-63 the b polynomial, coefficient l + 32 t in lane l).
+constexpr size_t mem_lds_bytes(int waves, bool shared, bool pair) {
+  return (size_t)FFT_TAB_C64 * 16 + (shared ? 2 * FFT_PIECE_C64 * 16 : 0) +
+         (size_t)waves * (FFT_WAVE_F64 * 8 + (pair ? 2 * RING_N * 4 : 0));
 }
 
-// z = C (ext) P for the pair P at the start of this wave's LDS area; the wave's transpose
-// regions follow the pair. The product of external_product, with the digits re-read from LDS
-// and every LDS and key address formed anew in each round (from an opaque copy of the lane
-// index), so that none of them stays live across the rounds. KEY_LATE issues a round's first
-// key loads after its forward transform instead of before its digits: fewer live registers
-// during the transform, less latency hidden (the choice that keeps each caller's register
-// spills smallest at 256 VGPRs).
-template <bool KEY_LATE>
-__device__ __forceinline__ void ext_product_lds(u32* wbase, const u64* __restrict__ C, const u64* tws, int lane,
-                                                u32 (&z)[32]) {
-  u64 sum[32];
-#pragma unroll
-  for (int s = 0; s < 32; s++) sum[s] = 0;
-#pragma unroll 1
-  for (int k = 0; k < GADGET_L; k++) {
-    const int ln = opaque_lane(lane);
-    const int li = ln & 31;
-    const u32* p = wbase + (ln >> 5) * RING_N + li;
-    const ulonglong2* key = reinterpret_cast<const ulonglong2*>(C) + (size_t)k * 32 * 64 + ln;
-    ulonglong2 kc[KCH];
-    if (!KEY_LATE) {
-#pragma unroll
-      for (int q = 0; q < KCH; q++) kc[q] = key[q * 64];
-    }
-    u64 x[32];
-    const int sh = 32 - BG_BIT * (k + 1);
-#pragma unroll
-    for (int t = 0; t < 32; t++) x[t] = gadget_digit(p[32 * t], sh);
-    ntt_forward<true>(x, tws, wbase + 2 * RING_N + (ln >> 5) * TREGION, li);
-    if (KEY_LATE) {
-#pragma unroll
-      for (int q = 0; q < KCH; q++) kc[q] = key[q * 64];
-    }
-#pragma unroll
-    for (int c = 0; c < 32 / KCH; c++) {
-      ulonglong2 kn[KCH];
-      if (c + 1 < 32 / KCH) {
-#pragma unroll
-        for (int q = 0; q < KCH; q++) kn[q] = key[(KCH * (c + 1) + q) * 64];
-      }
-#pragma unroll
-      for (int q = 0; q < KCH; q++) {
-        const int s = KCH * c + q;
-        u64 xa, xb;
-        both_halves(x[s], xa, xb);
-        sum[s] = gl_add(sum[s], gl_dot2(xa, kc[q].x, xb, kc[q].y));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (c + 1 < 32 / KCH) {
-#pragma unroll
-        for (int q = 0; q < KCH; q++) kc[q] = kn[q];
-      }
-    }
-  }
-  const int ln = opaque_lane(lane);
-  ntt_inverse_lift(sum, tws + 1024, wbase + 2 * RING_N + (ln >> 5) * TREGION, ln & 31, z);
+template <int WAVES>
+__device__ __forceinline__ void stage_tables(c64* tabs, const c64* __restrict__ tab) {
+  for (int i = threadIdx.x; i < FFT_TAB_C64; i += WAVES * 64) tabs[i] = tab[i];
 }
 
-// One wave per CMUX: out = x0 + C (ext) (x1 - x0).
-template <int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_cmux_tree_level(const u64* __restrict__ sel, uint64_t sel_r_stride,
+// One wave per CMUX: out = x0 + C (ext) (x1 - x0), for the `per` CMUXes of one tree level of each of R
+// reads (job = r per + (blk half + m)). SHARED: a workgroup takes eight CMUXes of one read, which use the
+// same selector and stream it together; a wave past the read's last CMUX repeats that one. Otherwise
+// each wave reads its selector by itself. A level of 65,536 CMUXes reads 147 KB of selector for each:
+// through the caches alone that bounds it.
+template <int WAVES, bool SHARED>
+__global__ __launch_bounds__(WAVES * 64) void k_cmux_tree_level(const c64* __restrict__ sel, uint64_t sel_r_stride,
                                                                 int selbit, const u32* __restrict__ in, uint64_t s_r,
                                                                 uint64_t s_b, u32* __restrict__ out, uint64_t R,
-                                                                uint64_t nb, uint64_t half,
-                                                                const u64* __restrict__ tw) {
-  extern __shared__ u64 lds[];
-  stage_twiddles<WAVES>(lds, tw);
+                                                                uint64_t per, uint64_t half,
+                                                                const c64* __restrict__ tab) {
+  extern __shared__ c64 lds[];
+  c64* ring = lds + FFT_TAB_C64;
+  stage_tables<WAVES>(lds, tab);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint64_t job = (uint64_t)blockIdx.x * WAVES + wave;
-  if (job >= R * nb * half) return;
+  uint64_t r, w;
+  bool live = true;
+  SharedKey<WAVES> shared;
+  if (SHARED) {
+    const uint64_t bpr = (per + WAVES - 1) / WAVES;
+    r = blockIdx.x / bpr;
+    w = (blockIdx.x - r * bpr) * WAVES + wave;
+    live = w < per;
+    if (!live) w = per - 1;
+    shared.start((gkey)sel + (r * sel_r_stride + (uint64_t)selbit) * TRGSW_FFT_C64, ring, FFT_PIECES);
+  } else {
+    const uint64_t job = (uint64_t)blockIdx.x * WAVES + wave;
+    r = job / per;
+    w = job - r * per;
+  }
+  __syncthreads();
+  if (!SHARED && r >= R) return;
   const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
-  const uint64_t m = job % half, rb = job / half, blk = rb % nb, r = rb / nb;
-  const u32* x0 = in + r * s_r + blk * s_b + (2 * m) * TRLWE_WORDS + h * RING_N;
+  const uint64_t blk = w / half, m = w - blk * half;
+  const u32* x0 = in + r * s_r + blk * s_b + (2 * m) * TRLWE_WORDS + h * RING_N + l;
   const u32* x1 = x0 + TRLWE_WORDS;
-  u32* wbase = reinterpret_cast<u32*>(lds + 2048) + wave * MEM_WAVE_U32;
-  u32* buf = wbase + h * RING_N;
-#pragma unroll
-  for (int t = 0; t < 32; t++) buf[l + 32 * t] = x1[l + 32 * t] - x0[l + 32 * t];
-  wave_lds_sync();
+  double* reg = reinterpret_cast<double*>(ring + (SHARED ? 2 * FFT_PIECE_C64 : 0)) + wave * FFT_WAVE_F64 + h * FFT_REGION;
+  auto word = [&](int t) { return digit_word(x1[32 * t] - x0[32 * t]); };
   u32 z[32];
-  ext_product_lds<false>(wbase, sel + (r * sel_r_stride + (uint64_t)selbit) * TRGSW_NTT_U64, lds, lane, z);
-  // the epilogue's addresses are formed anew here rather than kept live across the product
-  const int ln = opaque_lane(lane);
-  const u32* y0 = in + r * s_r + blk * s_b + (2 * m) * TRLWE_WORDS + (ln >> 5) * RING_N + (ln & 31);
-  u32* o = out + job * TRLWE_WORDS + (ln >> 5) * RING_N + (ln & 31);
+  if constexpr (SHARED) {
+    fft_external_product(word, shared, lds, reg, lane, z);
+  } else {
+    GlobalKey key;
+    key.base = (gkey)sel + (r * sel_r_stride + (uint64_t)selbit) * TRGSW_FFT_C64 + lane;
+    fft_external_product(word, key, lds, reg, lane, z);
+  }
+  if (!live) return;
+  u32* o = out + (r * per + w) * TRLWE_WORDS + h * RING_N + l;
 #pragma unroll
-  for (int t = 0; t < 32; t++) o[32 * t] = y0[32 * t] + z[t];
+  for (int t = 0; t < 32; t++) o[32 * t] = x0[32 * t] + z[t];
 }
 
 // One wave per read: R <- CMUX(C_j, R, X^{-w 2^j} R) = R + C_j (ext) (X^{-w 2^j} R - R), j
-// ascending. R lives in the wave's LDS buffer; the digits of the rotation difference are
-// formed from it in every round, and the product is added to it in place.
+// ascending. R lives in the wave's LDS buffer, where the rotated coefficients are read, and the
+// product is added to it in place.
 template <int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_rom_rotate(const u64* __restrict__ sel, uint64_t sel_r_stride,
+__global__ __launch_bounds__(WAVES * 64) void k_rom_rotate(const c64* __restrict__ sel, uint64_t sel_r_stride,
                                                            u32* __restrict__ accbuf, uint64_t R, int rotbits, int w,
-                                                           const u64* __restrict__ tw) {
-  extern __shared__ u64 lds[];
-  stage_twiddles<WAVES>(lds, tw);
+                                                           const c64* __restrict__ tab) {
+  extern __shared__ c64 lds[];
+  stage_tables<WAVES>(lds, tab);
+  __syncthreads();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t r = (uint64_t)blockIdx.x * WAVES + wave;
   if (r >= R) return;
   const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
-  u32* wbase = reinterpret_cast<u32*>(lds + 2048) + wave * MEM_WAVE_U32;
+  double* wbase = reinterpret_cast<double*>(lds + FFT_TAB_C64) + wave * (FFT_WAVE_F64 + RING_N);
+  double* reg = wbase + h * FFT_REGION;
+  u32* accs = reinterpret_cast<u32*>(wbase + FFT_WAVE_F64) + h * RING_N;
   u32* p = accbuf + r * TRLWE_WORDS + h * RING_N;
-  {
-    u32* accs = wbase + h * RING_N;
 #pragma unroll
-    for (int t = 0; t < 32; t++) accs[l + 32 * t] = p[l + 32 * t];
-  }
+  for (int t = 0; t < 32; t++) accs[l + 32 * t] = p[l + 32 * t];
   wave_lds_sync();
   for (int j = 0; j < rotbits; j++) {
-    const int k = (2 * RING_N - (w << j)) & (2 * RING_N - 1);
-    const int ln = opaque_lane(lane);
-    const int li = ln & 31, hi = ln >> 5;
-    u32* accs = wbase + hi * RING_N;
-    auto digits = [&](int sh, u64 (&x)[32]) {
-#pragma unroll
-      for (int t = 0; t < 32; t++) {
-        const int idx = (li + 32 * t - k) & (2 * RING_N - 1);
-        u32 v = accs[idx & (RING_N - 1)];
-        if (idx & RING_N) v = 0u - v;
-        x[t] = gadget_digit(v - accs[li + 32 * t], sh);
-      }
-    };
+    const int bt = 4 * (l + (w << j));  // the rotation by X^-k reads coefficient i + k
+    GlobalKey key;
+    key.base = (gkey)sel + (r * sel_r_stride + (uint64_t)j) * TRGSW_FFT_C64 + lane;
     u32 z[32];
-    external_product(digits, sel + (r * sel_r_stride + (uint64_t)j) * TRGSW_NTT_U64, lds, lds + 1024,
-                     wbase + 2 * RING_N + hi * TREGION, ln, z);
+    fft_external_product([&](int t) { return rotated_word(accs, bt + 128 * t, accs[l + 32 * t]); }, key, lds, reg, lane, z);
 #pragma unroll
     for (int t = 0; t < 32; t++)
-      __hip_atomic_fetch_add(&accs[li + 32 * t], z[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+      __hip_atomic_fetch_add(&accs[l + 32 * t], z[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     wave_lds_sync();
   }
-  const u32* accs = wbase + h * RING_N;
 #pragma unroll
   for (int t = 0; t < 32; t++) p[l + 32 * t] = accs[l + 32 * t];
 }
@@ -188,52 +140,43 @@ __global__ __launch_bounds__(256) void k_ram_control(const u32* __restrict__ acc
 // One wave per write bar (bit i, address A): y = u_i; for d < v: y = CMUX(s_d, R[i][A], y)
 // = R[i][A] + s_d (ext) (y - R[i][A]) with s_d = C_d (bit d of A is 1) or G - C_d (0);
 // then SampleExtract_0(y) into tlwe1[i 2^v + A]. The chain runs on the difference
-// D = y - R[i][A]: D starts as u_i - R[i][A], each step replaces it by s_d (ext) D, and the
-// result is y = R[i][A] + D. D lives in the wave's LDS buffer.
+// D = y - R[i][A]: D starts as u_i - R[i][A], each step replaces it by s_d (ext) D (in registers: a
+// product leaves every lane the coefficients it takes next), and the result is y = R[i][A] + D.
 template <int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_ram_bars(const u64* __restrict__ sel, const u64* __restrict__ selneg,
+__global__ __launch_bounds__(WAVES * 64) void k_ram_bars(const c64* __restrict__ sel, const c64* __restrict__ selneg,
                                                          const u32* __restrict__ ram, const u32* __restrict__ u,
                                                          u32* __restrict__ tlwe1, int v, int w,
-                                                         const u64* __restrict__ tw) {
-  extern __shared__ u64 lds[];
-  stage_twiddles<WAVES>(lds, tw);
+                                                         const c64* __restrict__ tab) {
+  extern __shared__ c64 lds[];
+  stage_tables<WAVES>(lds, tab);
+  __syncthreads();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t bar = (uint64_t)blockIdx.x * WAVES + wave;
   if (bar >= ((uint64_t)w << v)) return;
   const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
   const uint64_t i = bar >> v, A = bar & ((1ull << v) - 1);
-  u32* wbase = reinterpret_cast<u32*>(lds + 2048) + wave * MEM_WAVE_U32;
-  u32* buf = wbase + h * RING_N;
-  const u32* old = ram + bar * TRLWE_WORDS + h * RING_N;
-  const u32* ui = u + i * TRLWE_WORDS + h * RING_N;
+  double* reg = reinterpret_cast<double*>(lds + FFT_TAB_C64) + wave * FFT_WAVE_F64 + h * FFT_REGION;
+  const u32* old = ram + bar * TRLWE_WORDS + h * RING_N + l;
+  const u32* ui = u + i * TRLWE_WORDS + h * RING_N + l;
+  u32 z[32];
 #pragma unroll
-  for (int t = 0; t < 32; t++) buf[l + 32 * t] = ui[l + 32 * t] - old[l + 32 * t];
-  wave_lds_sync();
+  for (int t = 0; t < 32; t++) z[t] = ui[32 * t] - old[32 * t];
   for (int d = 0; d < v; d++) {
-    const u64* C = (((A >> d) & 1) ? sel : selneg) + (size_t)d * TRGSW_NTT_U64;
-    u32 z[32];
-    ext_product_lds<true>(wbase, C, lds, lane, z);
-    // a lane reads and writes only its own coefficients of D
-#pragma unroll
-    for (int t = 0; t < 32; t++) buf[l + 32 * t] = z[t];
-    wave_lds_sync();
+    GlobalKey key;
+    key.base = (gkey)(((A >> d) & 1) ? sel : selneg) + (size_t)d * TRGSW_FFT_C64 + lane;
+    fft_external_product([&](int t) { return digit_word(z[t]); }, key, lds, reg, lane, z);
   }
-  const int ln = opaque_lane(lane);  // addresses formed anew, not kept live across the chain
-  const int li = ln & 31;
-  const u32* cell = ram + bar * TRLWE_WORDS + (ln >> 5) * RING_N;
-  const u32* dfin = wbase + (ln >> 5) * RING_N;
-  u32 y[32];
 #pragma unroll
-  for (int t = 0; t < 32; t++) y[t] = cell[li + 32 * t] + dfin[li + 32 * t];
+  for (int t = 0; t < 32; t++) z[t] += old[32 * t];
   u32* out = tlwe1 + bar * (RING_N + 1);
   if (h == 0) {
 #pragma unroll
     for (int t = 0; t < 32; t++) {
       const int j = l + 32 * t;
-      out[(RING_N - j) & (RING_N - 1)] = (j == 0) ? y[t] : 0u - y[t];
+      out[(RING_N - j) & (RING_N - 1)] = (j == 0) ? z[t] : 0u - z[t];
     }
   } else if (l == 0) {
-    out[RING_N] = y[0];
+    out[RING_N] = z[0];
   }
 }
 
@@ -265,45 +208,45 @@ static unsigned blocks_for(uint64_t n, int per) { return (unsigned)((n + per - 1
 // holds one workgroup) for wide launches, one wave per workgroup for narrow ones, where
 // spreading the few chains over all CUs shortens the launch.
 hipError_t init_memory_kernel_attributes() {
-  const void* fns[] = {reinterpret_cast<const void*>(&k_cmux_tree_level<8>),
-                       reinterpret_cast<const void*>(&k_rom_rotate<8>),
-                       reinterpret_cast<const void*>(&k_ram_bars<8>),
-                       reinterpret_cast<const void*>(&k_cmux_tree_level<1>),
-                       reinterpret_cast<const void*>(&k_rom_rotate<1>),
-                       reinterpret_cast<const void*>(&k_ram_bars<1>)};
-  for (int f = 0; f < 6; f++) {
-    const hipError_t e =
-        hipFuncSetAttribute(fns[f], hipFuncAttributeMaxDynamicSharedMemorySize, (int)mem_lds_bytes(f < 3 ? 8 : 1));
-    if (e != hipSuccess) return e;
-  }
+  const struct {
+    const void* fn;
+    size_t lds;
+  } k[] = {{reinterpret_cast<const void*>(&k_cmux_tree_level<8, true>), mem_lds_bytes(8, true, false)},
+           {reinterpret_cast<const void*>(&k_cmux_tree_level<1, false>), mem_lds_bytes(1, false, false)},
+           {reinterpret_cast<const void*>(&k_rom_rotate<8>), mem_lds_bytes(8, false, true)},
+           {reinterpret_cast<const void*>(&k_rom_rotate<1>), mem_lds_bytes(1, false, true)},
+           {reinterpret_cast<const void*>(&k_ram_bars<8>), mem_lds_bytes(8, false, false)},
+           {reinterpret_cast<const void*>(&k_ram_bars<1>), mem_lds_bytes(1, false, false)}};
+  for (const auto& x : k)
+    if (hipError_t e = hipFuncSetAttribute(x.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)x.lds)) return e;
   return hipSuccess;
 }
 
 static bool wide_launch(const vsp_context* ctx, uint64_t chains) { return chains >= 8ull * (uint64_t)ctx->cus; }
 
-hipError_t launch_cmux_tree_level(const vsp_context* ctx, const uint64_t* sel, uint64_t sel_r_stride, int selbit,
+hipError_t launch_cmux_tree_level(const vsp_context* ctx, const c64* sel, uint64_t sel_r_stride, int selbit,
                                   const uint32_t* in, uint64_t s_r, uint64_t s_b, uint32_t* out, uint64_t R,
                                   uint64_t nb, uint64_t W, hipStream_t st) {
-  const uint64_t jobs = R * nb * (W / 2);
-  if (jobs == 0) return hipSuccess;
-  if (wide_launch(ctx, jobs))
-    hipLaunchKernelGGL(k_cmux_tree_level<8>, dim3(blocks_for(jobs, 8)), dim3(512), mem_lds_bytes(8), st, sel,
-                       sel_r_stride, selbit, in, s_r, s_b, out, R, nb, W / 2, ctx->tw);
+  const uint64_t per = nb * (W / 2);
+  if (R * per == 0) return hipSuccess;
+  // eight CMUXes of a read share its selector while that leaves enough workgroups
+  if (per >= 8 && wide_launch(ctx, R * per))
+    hipLaunchKernelGGL((k_cmux_tree_level<8, true>), dim3((unsigned)(R * ((per + 7) / 8))), dim3(512),
+                       mem_lds_bytes(8, true, false), st, sel, sel_r_stride, selbit, in, s_r, s_b, out, R, per, W / 2,
+                       ctx->ftab);
   else
-    hipLaunchKernelGGL(k_cmux_tree_level<1>, dim3(blocks_for(jobs, 1)), dim3(64), mem_lds_bytes(1), st, sel,
-                       sel_r_stride, selbit, in, s_r, s_b, out, R, nb, W / 2, ctx->tw);
+    hipLaunchKernelGGL((k_cmux_tree_level<1, false>), dim3(blocks_for(R * per, 1)), dim3(64),
+                       mem_lds_bytes(1, false, false), st, sel, sel_r_stride, selbit, in, s_r, s_b, out, R, per, W / 2,
+                       ctx->ftab);
   return hipGetLastError();
 }
 
-hipError_t launch_rom_rotate(const vsp_context* ctx, const uint64_t* sel, uint64_t sel_r_stride, uint32_t* acc,
+hipError_t launch_rom_rotate(const vsp_context* ctx, const c64* sel, uint64_t sel_r_stride, uint32_t* acc,
                              uint64_t R, int rotbits, int w, hipStream_t st) {
   if (R == 0 || rotbits == 0) return hipSuccess;
-  if (wide_launch(ctx, R))
-    hipLaunchKernelGGL(k_rom_rotate<8>, dim3(blocks_for(R, 8)), dim3(512), mem_lds_bytes(8), st, sel, sel_r_stride,
-                       acc, R, rotbits, w, ctx->tw);
-  else
-    hipLaunchKernelGGL(k_rom_rotate<1>, dim3(blocks_for(R, 1)), dim3(64), mem_lds_bytes(1), st, sel, sel_r_stride,
-                       acc, R, rotbits, w, ctx->tw);
+  const int waves = wide_launch(ctx, R) ? 8 : 1;
+  hipLaunchKernelGGL(waves == 8 ? &k_rom_rotate<8> : &k_rom_rotate<1>, dim3(blocks_for(R, waves)), dim3(64 * waves),
+                     mem_lds_bytes(waves, false, true), st, sel, sel_r_stride, acc, R, rotbits, w, ctx->ftab);
   return hipGetLastError();
 }
 
@@ -319,15 +262,12 @@ hipError_t launch_ram_control(const uint32_t* acc2, uint32_t* u, int w, hipStrea
   return hipGetLastError();
 }
 
-hipError_t launch_ram_bars(const vsp_context* ctx, const uint64_t* sel, const uint64_t* selneg, const uint32_t* ram,
+hipError_t launch_ram_bars(const vsp_context* ctx, const c64* sel, const c64* selneg, const uint32_t* ram,
                            const uint32_t* u, uint32_t* tlwe1, int v, int w, hipStream_t st) {
   const uint64_t bars = (uint64_t)w << v;
-  if (wide_launch(ctx, bars))
-    hipLaunchKernelGGL(k_ram_bars<8>, dim3(blocks_for(bars, 8)), dim3(512), mem_lds_bytes(8), st, sel, selneg, ram, u,
-                       tlwe1, v, w, ctx->tw);
-  else
-    hipLaunchKernelGGL(k_ram_bars<1>, dim3(blocks_for(bars, 1)), dim3(64), mem_lds_bytes(1), st, sel, selneg, ram, u,
-                       tlwe1, v, w, ctx->tw);
+  const int waves = wide_launch(ctx, bars) ? 8 : 1;
+  hipLaunchKernelGGL(waves == 8 ? &k_ram_bars<8> : &k_ram_bars<1>, dim3(blocks_for(bars, waves)), dim3(64 * waves),
+                     mem_lds_bytes(waves, false, false), st, sel, selneg, ram, u, tlwe1, v, w, ctx->ftab);
   return hipGetLastError();
 }
 
@@ -352,7 +292,7 @@ static int ilog2(uint64_t x) {
 // CMUX trees of `levels` levels over `nb` blocks per read (cells [nb][2^levels] shared by all
 // reads, block stride s_b words), address bits `bit0`.. of each read's selectors. Leaves
 // the R * nb results in *result (one of two ping-pong buffers a, b).
-static hipError_t run_trees(const vsp_context* ctx, const uint64_t* sel, uint64_t sel_r_stride, int bit0, int levels,
+static hipError_t run_trees(const vsp_context* ctx, const c64* sel, uint64_t sel_r_stride, int bit0, int levels,
                             const uint32_t* cells, uint64_t s_b, uint64_t R, uint64_t nb, uint32_t* a, uint32_t* b,
                             uint32_t** result, hipStream_t st) {
   uint64_t W = 1ull << levels;
@@ -401,6 +341,11 @@ static hipError_t launch_ram_control_tables(uint32_t* idx, uint8_t* ops, uint32_
   return hipGetLastError();
 }
 
+// Reads per launch sequence: at most 2^14 transformed selectors (2.4 GB of scratch) at a time.
+static uint64_t read_chunk(uint64_t R, uint32_t v) {
+  return std::min<uint64_t>(R, std::max<uint64_t>(1, (1ull << 14) / v));
+}
+
 }  // namespace vsp
 
 using namespace vsp;
@@ -425,23 +370,28 @@ vsp_status vsp_rom_read(vsp_context* ctx, const uint32_t* d_rom, uint32_t P, con
   if ((s = check_device_range(ctx, d_out, out_b, "d_out"))) return s;
   if ((s = check_no_overlap(d_out, out_b, d_rom, rom_b, "d_out and d_rom"))) return s;
   if ((s = check_no_overlap(d_out, out_b, d_addr, addr_b, "d_out and d_addr"))) return s;
-  const uint64_t half = P > 1 ? P / 2 : 1;
-  if ((s = scratch_reserve(ctx, ctx->ntt_sel, (size_t)R * v * TRGSW_NTT_U64 * 8))) return s;
-  if ((s = scratch_reserve(ctx, ctx->mem_a, (size_t)R * half * TRLWE_WORDS * 4))) return s;
-  if ((s = scratch_reserve(ctx, ctx->mem_b, (size_t)R * half * TRLWE_WORDS * 4))) return s;
-  if ((s = scratch_reserve(ctx, ctx->tlwe1, (size_t)R * w * (RING_N + 1) * 4))) return s;
+  const uint64_t half = P > 1 ? P / 2 : 1, chunk = read_chunk(R, v);
+  if ((s = scratch_reserve(ctx, ctx->sel, (size_t)chunk * v * TRGSW_FFT_C64 * sizeof(c64)))) return s;
+  if ((s = scratch_reserve(ctx, ctx->mem_a, (size_t)chunk * half * TRLWE_WORDS * 4))) return s;
+  if ((s = scratch_reserve(ctx, ctx->mem_b, (size_t)chunk * half * TRLWE_WORDS * 4))) return s;
+  if ((s = scratch_reserve(ctx, ctx->tlwe1, (size_t)chunk * w * (RING_N + 1) * 4))) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  uint64_t* sel = static_cast<uint64_t*>(ctx->ntt_sel.ptr);
-  hipError_t e;
-  if ((e = launch_trgsw_to_ntt(ctx, d_addr, sel, R * v, st)) != hipSuccess) return hip_fail(e, "selector conversion");
-  uint32_t* acc = nullptr;
-  if ((e = run_trees(ctx, sel, v, rotbits, (int)(v - rotbits), d_rom, 0, R, 1, static_cast<uint32_t*>(ctx->mem_a.ptr),
-                     static_cast<uint32_t*>(ctx->mem_b.ptr), &acc, st)) != hipSuccess)
-    return hip_fail(e, "ROM tree");
-  if ((e = launch_rom_rotate(ctx, sel, v, acc, R, rotbits, (int)w, st)) != hipSuccess) return hip_fail(e, "ROM rotate");
+  c64* sel = static_cast<c64*>(ctx->sel.ptr);
   uint32_t* t1 = static_cast<uint32_t*>(ctx->tlwe1.ptr);
-  if ((e = launch_sample_extract(acc, t1, R, (int)w, st)) != hipSuccess) return hip_fail(e, "sample extract");
-  if ((e = launch_keyswitch(ctx, nullptr, t1, nullptr, d_out, R * w, st)) != hipSuccess) return hip_fail(e, "key switch");
+  for (uint64_t r0 = 0; r0 < R; r0 += chunk) {
+    const uint64_t nr = std::min<uint64_t>(chunk, R - r0);
+    hipError_t e;
+    if ((e = launch_trgsw_to_fft(ctx, d_addr + r0 * v * TRGSW_WORDS, sel, nr * v, st)) != hipSuccess)
+      return hip_fail(e, "selector conversion");
+    uint32_t* acc = nullptr;
+    if ((e = run_trees(ctx, sel, v, rotbits, (int)(v - rotbits), d_rom, 0, nr, 1, static_cast<uint32_t*>(ctx->mem_a.ptr),
+                       static_cast<uint32_t*>(ctx->mem_b.ptr), &acc, st)) != hipSuccess)
+      return hip_fail(e, "ROM tree");
+    if ((e = launch_rom_rotate(ctx, sel, v, acc, nr, rotbits, (int)w, st)) != hipSuccess) return hip_fail(e, "ROM rotate");
+    if ((e = launch_sample_extract(acc, t1, nr, (int)w, st)) != hipSuccess) return hip_fail(e, "sample extract");
+    if ((e = launch_keyswitch(ctx, nullptr, t1, nullptr, d_out + r0 * w * (LWE_N + 1), nr * w, st)) != hipSuccess)
+      return hip_fail(e, "key switch");
+  }
   return VSP_OK;
 }
 
@@ -462,22 +412,29 @@ vsp_status vsp_ram_read(vsp_context* ctx, const uint32_t* d_ram, uint32_t v, uin
   if ((s = check_device_range(ctx, d_out, out_b, "d_out"))) return s;
   if ((s = check_no_overlap(d_out, out_b, d_ram, ram_b, "d_out and d_ram"))) return s;
   if ((s = check_no_overlap(d_out, out_b, d_addr, addr_b, "d_out and d_addr"))) return s;
-  if ((s = scratch_reserve(ctx, ctx->ntt_sel, (size_t)R * v * TRGSW_NTT_U64 * 8))) return s;
-  const size_t level_b = (size_t)R * (cells / 2) * TRLWE_WORDS * 4;
+  const uint64_t chunk = read_chunk(R, v);
+  if ((s = scratch_reserve(ctx, ctx->sel, (size_t)chunk * v * TRGSW_FFT_C64 * sizeof(c64)))) return s;
+  const size_t level_b = (size_t)chunk * (cells / 2) * TRLWE_WORDS * 4;
   if ((s = scratch_reserve(ctx, ctx->mem_a, level_b))) return s;
   if ((s = scratch_reserve(ctx, ctx->mem_b, level_b))) return s;
-  if ((s = scratch_reserve(ctx, ctx->tlwe1, (size_t)R * w * (RING_N + 1) * 4))) return s;
+  if ((s = scratch_reserve(ctx, ctx->tlwe1, (size_t)chunk * w * (RING_N + 1) * 4))) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  uint64_t* sel = static_cast<uint64_t*>(ctx->ntt_sel.ptr);
-  hipError_t e;
-  if ((e = launch_trgsw_to_ntt(ctx, d_addr, sel, R * v, st)) != hipSuccess) return hip_fail(e, "selector conversion");
-  uint32_t* res = nullptr;
-  if ((e = run_trees(ctx, sel, v, 0, (int)v, d_ram, (1ull << v) * TRLWE_WORDS, R, w, static_cast<uint32_t*>(ctx->mem_a.ptr),
-                     static_cast<uint32_t*>(ctx->mem_b.ptr), &res, st)) != hipSuccess)
-    return hip_fail(e, "RAM tree");
+  c64* sel = static_cast<c64*>(ctx->sel.ptr);
   uint32_t* t1 = static_cast<uint32_t*>(ctx->tlwe1.ptr);
-  if ((e = launch_sample_extract(res, t1, R * w, 1, st)) != hipSuccess) return hip_fail(e, "sample extract");
-  if ((e = launch_keyswitch(ctx, nullptr, t1, nullptr, d_out, R * w, st)) != hipSuccess) return hip_fail(e, "key switch");
+  for (uint64_t r0 = 0; r0 < R; r0 += chunk) {
+    const uint64_t nr = std::min<uint64_t>(chunk, R - r0);
+    hipError_t e;
+    if ((e = launch_trgsw_to_fft(ctx, d_addr + r0 * v * TRGSW_WORDS, sel, nr * v, st)) != hipSuccess)
+      return hip_fail(e, "selector conversion");
+    uint32_t* res = nullptr;
+    if ((e = run_trees(ctx, sel, v, 0, (int)v, d_ram, (1ull << v) * TRLWE_WORDS, nr, w,
+                       static_cast<uint32_t*>(ctx->mem_a.ptr), static_cast<uint32_t*>(ctx->mem_b.ptr), &res, st)) !=
+        hipSuccess)
+      return hip_fail(e, "RAM tree");
+    if ((e = launch_sample_extract(res, t1, nr * w, 1, st)) != hipSuccess) return hip_fail(e, "sample extract");
+    if ((e = launch_keyswitch(ctx, nullptr, t1, nullptr, d_out + r0 * w * (LWE_N + 1), nr * w, st)) != hipSuccess)
+      return hip_fail(e, "key switch");
+  }
   return VSP_OK;
 }
 
@@ -499,8 +456,8 @@ vsp_status vsp_ram_write(vsp_context* ctx, uint32_t* d_ram, uint32_t v, uint32_t
   if ((s = check_no_overlap(d_ram, ram_b, d_addr, addr_b, "d_ram and d_addr"))) return s;
   if ((s = check_no_overlap(d_ram, ram_b, d_flag, T0, "d_ram and d_flag"))) return s;
   if ((s = check_no_overlap(d_ram, ram_b, d_data, (size_t)w * T0, "d_ram and d_data"))) return s;
-  // scratch: selectors (C and G - C, NTT), torus G - C, read trees, control, bars, refresh
-  if ((s = scratch_reserve(ctx, ctx->ntt_sel, (size_t)2 * v * TRGSW_NTT_U64 * 8))) return s;
+  // scratch: selectors (C and G - C, transformed), torus G - C, read trees, control, bars, refresh
+  if ((s = scratch_reserve(ctx, ctx->sel, (size_t)2 * v * TRGSW_FFT_C64 * sizeof(c64)))) return s;
   const size_t tree_b = (cells / 2 > 0 ? cells / 2 : 1) * TR;
   if ((s = scratch_reserve(ctx, ctx->mem_a, tree_b))) return s;
   if ((s = scratch_reserve(ctx, ctx->mem_b, tree_b))) return s;
@@ -524,8 +481,8 @@ vsp_status vsp_ram_write(vsp_context* ctx, uint32_t* d_ram, uint32_t v, uint32_t
   void* mfw = matrix ? ctx->mf_work.ptr : nullptr;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* mc = static_cast<char*>(ctx->mem_c.ptr);
-  uint64_t* sel = static_cast<uint64_t*>(ctx->ntt_sel.ptr);
-  uint64_t* selneg = sel + (size_t)v * TRGSW_NTT_U64;
+  c64* sel = static_cast<c64*>(ctx->sel.ptr);
+  c64* selneg = sel + (size_t)v * TRGSW_FFT_C64;
   uint32_t* gneg = reinterpret_cast<uint32_t*>(mc);
   uint32_t* src = reinterpret_cast<uint32_t*>(mc + off_src);
   uint32_t* idx = reinterpret_cast<uint32_t*>(mc + off_idx);
@@ -538,8 +495,8 @@ vsp_status vsp_ram_write(vsp_context* ctx, uint32_t* d_ram, uint32_t v, uint32_t
   hipError_t e;
   // selectors
   if ((e = launch_gadget_minus(d_addr, gneg, v, st)) != hipSuccess) return hip_fail(e, "G - C");
-  if ((e = launch_trgsw_to_ntt(ctx, d_addr, sel, v, st)) != hipSuccess) return hip_fail(e, "selector conversion");
-  if ((e = launch_trgsw_to_ntt(ctx, gneg, selneg, v, st)) != hipSuccess) return hip_fail(e, "selector conversion");
+  if ((e = launch_trgsw_to_fft(ctx, d_addr, sel, v, st)) != hipSuccess) return hip_fail(e, "selector conversion");
+  if ((e = launch_trgsw_to_fft(ctx, gneg, selneg, v, st)) != hipSuccess) return hip_fail(e, "selector conversion");
   // read unit at the address: r_i -> src rows 1 + w + i
   uint32_t* res = nullptr;
   if ((e = run_trees(ctx, sel, v, 0, (int)v, d_ram, (1ull << v) * TRLWE_WORDS, 1, w, static_cast<uint32_t*>(ctx->mem_a.ptr),

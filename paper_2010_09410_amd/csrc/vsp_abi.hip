@@ -330,7 +330,7 @@ vsp_status vsp_context_destroy(vsp_context* ctx) {
   profile_clear(ctx);
   for (void* p : {(void*)ctx->bkf, (void*)ctx->ftab, (void*)ctx->ksk, (void*)ctx->mf_key, (void*)ctx->ks_mf, (void*)ctx->tw,
                   (void*)ctx->dev_err,
-                  ctx->abar.ptr, ctx->tlwe1.ptr, ctx->ntt_sel.ptr, ctx->mem_a.ptr, ctx->mem_b.ptr, ctx->mem_c.ptr,
+                  ctx->abar.ptr, ctx->tlwe1.ptr, ctx->sel.ptr, ctx->mem_a.ptr, ctx->mem_b.ptr, ctx->mem_c.ptr,
                   ctx->mem_d.ptr, ctx->mf_work.ptr})
     if (p) (void)hipFree(p);
   delete ctx;
@@ -662,11 +662,11 @@ vsp_status vsp_debug_external_product(vsp_context* ctx, const uint32_t* d_trgsw,
   if ((s = check_device_range(ctx, d_out, xb, "d_out"))) return s;
   if ((s = check_no_overlap(d_out, xb, d_x, xb, "d_out and d_x"))) return s;
   if ((s = check_no_overlap(d_out, xb, d_trgsw, cb, "d_out and d_trgsw"))) return s;
-  if ((s = scratch_reserve(ctx, ctx->ntt_sel, (size_t)J * TRGSW_NTT_U64 * 8))) return s;
+  if ((s = scratch_reserve(ctx, ctx->sel, (size_t)J * TRGSW_FFT_C64 * sizeof(c64)))) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  uint64_t* cn = static_cast<uint64_t*>(ctx->ntt_sel.ptr);
+  c64* cn = static_cast<c64*>(ctx->sel.ptr);
   hipError_t e;
-  if ((e = launch_trgsw_to_ntt(ctx, d_trgsw, cn, J, st)) != hipSuccess) return hip_fail(e, "trgsw conversion");
+  if ((e = launch_trgsw_to_fft(ctx, d_trgsw, cn, J, st)) != hipSuccess) return hip_fail(e, "trgsw conversion");
   if ((e = launch_ext_product(ctx, cn, d_x, d_out, J, st)) != hipSuccess) return hip_fail(e, "external product");
   return VSP_OK;
 }

@@ -187,7 +187,7 @@ struct vsp_context {
   vsp::c64* ftab = nullptr;       // lane tables of the complex transform (fft.h)
   uint64_t* tw = nullptr;         // psi_u^j [32][32] then psi_u^-j [32][32]
   int* dev_err = nullptr;         // device error flags
-  vsp::Scratch abar, tlwe1, ntt_sel, mem_a, mem_b, mem_c, mem_d, mf_work;
+  vsp::Scratch abar, tlwe1, sel, mem_a, mem_b, mem_c, mem_d, mf_work;
   vsp::Tuning tune;
   mutable vsp::Profile prof;     // instrumentation, also recorded by launches on a const context
   std::mutex mu;                  // serialises scratch growth
@@ -231,9 +231,6 @@ struct ProfScope {
 hipError_t init_kernel_attributes();
 // Gates the device runs at once with each blind-rotation shape (resident groups x CUs x waves).
 hipError_t blind_rotate_capacity(int device, uint64_t (&cap)[kBrShapes]);
-// Torus TRGSW [count][2l][2][N] -> key layout [count][TRGSW_NTT_U64], scaled by 1/N.
-hipError_t launch_trgsw_to_ntt(const vsp_context* ctx, const uint32_t* src, uint64_t* dst, uint64_t count,
-                               hipStream_t st);
 // Torus TRGSW [count][2l][2][N] -> the complex transform's key layout [count][TRGSW_FFT_C64].
 hipError_t launch_trgsw_to_fft(const vsp_context* ctx, const uint32_t* src, c64* dst, uint64_t count, hipStream_t st);
 // Gate linear combination + modulus switch (abar [B][n+1]); NOT / invalid ops write out directly.
@@ -296,7 +293,7 @@ hipError_t launch_keyswitch(const vsp_context* ctx, const uint8_t* ops, const ui
                             uint32_t* out, uint64_t B, hipStream_t st, int form = -1, const uint32_t* ksk = nullptr,
                             const int8_t* ks_mf = nullptr);
 // out[j] = C_j (ext) x_j, or with `x0` given: out[j] = x0_j + C_j (ext) (x_j - x0_j).
-hipError_t launch_ext_product(const vsp_context* ctx, const uint64_t* Cn, const uint32_t* x, uint32_t* out,
+hipError_t launch_ext_product(const vsp_context* ctx, const c64* Cn, const uint32_t* x, uint32_t* out,
                               uint64_t J, hipStream_t st);
 hipError_t launch_polymul(const vsp_context* ctx, const int32_t* a, const uint32_t* b, uint32_t* out, uint64_t J,
                           hipStream_t st);
@@ -312,18 +309,18 @@ uint32_t* circuit_wires(vsp_circuit* c);
 hipError_t init_memory_kernel_attributes();
 // One level of CMUX trees: for r < R, blk < nb, m < W/2:
 //   out[(r nb + blk) W/2 + m] = CMUX(sel[r * sel_r_stride + selbit], in[r s_r + blk s_b + 2m], in[.. + 2m + 1]).
-hipError_t launch_cmux_tree_level(const vsp_context* ctx, const uint64_t* sel, uint64_t sel_r_stride, int selbit,
+hipError_t launch_cmux_tree_level(const vsp_context* ctx, const c64* sel, uint64_t sel_r_stride, int selbit,
                                   const uint32_t* in, uint64_t s_r, uint64_t s_b, uint32_t* out, uint64_t R,
                                   uint64_t nb, uint64_t W, hipStream_t st);
 // R <- CMUX(C_j, R, X^{-w 2^j} R) for j < rotbits, per read.
-hipError_t launch_rom_rotate(const vsp_context* ctx, const uint64_t* sel, uint64_t sel_r_stride, uint32_t* acc,
+hipError_t launch_rom_rotate(const vsp_context* ctx, const c64* sel, uint64_t sel_r_stride, uint32_t* acc,
                              uint64_t R, int rotbits, int w, hipStream_t st);
 // SampleExtract_h for h < W of each TRLWE: in [R][2][N] -> out [R][W][N+1].
 hipError_t launch_sample_extract(const uint32_t* in, uint32_t* out, uint64_t R, int W, hipStream_t st);
 // u_i = acc_and[i] + acc_andnot[i] + (0, mu X^0).
 hipError_t launch_ram_control(const uint32_t* acc2, uint32_t* u, int w, hipStream_t st);
 // Write bars: SE_0 of the chained CMUX per (bit i, address A) into tlwe1 [w 2^v][N+1].
-hipError_t launch_ram_bars(const vsp_context* ctx, const uint64_t* sel, const uint64_t* selneg, const uint32_t* ram,
+hipError_t launch_ram_bars(const vsp_context* ctx, const c64* sel, const c64* selneg, const uint32_t* ram,
                            const uint32_t* u, uint32_t* tlwe1, int v, int w, hipStream_t st);
 // out = G - C for TRGSW [count][2l][2][N] (torus), the comparison with a constant 0 bit.
 hipError_t launch_gadget_minus(const uint32_t* C, uint32_t* out, uint64_t count, hipStream_t st);

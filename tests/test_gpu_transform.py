@@ -65,3 +65,44 @@ def test_shared_key_workgroups_with_idle_waves(gpu, keys, B):
         gpu.set_tuning(B, 0, ks)
     for o in outs[1:]:
         np.testing.assert_array_equal(o, outs[0])
+
+
+# operand words whose three gadget digits are all -32 or all 31
+LOW, HIGH = np.uint32(0x7DF7E000), np.uint32(0x7DF7A000)
+
+
+def test_extreme_external_products_equal_oracle(gpu):
+    """Digits and key words at the ends of their ranges, in the sign patterns (constant, alternating, a slow square wave,
+    random) whose products pile up in single coefficients or single transform slots."""
+    g = W.rng(81)
+    j = np.arange(N)
+    signs = [np.ones(N, bool), j % 2 == 0, np.cos(np.pi * (j + 0.5) / N) >= 0, g.integers(0, 2, N) == 1]
+    C, x = [], []
+    for a in signs:
+        for b in signs:
+            key = np.where(a, np.uint32(0x7FFFFFF7), np.uint32(0x80000000))
+            C.append(np.broadcast_to(key, (6, 2, N)))
+            x.append(np.broadcast_to(np.where(b, HIGH, LOW), (2, N)))
+    C, x = np.ascontiguousarray(C), np.ascontiguousarray(x)
+    out = to_host(gpu.debug_external_product(gpu.tensor(C), gpu.tensor(x)))
+    for i in range(len(C)):
+        np.testing.assert_array_equal(out[i], oracle.external_product(C[i], x[i]), err_msg=f"pair {i}")
+
+
+def random_words(gpu, seed, *shape):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randint(-(1 << 31), 1 << 31, shape, generator=gen, device="cuda", dtype=torch.int32)
+
+
+def test_ram_reads_in_chunks_and_shared_selectors(gpu):
+    """Reads beyond one launch sequence (2^14 / v of them) and tree levels whose CMUX count per read is no multiple of
+    eight give what each read gives by itself (one wave per CMUX, pinned by the oracle in test_gpu_memory.py)."""
+    ram, addr = random_words(gpu, 1, 1, 4, 2, N), random_words(gpu, 2, 8200, 2, 6, 2, N)
+    out = to_host(gpu.ram_read(ram, addr))
+    for r in (0, 8191, 8192, 8199):
+        np.testing.assert_array_equal(out[r], to_host(gpu.ram_read(ram, addr[r:r + 1]))[0], err_msg=f"read {r}")
+    ram, addr = random_words(gpu, 3, 5, 8, 2, N), random_words(gpu, 4, 300, 3, 6, 2, N)   # 20, 10, 5 CMUXes per read
+    out = to_host(gpu.ram_read(ram, addr))
+    for r in (0, 7, 299):
+        np.testing.assert_array_equal(out[r], to_host(gpu.ram_read(ram, addr[r:r + 1]))[0], err_msg=f"read {r}")
