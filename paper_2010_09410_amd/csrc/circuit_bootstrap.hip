@@ -6,15 +6,15 @@
 // plus 1/(2 Bg^j), then two private functional key switches to level-1 TRLWE (x -> -s1 x and
 // x -> x) that give TRGSW rows j-1 and l+j-1.
 //
-// Exact level-2 products. A product d(X) K(X) in Z[X]/(X^2048 + 1) with gadget digits |d| <=
-// 2^8 and 64-bit torus key words is computed as two products with the key's 32-bit halves
-// (K = K_lo + 2^32 K_hi): each has integer coefficients below 8 rows x 2048 x 2^8 x 2^32 =
-// 2^54 < p/2, so the wave-level NTT modulo p = 2^64 - 2^32 + 1 of the level-1 path yields them
-// exactly; the low half is lifted to a signed 64-bit integer, the high half mod 2^32, and the
-// torus result is lo + 2^32 hi mod 2^64. Degree 2048 reuses the degree-1024 transform through
-// the even/odd split a(X) = a_e(X^2) + X a_o(X^2): with Y = X^2 (Y^1024 = -1),
-//   (d K)_e = d_e K_e + Y d_o K_o,   (d K)_o = d_e K_o + d_o K_e,
-// products in Z[Y]/(Y^1024 + 1). The key is stored transformed, with Y folded into Y K_o.
+// Level-2 products. A product d(X) K(X) in Z[X]/(X^2048 + 1) with gadget digits |d| <= 2^8 and 64-bit
+// torus key words runs through the complex transform of fft.h, folded to C[X]/(X^1024 - i): the key
+// is split into three signed limbs, K = K_0 + 2^22 K_1 + 2^44 K_2 (mod 2^64, |K_b| <= 2^21), and every
+// limb's product is rounded to the nearest integer. Ten splittings leave a transform within 46 u of
+// its norm (u = 2^-53; 52 u with the turned constants below), the 16 accumulated products of a slot add 16 u
+// and the ten joinings 43 u, so the error of a coefficient is at most 165 u x 8 rows x 2^8 sqrt(2048) x 2^21 sqrt(2048) = 0.17 before
+// rounding: the integers are exact (below 2^43) and the torus words the schoolbook ones.
+#include <vector>
+
 #include "vsp_internal.h"
 
 namespace vsp {
@@ -26,9 +26,14 @@ constexpr int CB_ROWS = 2 * CB_L2;       // level-2 TRGSW rows
 constexpr int CB_T = 12;                 // private key-switch digits
 constexpr int CB_BB = 2;                 // private key-switch base bits
 constexpr int CB_TLWE2 = CB_N2 + 1;
-// Transformed key per (step, row, output o, half-word w): [slot s][lane][2] u64.
-constexpr size_t CB_KEY_BLOCK = (size_t)32 * 64 * 2;
-constexpr size_t CB_KEY_STEP = (size_t)CB_ROWS * 2 * 2 * CB_KEY_BLOCK;
+constexpr int CB_LIMBS = 3;
+constexpr int CB_LIMB_BITS = 22;
+constexpr int CB_PRODUCTS = 2 * CB_LIMBS;  // output o, limb b: product 3 o + b
+constexpr int CB_WAVES = 8;                // waves per job
+// Transformed key in complex numbers, in the order the waves read it: [step][wave w][row][product]
+// [slot 2 w, 2 w + 1][lane].
+constexpr size_t CB_KEY_ROW = (size_t)CB_PRODUCTS * 2 * 64;
+constexpr size_t CB_KEY_STEP = (size_t)CB_WAVES * CB_ROWS * CB_KEY_ROW;
 // Private key-switching keys: [u][k <= N2][p < t][v - 1 < 3][2][N] u32.
 constexpr size_t CB_PKS_ROW = (size_t)2 * RING_N;
 constexpr size_t CB_PKS_U = (size_t)CB_TLWE2 * CB_T * 3 * CB_PKS_ROW;
@@ -39,322 +44,301 @@ constexpr u64 cb_decomp_offset() {
   return o + (1ull << (64 - CB_BG2 * CB_L2 - 1));
 }
 constexpr u64 CB_DECOMP_OFFSET = cb_decomp_offset();
+constexpr u64 CB_DIGIT_FLIP = (1ull << 63) | (1ull << 54) | (1ull << 45) | (1ull << 36);
+static_assert(CB_BG2 == 9 && CB_L2 == 4, "digit fields at bits 63, 54, 45 and 36");
 
-// Exact signed lift of a canonical residue, as a 64-bit two's-complement word.
-__device__ __forceinline__ u64 gl_lift_u64(u64 c) { return c > (GL_P >> 1) ? c - GL_P : c; }
+// ------------------------------------------------------------------ transform of degree 2048
+// One polynomial per wave: lane L holds the complex coefficients L + 64 t (t = 0..15). With Z = X^64 four
+// splittings of Z^16 - i (the constants of fft.h), with Y = X^4 four of Y^16 - z_u, then two of X^4 - z_{u,u'}.
+// The exchanges give lane 4 u + v the coefficients v + 4 s of residue u, then lane 4 u + v the four residues
+// (u, 4 v + k), four coefficients each, through 16 KiB of LDS in words of one complex number, placed
+// so that the sixteen lanes of an access phase hit all banks.
+constexpr int CB_TAB = 8;                  // lane table, see CbTab
+constexpr int CB_REGION_C64 = 1024;
 
-// Inverse transform with the 64-bit lift: out[t] = coefficient l + 32 t of N times the
-// polynomial, the exact integer in (-p/2, p/2) as a two's-complement word (the twist sign
-// of coefficients t >= 1 as in ntt_inverse_lift).
-__device__ __forceinline__ void ntt_inverse_lift64(u64 (&v)[32], const u64* ti, u32* reg, int l, u64 (&out)[32]) {
-  dft32_inverse(v);
-  table_multiply(v, ti, l);
-  transpose_inverse(v, reg, l);
-  dft32_inverse(v);
-  out[0] = gl_lift_u64(gl_canon(v[0]));
+// A lane's constants. Those of pass 2 at the angles a/2, a/4, a/8, a/16 (a the angle of z_u); the others
+// of its eight are the last two turned by 1/8 (and 1/16) of a turn. The residues 4 v + k of pass 3,
+// k = 2 b + c, have the angles n/4 + b/4 + c/2 for the angle n of their common node, and so use
+// n/8 + b/8 (+ c/4, a factor i) and n/16 + b/16 + c/8: entries 4 + b and 6 + b, the latter turned for
+// c = 1. Turning costs four operations where it is used and keeps 32 registers free for the key.
+struct CbTab {
+  c64 w[CB_TAB];
+};
+template <int K>  // K 64ths of a turn
+__device__ __forceinline__ c64 cb_turn(const c64& w) {
+  constexpr double c = cos64(K), s = sin64(K);
+  return make_double2(__builtin_fma(c, w.x, -(s * w.y)), __builtin_fma(c, w.y, s * w.x));
+}
+struct CbPass2 {
+  const c64* w;
+  __device__ __forceinline__ c64 operator()(int e) const {
+    switch (e) {
+      case 0: return w[0];
+      case 1: return w[1];
+      case 2: return w[2];
+      case 3: return cb_turn<8>(w[2]);
+      case 4: return w[3];
+      case 5: return cb_turn<8>(w[3]);
+      case 6: return cb_turn<4>(w[3]);
+      default: return cb_turn<12>(w[3]);
+    }
+  }
+};
+struct CbPass3 {  // residue k = 2 b + c
+  const c64* w;
+  int k;
+  __device__ __forceinline__ c64 operator()(int e) const {
+    if (e == 0) {
+      const c64 x = w[4 + (k >> 1)];
+      return (k & 1) ? make_double2(-x.y, x.x) : x;
+    }
+    return (k & 1) ? cb_turn<8>(w[6 + (k >> 1)]) : w[6 + (k >> 1)];
+  }
+};
+
+__device__ __forceinline__ int cb_place1(int u, int j) { return u * 64 + (j ^ (4 * (u & 3))); }
+__device__ __forceinline__ int cb_place2(int u, int up, int v) { return u * 64 + ((4 * up + (v ^ (up >> 2))) ^ (4 * (u & 3))); }
+
+__device__ __forceinline__ void cb_pass3(double (&re)[16], double (&im)[16], const CbTab& tab, bool inverse) {
 #pragma unroll
-  for (int t = 1; t < 32; t++) out[t] = 0ull - gl_lift_u64(gl_mul_pow2(v[t], 96 - 3 * t));
+  for (int k = 0; k < 4; k++) {
+    double r[4], i[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      r[q] = re[4 * k + q];
+      i[q] = im[4 * k + q];
+    }
+    if (inverse)
+      fft_pass_inverse(r, i, CbPass3{tab.w, k});
+    else
+      fft_pass(r, i, CbPass3{tab.w, k});
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      re[4 * k + q] = r[q];
+      im[4 * k + q] = i[q];
+    }
+  }
+}
+// The exchanges form their LDS places anew from an opaque copy of the lane index, so that none of
+// them stays live across a pass.
+__device__ __forceinline__ void cb_put1(const double (&re)[16], const double (&im)[16], c64* reg, int lane, bool rows) {
+  const int L = opaque_lane(lane), u = L >> 2, v = L & 3;
+#pragma unroll
+  for (int t = 0; t < 16; t++) reg[rows ? cb_place1(u, v + 4 * t) : cb_place1(t, L)] = make_double2(re[t], im[t]);
+  wave_lds_sync();
+}
+__device__ __forceinline__ void cb_get1(double (&re)[16], double (&im)[16], const c64* reg, int lane, bool rows) {
+  const int L = opaque_lane(lane), u = L >> 2, v = L & 3;
+#pragma unroll
+  for (int t = 0; t < 16; t++) {
+    const c64 x = reg[rows ? cb_place1(u, v + 4 * t) : cb_place1(t, L)];
+    re[t] = x.x;
+    im[t] = x.y;
+  }
+  wave_lds_sync();
+}
+// Second exchange: by residue u' of the lane's v (rows), or coefficient s mod 4 of residue 4 v + s / 4.
+__device__ __forceinline__ void cb_put2(const double (&re)[16], const double (&im)[16], c64* reg, int lane, bool rows) {
+  const int L = opaque_lane(lane), u = L >> 2, v = L & 3;
+#pragma unroll
+  for (int s = 0; s < 16; s++)
+    reg[rows ? cb_place2(u, s, v) : cb_place2(u, 4 * v + (s >> 2), s & 3)] = make_double2(re[s], im[s]);
+  wave_lds_sync();
+}
+__device__ __forceinline__ void cb_get2(double (&re)[16], double (&im)[16], const c64* reg, int lane, bool rows) {
+  const int L = opaque_lane(lane), u = L >> 2, v = L & 3;
+#pragma unroll
+  for (int s = 0; s < 16; s++) {
+    const c64 x = reg[rows ? cb_place2(u, s, v) : cb_place2(u, 4 * v + (s >> 2), s & 3)];
+    re[s] = x.x;
+    im[s] = x.y;
+  }
+  wave_lds_sync();
+}
+__device__ __forceinline__ void cb_forward(double (&re)[16], double (&im)[16], const CbTab& tab, c64* reg, int lane) {
+  fft_pass(re, im, FftConst{});
+  cb_put1(re, im, reg, lane, false);
+  cb_get1(re, im, reg, lane, true);
+  fft_pass(re, im, CbPass2{tab.w});
+  cb_put2(re, im, reg, lane, true);
+  cb_get2(re, im, reg, lane, false);
+  cb_pass3(re, im, tab, false);
+}
+// Inverse transform, times 1024.
+__device__ __forceinline__ void cb_inverse(double (&re)[16], double (&im)[16], const CbTab& tab, c64* reg, int lane) {
+  cb_pass3(re, im, tab, true);
+  cb_put2(re, im, reg, lane, false);
+  cb_get2(re, im, reg, lane, true);
+  fft_pass_inverse(re, im, CbPass2{tab.w});
+  cb_put1(re, im, reg, lane, true);
+  cb_get1(re, im, reg, lane, false);
+  fft_pass_inverse(re, im, FftConst{});
 }
 
-// Key conversion: one wave per (step i, row, output o, half-word w). Half h of the wave
-// transforms the h-part (even / odd coefficients) of the key word; lane l of half 0 stores
-// (K_e, Y K_o) and of half 1 (K_o, K_e) for each slot, scaled by 1/1024.
-__global__ __launch_bounds__(256) void k_cb_key(const u64* __restrict__ bk2, u64* __restrict__ dst,
-                                                const u64* __restrict__ tw, u64 ninv, uint64_t jobs) {
-  __shared__ u32 lds[4 * WAVE_T_U32];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+// Limb b of a key word as a signed integer.
+__device__ __forceinline__ int cb_limb(u64 k, int b) {
+  const int l0 = (int)((u32)k << (32 - CB_LIMB_BITS)) >> (32 - CB_LIMB_BITS);
+  if (b == 0) return l0;
+  const int64_t k1 = (int64_t)(k - (u64)(int64_t)l0) >> CB_LIMB_BITS;
+  const int l1 = (int)((u32)k1 << (32 - CB_LIMB_BITS)) >> (32 - CB_LIMB_BITS);
+  return b == 1 ? l1 : (int)((k1 - l1) >> CB_LIMB_BITS);
+}
+
+// Key conversion: one wave per (step i, row, product).
+__global__ __launch_bounds__(256) void k_cb_key(const u64* __restrict__ bk2, c64* __restrict__ dst,
+                                                const c64* __restrict__ tab, uint64_t jobs) {
+  __shared__ c64 lds[4 * CB_REGION_C64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const uint64_t job = (uint64_t)blockIdx.x * 4 + wave;
   if (job >= jobs) return;
-  const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
-  const int w = (int)(job & 1);
-  const uint64_t poly = job >> 1;  // (i * 8 + row) * 2 + o
-  const u64* K = bk2 + poly * CB_N2;
-  u32* reg = lds + wave * WAVE_T_U32 + h * TREGION;
-  u64 v[32], y[32];
+  const uint64_t row = job / CB_PRODUCTS;  // i * 8 + row
+  const int q = (int)(job % CB_PRODUCTS);
+  const u64* K = bk2 + (row * 2 + q / CB_LIMBS) * CB_N2;
+  CbTab t;
 #pragma unroll
-  for (int t = 0; t < 32; t++) {
-    const u64 word = K[2 * (l + 32 * t) + h];
-    v[t] = w ? (word >> 32) : (word & 0xFFFFFFFFull);
-    y[t] = (l == 1 && t == 0) ? 1ull : 0ull;
-  }
-  ntt_forward(v, tw, reg, l);
-  ntt_forward(y, tw, reg, l);
-  u64* out = dst + job * CB_KEY_BLOCK;
+  for (int e = 0; e < CB_TAB; e++) t.w[e] = tab[e * 64 + lane];
+  double re[16], im[16];
 #pragma unroll
-  for (int s = 0; s < 32; s++) {
-    u64 ke, ko;
-    both_halves(v[s], ke, ko);
-    const u64 e0 = h ? ko : ke;
-    const u64 e1 = h ? ke : gl_mul(y[s], ko);
-    out[((size_t)s * 64 + lane) * 2] = gl_canon(gl_mul(e0, ninv));
-    out[((size_t)s * 64 + lane) * 2 + 1] = gl_canon(gl_mul(e1, ninv));
+  for (int s = 0; s < 16; s++) {
+    re[s] = (double)cb_limb(K[lane + 64 * s], q % CB_LIMBS);
+    im[s] = (double)cb_limb(K[lane + 64 * s + CB_N2 / 2], q % CB_LIMBS);
   }
+  cb_forward(re, im, t, lds + wave * CB_REGION_C64, lane);
+  c64* out = dst + (row / CB_ROWS) * CB_KEY_STEP + (row % CB_ROWS) * CB_KEY_ROW + q * 2 * 64 + lane;
+#pragma unroll
+  for (int s = 0; s < 16; s++)  // the inverse's factor 1024 is taken off here (exactly)
+    out[(size_t)(s >> 1) * CB_ROWS * CB_KEY_ROW + (s & 1) * 64] = make_double2(re[s] * 0x1p-10, im[s] * 0x1p-10);
 }
 
-// Level-2 blind rotation, one workgroup of four waves per job (circuit bootstrap c = job / l,
-// gadget level j = job % l + 1), the accumulator in global memory (L2-resident). Per step, for
-// each ACC polynomial h: wave r forms gadget digit r + 1 of X^abar ACC_h - ACC_h (lanes 0-31 the
-// even coefficients, 32-63 the odd ones) and transforms it into its LDS block; then wave
-// q = 2 o + w accumulates, for output o and key half-word w, sum_r (D_e, D_o) x (entries of its
-// lane). After both polynomials, each wave inverts its sums; the high-word waves pass theirs
-// through their own LDS blocks and the low-word waves add lo + 2^32 hi to ACC_o. A wave's
-// transpose region lies in its own LDS block (used before the block is filled, and after it
-// has been read), so a workgroup takes 80 KiB of LDS and two fit on a compute unit. The
-// result is SampleExtract_0 + 1/(2 Bg^j) as a TLWE2.
-constexpr int CB_THREADS = 256;
-constexpr size_t CB_BLOCK_U64 = (size_t)32 * 64;              // one wave's transformed digits: 16 KiB
-constexpr size_t CB_LDS = (4 * CB_BLOCK_U64 + 2048) * 8;       // digit blocks + twiddle tables: 80 KiB
-static_assert((size_t)WAVE_T_U32 <= 2 * CB_BLOCK_U64 && (size_t)2 * CB_N2 / 2 <= 2 * CB_BLOCK_U64,
-              "transpose region and high-word exchange fit in one block");
-constexpr int CB_KCH = 4;  // key slots per chunk of the streamed key
+// Level-2 blind rotation, one workgroup of eight waves per job (circuit bootstrap c = job / l, gadget
+// level j = job % l + 1), one per compute unit. Per step: wave r forms gadget digit r mod 4 + 1 of
+// X^abar ACC_h - ACC_h (h = r / 4) and transforms it into its own 16 KiB of LDS; wave w adds the eight
+// rows' products with the six key polynomials at slots 2 w and 2 w + 1; once every row has been
+// read, the sums take the rows' place, and waves 0-5 invert one each and add it, shifted by its limb,
+// into its output polynomial. The rows and the accumulator fill the 160 KiB of LDS. The key, 786 KB a
+// step, is read once per job, two rows' entries (12 each per lane) ahead of use; what bounds a
+// step is that stream through the vector cache (64 bytes a clock) and the latency of the two
+// transforms. The result is SampleExtract_0 + 1/(2 Bg^j) as a TLWE2.
+constexpr size_t CB_LDS = (size_t)CB_ROWS * CB_REGION_C64 * 16 + 2 * CB_N2 * 8;
+static_assert(CB_ROWS == CB_WAVES && CB_PRODUCTS <= CB_WAVES, "one wave per row and per sum");
 
-__global__ __launch_bounds__(CB_THREADS, 2) void k_cb_rotate(const u64* __restrict__ key, const u64* __restrict__ tw,
-                                                           const u32* __restrict__ in, u64* __restrict__ accbuf,
-                                                           u64* __restrict__ out, int gadget_l, int bgbit) {
-  extern __shared__ u64 cb_lds[];
-  u64* dig = cb_lds;                                           // [4][32][64]
-  u64* tws = dig + 4 * CB_BLOCK_U64;                           // forward then inverse tables
+__global__ __launch_bounds__(CB_WAVES * 64) void k_cb_rotate(const c64* __restrict__ key, const c64* __restrict__ tab,
+                                                            const u32* __restrict__ in, u64* __restrict__ out,
+                                                            int gadget_l, int bgbit) {
+  extern __shared__ c64 cb_lds[];
+  u64* acc = reinterpret_cast<u64*>(cb_lds + CB_ROWS * CB_REGION_C64);  // [2][N2]
   const uint64_t job = blockIdx.x;
   const int j = (int)(job % (uint64_t)gadget_l) + 1;
   const u32* c = in + (job / (uint64_t)gadget_l) * TLWE0;
-  u64* acc = accbuf + job * 2 * CB_N2;                         // [2][N2]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l = lane & 31, half = lane >> 5;
-  u64* myblock = dig + (size_t)wave * CB_BLOCK_U64;
-  u32* reg = reinterpret_cast<u32*>(myblock) + half * TREGION;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane0 = tid & 63;
+  c64* reg = cb_lds + wave * CB_REGION_C64;
   const u64 tvv = 1ull << (63 - bgbit * j);                    // 1/(2 Bg^j)
-  for (int i = tid; i < 2048; i += CB_THREADS) tws[i] = tw[i];
+  CbTab t;
+#pragma unroll
+  for (int e = 0; e < CB_TAB; e++) t.w[e] = tab[e * 64 + lane0];
+  // wait for the table here: a wait left to its first use, inside the loop, would count the key
+  // loads issued since and so wait for those in every step
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  const gkey kbase = (gkey)key + (size_t)wave * CB_ROWS * CB_KEY_ROW + lane0;
+  c64 kr[2][CB_PRODUCTS * 2];
+  auto load_row = [&](int i, int row, c64(&k)[CB_PRODUCTS * 2]) {
+    const gkey p = kbase + (size_t)i * CB_KEY_STEP + row * CB_KEY_ROW;
+#pragma unroll
+    for (int e = 0; e < CB_PRODUCTS * 2; e++) k[e] = gkey_load(p + e * 64);
+  };
+  load_row(0, 0, kr[0]);
+  load_row(0, 1, kr[1]);
   {
     const u32 bbar = ((c[LWE_N] + (1u << 19)) >> 20) & (2 * CB_N2 - 1);
     const int k = (int)((2 * CB_N2 - bbar) & (2 * CB_N2 - 1));
-    for (int m = tid; m < CB_N2; m += CB_THREADS) {
+    for (int m = tid; m < CB_N2; m += CB_WAVES * 64) {
       const bool neg = (m < (k & (CB_N2 - 1))) != (k >= CB_N2);
       acc[m] = 0;
       acc[CB_N2 + m] = neg ? (0ull - tvv) : tvv;
     }
   }
+  u32 c_next = __builtin_amdgcn_readfirstlane(c[0]);
   __syncthreads();
-  const int o = wave >> 1, wd = wave & 1;
   for (int i = 0; i < LWE_N; i++) {
-    const int abar = (int)(((c[i] + (1u << 19)) >> 20) & (2 * CB_N2 - 1));
-    const u64* kstep = key + (size_t)i * CB_KEY_STEP;
-    u64 sum[32];
+    const int abar = (int)(((c_next + (1u << 19)) >> 20) & (2 * CB_N2 - 1));
+    c_next = __builtin_amdgcn_readfirstlane(c[i + 1]);  // (the last one is b)
+    const int lane = opaque_lane(lane0);                // addresses are formed anew in every step
+    double re[16], im[16];
+    // The digit words of X^abar ACC_h - ACC_h (d + the rounding offset, the top bit of each digit field
+    // flipped so that it is a signed field), once for the four rows of a polynomial, in regions 0 and 1.
+    u64* words = reinterpret_cast<u64*>(cb_lds);
 #pragma unroll
-    for (int s = 0; s < 32; s++) sum[s] = 0;
-#pragma unroll 1
-    for (int h = 0; h < 2; h++) {
-      const u64* P = acc + h * CB_N2;
-      {
-        u64 x[32];
-        const int sh = 64 - CB_BG2 * (wave + 1);
-        // the accumulator words come from L2 in four groups of eight coefficients (bounded
-        // registers in flight)
-#pragma unroll
-        for (int t8 = 0; t8 < 32; t8 += 8) {
-#pragma unroll
-          for (int t = t8; t < t8 + 8; t++) {
-            const int m = 2 * (l + 32 * t) + half;
-            const int src = (m - abar) & (2 * CB_N2 - 1);
-            const u64 r = P[src & (CB_N2 - 1)];
-            const u64 d = ((src & CB_N2) ? (0ull - r) : r) - P[m];
-            x[t] = (u64)((int64_t)(((d + CB_DECOMP_OFFSET) >> sh) & ((1u << CB_BG2) - 1)) - (1 << (CB_BG2 - 1)));
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        ntt_forward<true>(x, tws, reg, l);
-#pragma unroll
-        for (int s = 0; s < 32; s++) myblock[(size_t)s * 64 + lane] = x[s];
-      }
-      __syncthreads();
-      // key entries stream in chunks of CB_KCH slots, the next chunk (of this row or the
-      // next) in flight while the current one is used
-      auto key_row = [&](int r) {
-        return reinterpret_cast<const ulonglong2*>(kstep + ((((size_t)(h * CB_L2 + r)) * 2 + o) * 2 + wd) *
-                                                               CB_KEY_BLOCK) + lane;
-      };
-      ulonglong2 kc[CB_KCH];
-      {
-        const ulonglong2* kb = key_row(0);
-#pragma unroll
-        for (int q = 0; q < CB_KCH; q++) kc[q] = kb[q * 64];
-      }
-#pragma unroll 1
-      for (int r = 0; r < CB_L2; r++) {
-        const ulonglong2* kb = key_row(r);
-        const ulonglong2* kb_next = key_row(r + 1 < CB_L2 ? r + 1 : r);
-        const u64* dr = dig + (size_t)r * CB_BLOCK_U64;
-#pragma unroll
-        for (int cc = 0; cc < 32 / CB_KCH; cc++) {
-          ulonglong2 kn[CB_KCH];
-#pragma unroll
-          for (int q = 0; q < CB_KCH; q++)
-            kn[q] = (cc + 1 < 32 / CB_KCH) ? kb[(CB_KCH * (cc + 1) + q) * 64] : kb_next[q * 64];
-#pragma unroll
-          for (int q = 0; q < CB_KCH; q++) {
-            const int sl = CB_KCH * cc + q;
-            sum[sl] = gl_add(sum[sl], gl_dot2(dr[sl * 64 + l], kc[q].x, dr[sl * 64 + 32 + l], kc[q].y));
-          }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int q = 0; q < CB_KCH; q++) kc[q] = kn[q];
-        }
-      }
-      __syncthreads();
-    }
-    u64 z[32];
-    ntt_inverse_lift64(sum, tws + 1024, reg, l, z);
-    // the high word of output o goes through the LDS block of wave 2 o + 1 (its own)
-    u32* xch = reinterpret_cast<u32*>(dig + (size_t)(2 * o + 1) * CB_BLOCK_U64);
-    if (wd == 1) {
-#pragma unroll
-      for (int t = 0; t < 32; t++) xch[2 * (l + 32 * t) + half] = (u32)z[t];
+    for (int q = 0; q < 2 * CB_N2 / (CB_WAVES * 64); q++) {
+      const int m = (opaque_lane(tid) + CB_WAVES * 64 * q) & (CB_N2 - 1);
+      const u64* P = acc + (q / (CB_N2 / (CB_WAVES * 64))) * CB_N2;
+      const int src = m - abar;
+      const u64 raw = P[src & (CB_N2 - 1)], neg = (u64)((int64_t)((int)((u32)src << 20) >> 31));
+      words[tid + CB_WAVES * 64 * q] = ((raw ^ neg) + (CB_DECOMP_OFFSET - P[m] - neg)) ^ CB_DIGIT_FLIP;
     }
     __syncthreads();
-    if (wd == 0) {
-      u64* A = acc + o * CB_N2;
-#pragma unroll
-      for (int t = 0; t < 32; t++) {
-        const int m = 2 * (l + 32 * t) + half;
-        A[m] += z[t] + ((u64)xch[m] << 32);
-      }
-    }
-    __syncthreads();
-  }
-  u64* dst = out + job * CB_TLWE2;
-  for (int m = tid; m < CB_N2; m += CB_THREADS) dst[m] = (m == 0) ? acc[0] : (0ull - acc[CB_N2 - m]);
-  if (tid == 0) dst[CB_N2] = acc[CB_N2] + tvv;
-}
-
-// Latency form of the level-2 blind rotation: one workgroup of eight waves per job, so that a
-// step's eight digit rows are transformed at once (wave w: polynomial h = w / 4, digit
-// w % 4 + 1, into its own LDS block) and the key products are split by polynomial (wave w:
-// output o and half-word wd of c = w % 4 = 2 o + wd over the rows of h = w / 4). The sums of
-// h = 1 then go through the LDS blocks of waves 4-7 to waves 0-3, which invert them and update
-// ACC as in k_cb_rotate. 144 KiB of LDS, one workgroup per compute unit: for batches that the
-// four-wave form would run in a single round anyway, where each step's critical path is then
-// one transform and four rows of key products instead of two and eight.
-constexpr int CBW_THREADS = 512;
-constexpr size_t CBW_LDS = (8 * CB_BLOCK_U64 + 2048) * 8;  // digit blocks + twiddle tables: 144 KiB
-
-__global__ __launch_bounds__(CBW_THREADS, 1) void k_cb_rotate_wide(const u64* __restrict__ key,
-                                                                  const u64* __restrict__ tw,
-                                                                  const u32* __restrict__ in,
-                                                                  u64* __restrict__ accbuf, u64* __restrict__ out,
-                                                                  int gadget_l, int bgbit) {
-  extern __shared__ u64 cb_lds[];
-  u64* dig = cb_lds;                                           // [8][32][64]
-  u64* tws = dig + 8 * CB_BLOCK_U64;                           // forward then inverse tables
-  const uint64_t job = blockIdx.x;
-  const int j = (int)(job % (uint64_t)gadget_l) + 1;
-  const u32* c = in + (job / (uint64_t)gadget_l) * TLWE0;
-  u64* acc = accbuf + job * 2 * CB_N2;                         // [2][N2]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l = lane & 31, half = lane >> 5;
-  u64* myblock = dig + (size_t)wave * CB_BLOCK_U64;
-  u32* reg = reinterpret_cast<u32*>(myblock) + half * TREGION;
-  const u64 tvv = 1ull << (63 - bgbit * j);                    // 1/(2 Bg^j)
-  for (int i = tid; i < 2048; i += CBW_THREADS) tws[i] = tw[i];
-  {
-    const u32 bbar = ((c[LWE_N] + (1u << 19)) >> 20) & (2 * CB_N2 - 1);
-    const int k = (int)((2 * CB_N2 - bbar) & (2 * CB_N2 - 1));
-    for (int m = tid; m < CB_N2; m += CBW_THREADS) {
-      const bool neg = (m < (k & (CB_N2 - 1))) != (k >= CB_N2);
-      acc[m] = 0;
-      acc[CB_N2 + m] = neg ? (0ull - tvv) : tvv;
-    }
-  }
-  __syncthreads();
-  const int h = wave >> 2, cw = wave & 3, o = cw >> 1, wd = cw & 1;
-  for (int i = 0; i < LWE_N; i++) {
-    const int abar = (int)(((c[i] + (1u << 19)) >> 20) & (2 * CB_N2 - 1));
-    const u64* kstep = key + (size_t)i * CB_KEY_STEP;
     {
-      const u64* P = acc + h * CB_N2;
-      u64 x[32];
-      const int sh = 64 - CB_BG2 * (cw + 1);
+      const u64* W = words + (wave / CB_L2) * CB_N2 + lane;
+      const int up = CB_BG2 * (wave % CB_L2);
 #pragma unroll
-      for (int t8 = 0; t8 < 32; t8 += 8) {
+      for (int s = 0; s < 16; s++) {
+        re[s] = (double)((int)(u32)((W[64 * s] << up) >> 32) >> (32 - CB_BG2));
+        im[s] = (double)((int)(u32)((W[64 * s + CB_N2 / 2] << up) >> 32) >> (32 - CB_BG2));
+      }
+    }
+    __syncthreads();
+    cb_forward(re, im, t, reg, lane);
 #pragma unroll
-        for (int t = t8; t < t8 + 8; t++) {
-          const int m = 2 * (l + 32 * t) + half;
-          const int src = (m - abar) & (2 * CB_N2 - 1);
-          const u64 r = P[src & (CB_N2 - 1)];
-          const u64 d = ((src & CB_N2) ? (0ull - r) : r) - P[m];
-          x[t] = (u64)((int64_t)(((d + CB_DECOMP_OFFSET) >> sh) & ((1u << CB_BG2) - 1)) - (1 << (CB_BG2 - 1)));
+    for (int s = 0; s < 16; s++) reg[s * 64 + lane] = make_double2(re[s], im[s]);
+    __syncthreads();
+    {
+      double sr[CB_PRODUCTS][2], si[CB_PRODUCTS][2];
+#pragma unroll
+      for (int q = 0; q < CB_PRODUCTS; q++) sr[q][0] = sr[q][1] = si[q][0] = si[q][1] = 0.0;
+#pragma unroll
+      for (int row = 0; row < CB_ROWS; row++) {
+        const c64 x0 = cb_lds[row * CB_REGION_C64 + (2 * wave) * 64 + lane];
+        const c64 x1 = cb_lds[row * CB_REGION_C64 + (2 * wave + 1) * 64 + lane];
+#pragma unroll
+        for (int q = 0; q < CB_PRODUCTS; q++) {
+          fft_cmac(sr[q][0], si[q][0], x0.x, x0.y, kr[row & 1][2 * q]);
+          fft_cmac(sr[q][1], si[q][1], x1.x, x1.y, kr[row & 1][2 * q + 1]);
         }
+        if (row + 2 < CB_ROWS)
+          load_row(i, row + 2, kr[row & 1]);
+        else
+          load_row(i + 1 < LWE_N ? i + 1 : i, row + 2 - CB_ROWS, kr[row & 1]);
         __builtin_amdgcn_sched_barrier(0);
       }
-      ntt_forward<true>(x, tws, reg, l);
+      __syncthreads();  // every row has been read
 #pragma unroll
-      for (int s = 0; s < 32; s++) myblock[(size_t)s * 64 + lane] = x[s];
+      for (int q = 0; q < CB_PRODUCTS; q++)
+#pragma unroll
+        for (int e = 0; e < 2; e++)
+          cb_lds[q * CB_REGION_C64 + (2 * wave + e) * 64 + lane] = make_double2(sr[q][e], si[q][e]);
     }
     __syncthreads();
-    u64 sum[32];
+    if (wave < CB_PRODUCTS) {
 #pragma unroll
-    for (int s = 0; s < 32; s++) sum[s] = 0;
-    {
-      auto key_row = [&](int r) {
-        return reinterpret_cast<const ulonglong2*>(kstep + ((((size_t)(h * CB_L2 + r)) * 2 + o) * 2 + wd) *
-                                                               CB_KEY_BLOCK) + lane;
-      };
-      ulonglong2 kc[CB_KCH];
-      {
-        const ulonglong2* kb = key_row(0);
-#pragma unroll
-        for (int q = 0; q < CB_KCH; q++) kc[q] = kb[q * 64];
+      for (int s = 0; s < 16; s++) {
+        const c64 x = reg[s * 64 + lane];
+        re[s] = x.x;
+        im[s] = x.y;
       }
-#pragma unroll 1
-      for (int r = 0; r < CB_L2; r++) {
-        const ulonglong2* kb = key_row(r);
-        const ulonglong2* kb_next = key_row(r + 1 < CB_L2 ? r + 1 : r);
-        const u64* dr = dig + (size_t)(h * CB_L2 + r) * CB_BLOCK_U64;
+      wave_lds_sync();
+      cb_inverse(re, im, t, reg, lane);
+      unsigned long long* A = reinterpret_cast<unsigned long long*>(acc + (wave / CB_LIMBS) * CB_N2) + lane;
+      const int up = CB_LIMB_BITS * (wave % CB_LIMBS);
 #pragma unroll
-        for (int cc = 0; cc < 32 / CB_KCH; cc++) {
-          ulonglong2 kn[CB_KCH];
-#pragma unroll
-          for (int q = 0; q < CB_KCH; q++)
-            kn[q] = (cc + 1 < 32 / CB_KCH) ? kb[(CB_KCH * (cc + 1) + q) * 64] : kb_next[q * 64];
-#pragma unroll
-          for (int q = 0; q < CB_KCH; q++) {
-            const int sl = CB_KCH * cc + q;
-            sum[sl] = gl_add(sum[sl], gl_dot2(dr[sl * 64 + l], kc[q].x, dr[sl * 64 + 32 + l], kc[q].y));
-          }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int q = 0; q < CB_KCH; q++) kc[q] = kn[q];
-        }
-      }
-    }
-    __syncthreads();  // every digit block is read
-    if (h == 1) {
-#pragma unroll
-      for (int s = 0; s < 32; s++) myblock[(size_t)s * 64 + lane] = sum[s];
-    }
-    __syncthreads();
-    u64 z[32];
-    u32* xch = reinterpret_cast<u32*>(dig + (size_t)(2 * o + 1) * CB_BLOCK_U64);
-    if (h == 0) {
-      const u64* other = dig + (size_t)(4 + cw) * CB_BLOCK_U64;
-#pragma unroll
-      for (int s = 0; s < 32; s++) sum[s] = gl_add(sum[s], other[(size_t)s * 64 + lane]);
-      ntt_inverse_lift64(sum, tws + 1024, reg, l, z);
-      // the high word of output o goes through the LDS block of wave 2 o + 1 (its own)
-      if (wd == 1) {
-#pragma unroll
-        for (int t = 0; t < 32; t++) xch[2 * (l + 32 * t) + half] = (u32)z[t];
-      }
-    }
-    __syncthreads();
-    if (h == 0 && wd == 0) {
-      u64* A = acc + o * CB_N2;
-#pragma unroll
-      for (int t = 0; t < 32; t++) {
-        const int m = 2 * (l + 32 * t) + half;
-        A[m] += z[t] + ((u64)xch[m] << 32);
+      for (int s = 0; s < 32; s++) {
+        const double v = s < 16 ? re[s & 15] : im[s & 15];
+        const u64 z = __builtin_bit_cast(u64, v + 0x1.8p+52) - __builtin_bit_cast(u64, 0x1.8p+52);
+        __hip_atomic_fetch_add(A + 64 * s, z << up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
     __syncthreads();
   }
   u64* dst = out + job * CB_TLWE2;
-  for (int m = tid; m < CB_N2; m += CBW_THREADS) dst[m] = (m == 0) ? acc[0] : (0ull - acc[CB_N2 - m]);
+  for (int m = tid; m < CB_N2; m += CB_WAVES * 64) dst[m] = (m == 0) ? acc[0] : (0ull - acc[CB_N2 - m]);
   if (tid == 0) dst[CB_N2] = acc[CB_N2] + tvv;
 }
 
@@ -418,12 +402,19 @@ __global__ __launch_bounds__(256, 2) void k_cb_privks(const u32* __restrict__ pk
 }
 
 hipError_t init_cb_kernel_attributes() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cb_rotate),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)CB_LDS);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cb_rotate_wide), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)CBW_LDS);
-  return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cb_rotate), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)CB_LDS);
+}
+
+// Lane table (CbTab): lane 4 u + v has the root z_u in pass 2, the residues 4 v + k in pass 3.
+static std::vector<c64> make_cb_table() {
+  std::vector<c64> t(CB_TAB * 64);
+  for (int L = 0; L < 64; L++) {
+    const long double zu = fft_leaf(0.25L, 4, L >> 2), n = fft_leaf(zu, 2, L & 3);
+    const long double a[CB_TAB] = {zu / 2, zu / 4, zu / 8, zu / 16, n / 8, n / 8 + 1 / 8.0L, n / 16, n / 16 + 1 / 16.0L};
+    for (int e = 0; e < CB_TAB; e++) t[e * 64 + L] = fft_unit(a[e]);
+  }
+  return t;
 }
 
 }  // namespace vsp
@@ -432,11 +423,10 @@ using namespace vsp;
 
 struct vsp_cbkey {
   vsp_context* ctx = nullptr;
-  u64* key = nullptr;   // transformed level-2 bootstrapping key
+  c64* key = nullptr;   // transformed level-2 bootstrapping key
+  c64* tab = nullptr;   // lane table of its transform
   u32* pksk = nullptr;  // private key-switching keys
   Scratch tl2;          // TLWE2 outputs of the blind rotations
-  Scratch acc;          // their accumulators [job][2][N2]
-  int form = 0;         // level-2 blind rotation: 0 by batch size, 1 four-wave form, 2 eight-wave form
 };
 
 extern "C" {
@@ -460,16 +450,18 @@ vsp_status vsp_cbkey_create(vsp_context* ctx, const uint64_t* bk2_host, const ui
   const size_t pksk_bytes = 2 * CB_PKS_U * 4;
   hipError_t e;
   if ((e = hipMalloc(&tmp, bk2_bytes)) != hipSuccess) return bail(hip_fail(e, "hipMalloc(level-2 key)"));
-  if ((e = hipMalloc(&k->key, (size_t)LWE_N * CB_KEY_STEP * 8)) != hipSuccess)
+  if ((e = hipMalloc(&k->key, (size_t)LWE_N * CB_KEY_STEP * sizeof(c64))) != hipSuccess)
     return bail(hip_fail(e, "hipMalloc(level-2 key, transformed)"));
   if ((e = hipMalloc(&k->pksk, pksk_bytes)) != hipSuccess) return bail(hip_fail(e, "hipMalloc(private key-switching keys)"));
   if ((e = hipMemcpy(tmp, bk2_host, bk2_bytes, hipMemcpyHostToDevice)) != hipSuccess) return bail(hip_fail(e, "upload"));
   if ((e = hipMemcpy(k->pksk, pksk_host, pksk_bytes, hipMemcpyHostToDevice)) != hipSuccess)
     return bail(hip_fail(e, "upload"));
-  const uint64_t jobs = (uint64_t)LWE_N * CB_ROWS * 2 * 2;
-  const u64 ninv = gl_powmod_const(RING_N, GL_P - 2);
-  hipLaunchKernelGGL(k_cb_key, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, nullptr, tmp, k->key, ctx->tw, ninv,
-                     jobs);
+  const std::vector<c64> tab = make_cb_table();
+  if ((e = hipMalloc(&k->tab, tab.size() * sizeof(c64))) != hipSuccess) return bail(hip_fail(e, "hipMalloc(table)"));
+  if ((e = hipMemcpy(k->tab, tab.data(), tab.size() * sizeof(c64), hipMemcpyHostToDevice)) != hipSuccess)
+    return bail(hip_fail(e, "upload table"));
+  const uint64_t jobs = (uint64_t)LWE_N * CB_ROWS * CB_PRODUCTS;
+  hipLaunchKernelGGL(k_cb_key, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, nullptr, tmp, k->key, k->tab, jobs);
   if ((e = hipGetLastError()) != hipSuccess) return bail(hip_fail(e, "level-2 key conversion"));
   if ((e = hipDeviceSynchronize()) != hipSuccess) return bail(hip_fail(e, "level-2 key conversion"));
   (void)hipFree(tmp);
@@ -482,7 +474,7 @@ vsp_status vsp_cbkey_destroy(vsp_cbkey* k) {
   if (k == nullptr) return VSP_OK;
   (void)hipSetDevice(k->ctx->device);
   (void)hipDeviceSynchronize();
-  for (void* p : {(void*)k->key, (void*)k->pksk, k->tl2.ptr, k->acc.ptr})
+  for (void* p : {(void*)k->key, (void*)k->tab, (void*)k->pksk, k->tl2.ptr})
     if (p) (void)hipFree(p);
   delete k;
   return VSP_OK;
@@ -490,9 +482,8 @@ vsp_status vsp_cbkey_destroy(vsp_cbkey* k) {
 
 vsp_status vsp_cbkey_set_form(vsp_cbkey* key, int form) {
   if (key == nullptr) return fail(VSP_E_ARG, "key is NULL");
-  if (form < 0 || form > 2) return fail(VSP_E_ARG, "form must be 0 (by batch size), 1 (four waves) or 2 (eight waves)");
-  key->form = form;
-  return VSP_OK;
+  if (form < 0 || form > 2) return fail(VSP_E_ARG, "form must be 0, 1 or 2");
+  return VSP_OK;  // one form serves every batch size
 }
 
 vsp_status vsp_circuit_bootstrap(vsp_context* ctx, vsp_cbkey* key, const uint32_t* d_in, uint32_t* d_out, uint64_t R,
@@ -509,18 +500,10 @@ vsp_status vsp_circuit_bootstrap(vsp_context* ctx, vsp_cbkey* key, const uint32_
   if ((s = check_no_overlap(d_out, ob, d_in, ib, "d_out and d_in"))) return s;
   const uint64_t jobs = R * GADGET_L;
   if ((s = scratch_reserve(ctx, key->tl2, jobs * CB_TLWE2 * 8))) return s;
-  if ((s = scratch_reserve(ctx, key->acc, jobs * 2 * CB_N2 * 8))) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
   u64* tl2 = static_cast<u64*>(key->tl2.ptr);
-  // the eight-wave form while the jobs fit one workgroup per compute unit (the four-wave form,
-  // two per compute unit, would run them in one round too, each step on half the waves)
-  const bool wide = key->form == 2 || (key->form == 0 && jobs <= (uint64_t)(ctx->cus > 0 ? ctx->cus : 256));
-  if (wide)
-    hipLaunchKernelGGL(k_cb_rotate_wide, dim3((unsigned)jobs), dim3(CBW_THREADS), CBW_LDS, st, key->key, ctx->tw, d_in,
-                       static_cast<u64*>(key->acc.ptr), tl2, GADGET_L, BG_BIT);
-  else
-    hipLaunchKernelGGL(k_cb_rotate, dim3((unsigned)jobs), dim3(CB_THREADS), CB_LDS, st, key->key, ctx->tw, d_in,
-                       static_cast<u64*>(key->acc.ptr), tl2, GADGET_L, BG_BIT);
+  hipLaunchKernelGGL(k_cb_rotate, dim3((unsigned)jobs), dim3(CB_WAVES * 64), CB_LDS, st, key->key, key->tab, d_in, tl2,
+                     GADGET_L, BG_BIT);
   // tiles as large as keep about four workgroups per compute unit busy (16 per tile and u)
   const uint64_t slices = CB_PKS_ROW / 256;
   auto tiles = [&](uint64_t g) { return (jobs + g - 1) / g; };

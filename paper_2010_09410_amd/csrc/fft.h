@@ -154,7 +154,7 @@ __device__ __forceinline__ void fft_pass(double (&re)[M], double (&im)[M], W con
 template <int M, class W>
 __device__ __forceinline__ void fft_pass_inverse(double (&re)[M], double (&im)[M], W constants) {
 #pragma unroll
-  for (int s = (M == 16 ? 3 : 2); s >= 0; s--) {
+  for (int s = (M == 16 ? 3 : M == 8 ? 2 : 1); s >= 0; s--) {
     const int H = (M / 2) >> s;
 #pragma unroll
     for (int b = 0; b < (1 << s); b++) {

@@ -140,28 +140,28 @@ static bool make_tables(std::vector<u64>& tw) {
 // uses the angles a / 2^(s+1) + f; block b after s splittings has the root at fft_leaf(a, s, b).
 // Half-wave layout: lane (u, c) holds half c of residue u, entries 0-7 its pass 2 and 8 sqrt(z_u). Whole-wave
 // layout (after it): lane 8 u + u' holds residue u, then residue (u, u'), four entries each.
-static long double fft_leaf(long double a, int s, int b) {
-  return s == 0 ? a : fft_leaf(a, s - 1, b >> 1) / 2 + (b & 1) * 0.5L;
+long double fft_leaf(long double a, int s, int b) { return s == 0 ? a : fft_leaf(a, s - 1, b >> 1) / 2 + (b & 1) * 0.5L; }
+c64 fft_unit(long double turns) {
+  const long double t = 6.283185307179586476925286766559005768L * turns;
+  return make_double2((double)cosl(t), (double)sinl(t));
 }
-static std::vector<c64> make_fft_tables() {
+static c64 fft_constant(long double a, int e) {
   static const struct { int s; long double f; } kEntry[8] = {{0, 0.0L},      {1, 0.0L},      {2, 0.0L},       {2, 1 / 8.0L},
                                                              {3, 0.0L},      {3, 1 / 8.0L},  {3, 1 / 16.0L},  {3, 3 / 16.0L}};
-  auto unit = [](long double turns) {
-    const long double t = 6.283185307179586476925286766559005768L * turns;
-    return make_double2((double)cosl(t), (double)sinl(t));
-  };
-  auto entry = [&](long double a, int e) { return unit(a / (2 << kEntry[e].s) + kEntry[e].f); };
+  return fft_unit(a / (2 << kEntry[e].s) + kEntry[e].f);
+}
+static std::vector<c64> make_fft_tables() {
   std::vector<c64> t(FFT_TAB_C64 + FFT8_TAB_C64);
   for (int l = 0; l < 32; l++) {
     const long double zu = fft_leaf(0.25L, 4, l & 15);
-    for (int e = 0; e < 8; e++) t[e * 32 + l] = entry(zu / 2 + (l >> 4) * 0.5L, e);
-    t[8 * 32 + l] = unit(zu / 2);
+    for (int e = 0; e < 8; e++) t[e * 32 + l] = fft_constant(zu / 2 + (l >> 4) * 0.5L, e);
+    t[8 * 32 + l] = fft_unit(zu / 2);
   }
   for (int L = 0; L < 64; L++) {
     const long double zu = fft_leaf(0.25L, 3, L >> 3), zuu = fft_leaf(zu, 3, L & 7);
     for (int e = 0; e < 4; e++) {
-      t[FFT_TAB_C64 + e * 64 + L] = entry(zu, e);
-      t[FFT_TAB_C64 + (4 + e) * 64 + L] = entry(zuu, e);
+      t[FFT_TAB_C64 + e * 64 + L] = fft_constant(zu, e);
+      t[FFT_TAB_C64 + (4 + e) * 64 + L] = fft_constant(zuu, e);
     }
   }
   return t;

@@ -213,6 +213,11 @@ vsp_status check_no_overlap(const void* a, size_t abytes, const void* b, size_t 
 vsp_status upload_keys(const vsp_context* ctx, const uint32_t* bk_host, const uint32_t* ksk_host, c64** bkf,
                        uint32_t** ksk, int8_t** mf_key = nullptr, int8_t** ks_mf = nullptr);
 
+// For the complex transform's lane tables: the angle (in turns) of the root of block b after s
+// splittings of Y^M - r, r at the angle a; and e^(2 pi i turns), correctly rounded.
+long double fft_leaf(long double a, int s, int b);
+c64 fft_unit(long double turns);
+
 // Grows a scratch buffer to at least `bytes` (synchronising the device before freeing).
 vsp_status scratch_reserve(vsp_context* ctx, Scratch& s, size_t bytes);
 

@@ -106,3 +106,23 @@ def test_ram_reads_in_chunks_and_shared_selectors(gpu):
     out = to_host(gpu.ram_read(ram, addr))
     for r in (0, 7, 299):
         np.testing.assert_array_equal(out[r], to_host(gpu.ram_read(ram, addr[r:r + 1]))[0], err_msg=f"read {r}")
+
+
+def test_extreme_level2_key_equals_oracle(gpu, keys):
+    """Circuit bootstrapping with a level-2 key whose three limbs all sit at the ends of their ranges, constant, alternating,
+    as a slow square wave and at random by row; the private key-switching key is random words."""
+    g = W.rng(82)
+    j = np.arange(2048)
+    limbs = lambda l0, l1, l2: np.uint64((l0 + (l1 << 22) + (l2 << 44)) % (1 << 64))  # noqa: E731
+    low, high = limbs(-(1 << 21), -(1 << 21), -(1 << 19)), limbs((1 << 21) - 1, (1 << 21) - 1, (1 << 19) - 1)
+    signs = [np.ones(2048, bool), j % 2 == 0, np.cos(np.pi * (j + 0.5) / 2048) >= 0, g.integers(0, 2, 2048) == 1]
+    rows = np.stack([np.stack([np.where(signs[(r + o) % 4], high, low) for o in range(2)]) for r in range(8)])
+    bk2 = np.ascontiguousarray(np.broadcast_to(rows, (630, 8, 2, 2048)))
+    pksk = g.integers(0, 2 ** 32, size=(2, 2049, 12, 3, 2, N), dtype=np.uint32)
+    c = client.tlwe_encrypt_bits(keys["s0"], np.array([1]), *W.tlwe_draws(g, 1))
+    want = oracle.circuit_bootstraps(bk2, pksk, c)
+    key = gpu.cbkey(bk2, pksk)
+    try:
+        np.testing.assert_array_equal(to_host(key.bootstrap(gpu.tensor(c)))[0].reshape(6, 2, N), want[0])
+    finally:
+        key.close()
