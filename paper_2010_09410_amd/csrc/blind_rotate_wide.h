@@ -1,16 +1,24 @@
-// Latency forms of the blind rotation: one gate per workgroup of eight waves. Per step, waves 0-5 form
-// and transform one TRGSW row's digits each (row r: gadget level r mod 3 + 1 of ACC polynomial r / 3);
-// then wave w takes slot w of the transform, 64 values, and adds the six rows' products with the
-// three key polynomials; then waves 0-2 invert the three sums and add into the accumulator. A
-// step's critical path is one digit row, one forward and one inverse transform over whole waves and
-// three barriers; what bounds it is the latency of that chain (LDS exchanges, dependent
-// multiply-adds). Two variants:
-//  - one gate per compute unit (PER_SIMD 2): the wave's share of the next step's key (18 KiB) is loaded
-//    whole while the step goes on (AHEAD 6): 256 gates 3.6 ms;
+// Latency forms of the blind rotation: one gate per workgroup of eight waves. A step is four phases
+// between barriers:
+//  1. all waves add the last step's small products into their four coefficients per thread of ACC and
+//     form the digit words of X^a ACC - ACC (the new ACC is stored in phase 2, when all have read it);
+//  2. wave r < 6 transforms TRGSW row r's digits (gadget level r mod 3 + 1 of ACC polynomial r / 3);
+//  3. wave w takes slot w of the transform, 64 values, and adds the six rows' products with the three
+//     key polynomials;
+//  4. waves 0-2 invert one of the three sums each; waves 0 and 1 add their K_hi product into ACC, wave 2
+//     leaves the small products in LDS. No LDS atomics: 64 lanes of one take about 34 cycles.
+// What bounds a step is the latency of that chain, about 9,600 cycles: 800, 3,300 (three LDS writes of
+// 8 KiB by each of six waves, at 39 B/clk per pair of SIMDs, are 1,900 of it), 1,200 and 4,000. Each key
+// entry is read once per gate, its load issued where it delays no one: in phase 4, by waves 3-7 while
+// waves 0-2 invert and by those after they have stored their results (a wave's 18 KiB take 290 cycles
+// to issue; among the products they delayed the sums, in the inverse transform the transform). Two
+// variants:
+//  - one gate per compute unit (PER_SIMD 2): a wave's whole share of the next step's key ahead (AHEAD 6);
 //  - two gates per compute unit (PER_SIMD 4, 128 registers): one row of the key ahead (AHEAD 1), the two
-//    workgroups fill each other's waits: 512 gates 4.9 ms, against 7.0 ms in two rounds of the first.
-// Each key entry is read once per gate. Results are bit-identical to the one-wave form (exact integer
-// arithmetic).
+//    workgroups fill each other's waits.
+// Measured, 256 gates one per unit 2.62 ms, 512 gates two per unit 4.82; with three phases, each forward
+// wave forming its own digit words, LDS atomics into ACC and the loads among the products 3.72 and 5.25.
+// Results are bit-identical to the one-wave form (exact integer arithmetic).
 #pragma once
 #include "blind_rotate.h"
 
@@ -19,7 +27,8 @@ namespace vsp {
 constexpr int BRW_WAVES = 8;
 constexpr int BRW_ROWS = 2 * GADGET_L;
 // LDS: a region per row (its exchanges, then its transform [slot][lane]; the inverse exchanges reuse
-// the first three), the three sums [product][slot][lane], the accumulator.
+// the first three), the three sums [product][slot][lane] (before they are written, the digit words in
+// the first one's place; after they are read, the small products in the last one's), the accumulator.
 constexpr size_t brw_lds_bytes() {
   return (size_t)(BRW_ROWS + FFT_PRODUCTS) * FFT8_REGION_C64 * 16 + 2 * RING_N * 4;
 }
@@ -39,6 +48,8 @@ __global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane0 = tid & 63;
   c64* sums = lds + BRW_ROWS * FFT8_REGION_C64;
   u32* acc = reinterpret_cast<u32*>(sums + FFT_PRODUCTS * FFT8_REGION_C64);
+  u32* words = reinterpret_cast<u32*>(sums);                       // [2][N], in the first sum's place
+  u32* small = reinterpret_cast<u32*>(sums + 2 * FFT8_REGION_C64);  // [2][N], in the packed sum's place
   c64* reg = lds + (wave < BRW_ROWS ? wave : 0) * FFT8_REGION_C64;
   const u32* ab = abar + g * TLWE0;
   Fft8Lane tab;
@@ -65,7 +76,10 @@ __global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(
   load_rows(0, 0, key);
   {
     const int k0 = (2 * RING_N - (int)ab[LWE_N]) & (2 * RING_N - 1);
-    for (int j = tid; j < 2 * RING_N; j += BRW_WAVES * 64) acc[j] = j < RING_N ? 0u : rotated_testvector(j - RING_N, k0);
+    for (int j = tid; j < 2 * RING_N; j += BRW_WAVES * 64) {
+      acc[j] = j < RING_N ? 0u : rotated_testvector(j - RING_N, k0);
+      small[j] = 0;
+    }
   }
   int a_next = (int)__builtin_amdgcn_readfirstlane(ab[0]);
   __syncthreads();
@@ -73,18 +87,28 @@ __global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(
     const int a = a_next;
     a_next = (int)__builtin_amdgcn_readfirstlane(ab[i + 1]);  // (the last one is b)
     double re[8], im[8];
-    // with two workgroups on a compute unit (PER_SIMD 4, 128 registers) the lane's LDS addresses are
-    // formed anew in every step instead of being kept
+    // with 128 registers the lane's LDS addresses are formed anew in every step instead of being kept
     const int lane = PER_SIMD > 2 ? opaque_lane(lane0) : lane0;
     const int pm = place(lane), pl = place(fft_half_lane(lane));
+    u32 own[4];  // coefficients 512 q + tid of (a, b), polynomial q / 2: ACC with the last step's small products
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int p = (q >> 1) * RING_N, j = (q & 1) * (RING_N / 2) + wave * 64 + lane;
+      own[q] = acc[p + j] + small[p + j];
+      const int r = j - a, at = p + (r & (RING_N - 1));
+      const u32 v = acc[at] + small[at];
+      words[p + j] = digit_word((r & RING_N ? 0u - v : v) - own[q]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; q++) acc[q * (RING_N / 2) + wave * 64 + lane] = own[q];
     if (wave < BRW_ROWS) {
-      const u32* accs = acc + (wave / GADGET_L) * RING_N;
+      const u32* w = words + (wave / GADGET_L) * RING_N + lane;
       const int up = BG_BIT * (wave % GADGET_L);
 #pragma unroll
       for (int t = 0; t < 8; t++) {
-        const int j = lane + 64 * t;
-        re[t] = (double)((int)(rotated_word(accs, 4 * (j - a), accs[j]) << up) >> 26);
-        im[t] = (double)((int)(rotated_word(accs, 4 * (j - a) + 2 * RING_N, accs[j + RING_N / 2]) << up) >> 26);
+        re[t] = (double)((int)(w[64 * t] << up) >> 26);
+        im[t] = (double)((int)(w[64 * t + RING_N / 2] << up) >> 26);
       }
       fft8_forward(re, im, tab, reg, lane);
 #pragma unroll
@@ -101,17 +125,16 @@ __global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(
 #pragma unroll
           for (int q = 0; q < FFT_PRODUCTS; q++) fft_cmac(sr[q], si[q], x.x, x.y, key[j][q]);
         }
-        if (r0 + AHEAD < BRW_ROWS)
-          load_rows(i, r0 + AHEAD, key);
-        else
-          load_rows(i + 1 < LWE_N ? i + 1 : i, 0, key);
+        if (r0 + AHEAD < BRW_ROWS) load_rows(i, r0 + AHEAD, key);
       }
 #pragma unroll
       for (int q = 0; q < FFT_PRODUCTS; q++)
         sums[q * FFT8_REGION_C64 + wave * 64 + pm] = make_double2(sr[q], si[q]);
     }
     __syncthreads();
+    const int next = i + 1 < LWE_N ? i + 1 : i;
     if (wave < FFT_PRODUCTS) {
+      __builtin_amdgcn_s_setprio(3);  // the chain, against the other waves' loads
 #pragma unroll
       for (int s = 0; s < 8; s++) {
         const c64 x = sums[wave * FFT8_REGION_C64 + s * 64 + pl];
@@ -119,23 +142,34 @@ __global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(
         im[s] = x.y;
       }
       fft8_inverse(re, im, tab, reg, lane);
+      auto value = [&](int t) { return t < 8 ? re[t & 7] : im[t & 7]; };
+      if (wave < 2) {
+        u32* p = acc + wave * RING_N + lane;
+        u32 old[16];
 #pragma unroll
-      for (int t = 0; t < 16; t++) {
-        const double v = t < 8 ? re[t & 7] : im[t & 7];
-        u32* p = acc + lane + 64 * t;
-        if (wave < 2) {
-          __hip_atomic_fetch_add(p + wave * RING_N, fft_round_u32(v) << FFT_LO_BITS, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-        } else {
+        for (int t = 0; t < 16; t++) old[t] = p[64 * t];
+#pragma unroll
+        for (int t = 0; t < 16; t++) p[64 * t] = old[t] + (fft_round_u32(value(t)) << FFT_LO_BITS);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 16; t++) {
           u32 x, y;
-          fft_unpack(v, x, y);
-          __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          __hip_atomic_fetch_add(p + RING_N, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          fft_unpack(value(t), x, y);
+          small[lane + 64 * t] = x;
+          small[RING_N + lane + 64 * t] = y;
         }
       }
+      __builtin_amdgcn_sched_barrier(0);
+      if (AHEAD > 1) load_rows(next, 0, key);
+    } else if (AHEAD > 1) {
+      load_rows(next, 0, key);
     }
+    __builtin_amdgcn_s_setprio(0);
+    if (AHEAD == 1) load_rows(next, 0, key);
     __syncthreads();
   }
+  for (int j = tid; j < 2 * RING_N; j += BRW_WAVES * 64) acc[j] += small[j];
+  __syncthreads();
   if (trlwe) {
     for (int j = tid; j < 2 * RING_N; j += BRW_WAVES * 64) trlwe[g * 2 * RING_N + j] = acc[j];
   }
