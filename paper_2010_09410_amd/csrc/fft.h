@@ -54,9 +54,10 @@ constexpr int FFT_PRODUCTS = 3;    // K_hi of output a, K_hi of output b, packed
 constexpr int FFT_ROW = 34;
 constexpr int FFT_REGION = 16 * FFT_ROW;   // doubles per half
 constexpr int FFT_WAVE_F64 = 2 * FFT_REGION;
-// Lane tables: entry e of lane l at [e][l] (complex): 0-7 the constants of pass 2, 8 sqrt(z_u).
-constexpr int FFT_TAB = 9;
-constexpr int FFT_TAB_C64 = FFT_TAB * 32;
+// Lane tables: entry e of lane l at [e][l] (complex): 0-7 the constants of pass 2, 8 sqrt(z_u); then
+// those of the whole-wave inverse by lane (fft_wave_inverse).
+constexpr int FFT_HALF_TAB_C64 = 9 * 32;
+constexpr int FFT_TAB_C64 = FFT_HALF_TAB_C64 + 8 * 64;
 // Transformed TRGSW in complex numbers: [round k][slot pair p < 8][row e][product][lane]: lane
 // l + 32 s holds, for the row k (e = 0) or k + 3 (e = 1), the value of lane l's slot p + 8 s.
 constexpr int TRGSW_FFT_C64 = GADGET_L * 8 * 2 * FFT_PRODUCTS * 64;
@@ -332,6 +333,47 @@ __device__ __forceinline__ void fft8_inverse(double (&re)[8], double (&im)[8], c
   fft_pass_inverse(re, im, FftConst{});
 }
 
+// The inverse of a sum that lies as fft_key_round leaves it: lane m holds entry m of the slot pairs, so
+// it plays the whole-wave lane L with fft_half_lane(L) = m. Afterwards lane m holds the coefficients
+// m + 64 t. One polynomial on all 64 lanes, where the half-wave inverse would leave half of them idle (288
+// float64 instructions a wave instead of 576; a round of 2,048 gates, bound by their issue, takes 13.5 ms
+// instead of 14.8). The exchanges XOR a residue's words with a number that spreads these lanes over all banks.
+__host__ __device__ constexpr int fft_wave_role(int m) { return 4 * (m & 15) + 2 * ((m >> 4) & 1) + (m >> 5); }
+struct FftWavePass {
+  const c64* tab;  // [entry][lane], at the lane
+  __device__ __forceinline__ c64 operator()(int e) const { return tab[e * 64]; }
+};
+__device__ __forceinline__ void fft_wave_inverse(double (&re)[8], double (&im)[8], const c64* tab, c64* reg, int m) {
+  m = opaque_lane(m);
+  const int L = fft_wave_role(m), u = L >> 3, v = L & 7;
+  auto mix = [](int r) { return (r & 3) | ((r & 4) << 1); };
+  c64* row = reg + u * 64;
+  const int x = mix(u);
+  fft_pass_inverse(re, im, FftWavePass{tab + 4 * 64 + m});
+#pragma unroll
+  for (int a = 0; a < 8; a++) row[(8 * a + (v ^ a)) ^ x] = make_double2(re[a], im[a]);
+  wave_lds_sync();
+#pragma unroll
+  for (int b = 0; b < 8; b++) {
+    const c64 y = row[(8 * v + (b ^ v)) ^ x];
+    re[b] = y.x;
+    im[b] = y.y;
+  }
+  wave_lds_sync();
+  fft_pass_inverse(re, im, FftWavePass{tab + m});
+#pragma unroll
+  for (int s = 0; s < 8; s++) row[(v + 8 * s) ^ x] = make_double2(re[s], im[s]);
+  wave_lds_sync();
+#pragma unroll
+  for (int t = 0; t < 8; t++) {
+    const c64 y = reg[t * 64 + (m ^ mix(t))];
+    re[t] = y.x;
+    im[t] = y.y;
+  }
+  wave_lds_sync();
+  fft_pass_inverse(re, im, FftConst{});
+}
+
 // The integer nearest to x (|x| < 2^51) mod 2^32: adding 1.5 x 2^52 leaves it in the low bits.
 __device__ __forceinline__ u32 fft_round_u32(double x) {
   return (u32)__builtin_bit_cast(u64, x + 0x1.8p+52);
@@ -443,17 +485,6 @@ __device__ __forceinline__ void fft_take_hi(const FftSum& sum, double (&re)[16],
     swap32(im[p], im[p + 8]);
   }
 }
-// The sums of the packed product: all sixteen slots in the lower half, zeros in the upper one.
-__device__ __forceinline__ void fft_take_lo(const FftSum& sum, double (&re)[16], double (&im)[16]) {
-#pragma unroll
-  for (int p = 0; p < 8; p++) {
-    re[p] = sum.r[2][p];
-    im[p] = sum.i[2][p];
-    re[p + 8] = im[p + 8] = 0.0;
-    swap32(re[p], re[p + 8]);
-    swap32(im[p], im[p + 8]);
-  }
-}
 // The two small products of a packed coefficient: x = lo(a) + 2^22 lo(b) after rounding. Adding
 // 1.5 x 2^52 leaves the bits of the word 0x433 2^52 + 2^51 + lo(a) + 2^22 lo(b); rounding up by half of
 // 2^22 and shifting leaves lo(b) - 2^29 in the low 32 bits.
@@ -463,13 +494,14 @@ __device__ __forceinline__ void fft_unpack(double x, u32& lo_a, u32& lo_b) {
   lo_b = (u32)((v + (1u << (FFT_PACK_BITS - 1))) >> FFT_PACK_BITS) + (1u << 29);
 }
 
-// Output coefficient of this half from its own K_hi product hi and the packed product lo (lower
-// lanes): 16 hi + lo(a) in the lower lanes, 16 hi + lo(b) in the upper ones.
-__device__ __forceinline__ u32 fft_combine(u32 hi, double lo) {
+// This half's output coefficients l + 32 (2 t) and l + 32 (2 t + 1) from its K_hi products (in x, y) and
+// the packed product lo of coefficient lane + 64 t: 16 hi + lo(a) in the lower lanes, lo(b) in the upper.
+__device__ __forceinline__ void fft_combine(u32& x, u32& y, double lo) {
   u32 a, b;
   fft_unpack(lo, a, b);
   const auto own = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  return (hi << FFT_LO_BITS) + own[0];
+  x = (x << FFT_LO_BITS) + own[0];
+  y = (y << FFT_LO_BITS) + own[1];
 }
 
 // Wave-cooperative external product: out = this half's polynomial of C (ext) D (lanes 0-31 the
@@ -498,12 +530,11 @@ __device__ __forceinline__ void fft_external_product(Word word, Key& key, const 
     out[t] = fft_round_u32(re[t]);
     out[t + 16] = fft_round_u32(im[t]);
   }
-  fft_take_lo(sum, re, im);
-  fft_inverse(re, im, tab, reg, l);
+  fft_wave_inverse(sum.r[2], sum.i[2], tab + FFT_HALF_TAB_C64, reinterpret_cast<c64*>(reg - (lane >> 5) * FFT_REGION), lane);
 #pragma unroll
-  for (int t = 0; t < 16; t++) {
-    out[t] = fft_combine(out[t], re[t]);
-    out[t + 16] = fft_combine(out[t + 16], im[t]);
+  for (int t = 0; t < 8; t++) {
+    fft_combine(out[2 * t], out[2 * t + 1], sum.r[2][t]);
+    fft_combine(out[2 * t + 16], out[2 * t + 17], sum.i[2][t]);
   }
 }
 

@@ -164,6 +164,8 @@ static std::vector<c64> make_fft_tables() {
       t[FFT_TAB_C64 + (4 + e) * 64 + L] = fft_constant(zuu, e);
     }
   }
+  for (int e = 0; e < 8; e++)
+    for (int m = 0; m < 64; m++) t[FFT_HALF_TAB_C64 + e * 64 + m] = t[FFT_TAB_C64 + e * 64 + fft_wave_role(m)];
   return t;
 }
 
