@@ -211,14 +211,17 @@ __global__ __launch_bounds__(256) void k_cb_key(const u64* __restrict__ bk2, c64
 }
 
 // Level-2 blind rotation, one workgroup of eight waves per job (circuit bootstrap c = job / l, gadget
-// level j = job % l + 1), one per compute unit. Per step: wave r forms gadget digit r mod 4 + 1 of
-// X^abar ACC_h - ACC_h (h = r / 4) and transforms it into its own 16 KiB of LDS; wave w adds the eight
-// rows' products with the six key polynomials at slots 2 w and 2 w + 1; once every row has been
-// read, the sums take the rows' place, and waves 0-5 invert one each and add it, shifted by its limb,
-// into its output polynomial. The rows and the accumulator fill the 160 KiB of LDS. The key, 786 KB a
-// step, is read once per job, two rows' entries (12 each per lane) ahead of use; what bounds a
-// step is that stream through the vector cache (64 bytes a clock) and the latency of the two
-// transforms. The result is SampleExtract_0 + 1/(2 Bg^j) as a TLWE2.
+// level j = job % l + 1), one per compute unit. Per step: all waves form the digit words of
+// X^abar ACC - ACC; wave r transforms gadget digit r mod 4 + 1 of polynomial r / 4 into its own 16 KiB of
+// LDS; wave w adds the eight rows' products with the six key polynomials at slots 2 w and 2 w + 1; once
+// every row has been read, the sums take the rows' place, waves 0-5 invert one each and leave its
+// integers, shifted by their limb, in its region, and all waves add the three of each output to ACC.
+// The rows and the accumulator fill the 160 KiB of LDS. The key, 786 KB a step, is read once per job,
+// two rows' entries (12 each per lane) ahead of use. A step takes 17.8 us: 12.7 without the key loads
+// (VALU issue, 27,000 cycles, and LDS), the rest is the key's stream, 50 to 64 bytes a clock, past the two
+// rows that the registers hold. Those two are loaded beside the inverse transform; asked for among
+// the last products, where the stream is the bound, a step took 18.9 us. The result is
+// SampleExtract_0 + 1/(2 Bg^j) as a TLWE2.
 constexpr size_t CB_LDS = (size_t)CB_ROWS * CB_REGION_C64 * 16 + 2 * CB_N2 * 8;
 static_assert(CB_ROWS == CB_WAVES && CB_PRODUCTS <= CB_WAVES, "one wave per row and per sum");
 
@@ -303,10 +306,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cb_rotate(const c64* __restri
           fft_cmac(sr[q][0], si[q][0], x0.x, x0.y, kr[row & 1][2 * q]);
           fft_cmac(sr[q][1], si[q][1], x1.x, x1.y, kr[row & 1][2 * q + 1]);
         }
-        if (row + 2 < CB_ROWS)
-          load_row(i, row + 2, kr[row & 1]);
-        else
-          load_row(i + 1 < LWE_N ? i + 1 : i, row + 2 - CB_ROWS, kr[row & 1]);
+        if (row + 2 < CB_ROWS) load_row(i, row + 2, kr[row & 1]);
         __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();  // every row has been read
@@ -326,14 +326,25 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cb_rotate(const c64* __restri
       }
       wave_lds_sync();
       cb_inverse(re, im, t, reg, lane);
-      unsigned long long* A = reinterpret_cast<unsigned long long*>(acc + (wave / CB_LIMBS) * CB_N2) + lane;
+      // the integers, shifted by their limb, in the wave's own region
+      u64* z = reinterpret_cast<u64*>(reg) + lane;
       const int up = CB_LIMB_BITS * (wave % CB_LIMBS);
 #pragma unroll
       for (int s = 0; s < 32; s++) {
         const double v = s < 16 ? re[s & 15] : im[s & 15];
-        const u64 z = __builtin_bit_cast(u64, v + 0x1.8p+52) - __builtin_bit_cast(u64, 0x1.8p+52);
-        __hip_atomic_fetch_add(A + 64 * s, z << up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        z[64 * s] = (__builtin_bit_cast(u64, v + 0x1.8p+52) - __builtin_bit_cast(u64, 0x1.8p+52)) << up;
       }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_row(i + 1 < LWE_N ? i + 1 : i, 0, kr[0]);
+    load_row(i + 1 < LWE_N ? i + 1 : i, 1, kr[1]);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2 * CB_N2 / (CB_WAVES * 64); q++) {  // ACC += the three limbs' words
+      constexpr int PER = CB_N2 / (CB_WAVES * 64), REGION = CB_REGION_C64 * 2;
+      const int m = opaque_lane(tid) + CB_WAVES * 64 * (q % PER);
+      const u64* z = reinterpret_cast<const u64*>(cb_lds) + (q / PER) * CB_LIMBS * REGION + m;
+      acc[(q / PER) * CB_N2 + m] += z[0] + z[REGION] + z[2 * REGION];
     }
     __syncthreads();
   }
