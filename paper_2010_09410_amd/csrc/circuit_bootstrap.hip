@@ -13,9 +13,10 @@
 // its norm (u = 2^-53; 52 u with the turned constants below), the 16 accumulated products of a slot add 16 u
 // and the ten joinings 43 u, so the error of a coefficient is at most 165 u x 8 rows x 2^8 sqrt(2048) x 2^21 sqrt(2048) = 0.17 before
 // rounding: the integers are exact (below 2^43) and the torus words the schoolbook ones.
+#include <algorithm>
 #include <vector>
 
-#include "vsp_internal.h"
+#include "onehot_mfma.h"
 
 namespace vsp {
 
@@ -355,62 +356,88 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cb_rotate(const c64* __restri
 
 // Private functional key switch: out = sum_{k <= N2, p < t2} PKSK[u][k][p][v_{k,p} - 1] over the
 // nonzero base-4 digits v_{k,p} (most significant first) of c_k rounded to 24 bits. Row u = 0
-// is TRGSW row j - 1, u = 1 row l + j - 1. Row-stationary: workgroup (tile of G jobs, u, slice
-// of 256 output words), thread t owning word 256 slice + t; for every (k, p) it loads the three
-// key words of its column once and adds the one each job's digit selects, so the key is read
-// once per tile instead of once per job (sums mod 2^32 in any order: the same bits). The
-// rounded coefficients of the tile's jobs are staged in LDS a chunk of k at a time.
-constexpr int CBP_CHUNK = 32;
-template <int G>
-__global__ __launch_bounds__(256, 2) void k_cb_privks(const u32* __restrict__ pksk, const u64* __restrict__ tl2,
-                                                   u32* __restrict__ out, int gadget_l, uint64_t jobs) {
-  __shared__ u32 chat[CBP_CHUNK][G];
-  __shared__ u32 tab[CB_T][4][256];  // thread t's column: entry v of digit p (v = 0: zero)
-  const uint64_t j0 = (uint64_t)blockIdx.x * G;
-  const int u = blockIdx.y, tid = threadIdx.x, col = (int)blockIdx.z * 256 + tid;
-  const int ng = (int)((jobs - j0 < (uint64_t)G) ? jobs - j0 : (uint64_t)G);
-  constexpr int TB = CB_T * CB_BB;
-  const u32* key = pksk + (size_t)u * CB_PKS_U + col;
-  u32 a[G];
+// is TRGSW row j - 1, u = 1 row l + j - 1. Runs on the matrix cores (onehot_mfma.h): a coefficient
+// has three digit bytes.
+constexpr int CB_DIGIT_BYTES = CB_TLWE2 * CB_T / 4;
+constexpr int CB_QUADS = (CB_DIGIT_BYTES + 15) / 16;                        // of four blocks of four digit bytes
+constexpr int CB_COL_TILES = (int)(CB_PKS_ROW / 16);
+constexpr size_t CB_PKS_TILE = (size_t)CB_QUADS * 4 * OH_BLOCK;             // 16-byte entries of a column tile
+constexpr uint64_t CB_PKS_CHUNK = 8192;                                     // jobs whose digits are held at once
+
+// Key planes of one u, one digit (a word per plane) per thread.
+__global__ __launch_bounds__(256) void k_cb_pkskey(const u32* __restrict__ pksk, u32* __restrict__ dst) {
+  const uint64_t id = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  const int w = (int)(id & 3), lane = (int)((id >> 2) & 63);
+  const uint64_t rest = id >> 8;
+  const int block = (int)(rest % (CB_QUADS * 4)), ct = (int)(rest / (CB_QUADS * 4));
+  if (ct >= CB_COL_TILES) return;
+  const int i = 4 * block + (lane >> 4);
+  u32 x[3] = {0u, 0u, 0u}, p[OH_PLANES];
+  if (i < CB_DIGIT_BYTES)
 #pragma unroll
-  for (int g = 0; g < G; g++) a[g] = 0u;
+    for (int v = 0; v < 3; v++)
+      x[v] = pksk[((size_t)(i * 4 + w) * 3 + v) * CB_PKS_ROW + 16 * ct + (lane & 15)];
+  oh_planes(x[0], x[1], x[2], p);
 #pragma unroll
-  for (int p = 0; p < CB_T; p++) tab[p][0][tid] = 0u;
-  for (int k0 = 0; k0 < CB_TLWE2; k0 += CBP_CHUNK) {
-    __syncthreads();  // the previous chunk is consumed
-    for (int i = tid; i < CBP_CHUNK * G; i += 256) {
-      const int kk = i / G, g = i % G;
-      u32 v = 0u;
-      if (g < ng && k0 + kk < CB_TLWE2)
-        v = (u32)((tl2[(j0 + g) * CB_TLWE2 + k0 + kk] + (1ull << (64 - TB - 1))) >> (64 - TB));
-      chat[kk][g] = v;
-    }
-    __syncthreads();
-    const int kn = (CB_TLWE2 - k0 < CBP_CHUNK) ? CB_TLWE2 - k0 : CBP_CHUNK;
-    for (int kk = 0; kk < kn; kk++) {
-      const u32* kr = key + (size_t)(k0 + kk) * CB_T * 3 * CB_PKS_ROW;
-      u32 c[G];  // the jobs' rounded coefficients: the same in every lane
-#pragma unroll
-      for (int g = 0; g < G; g++) c[g] = __builtin_amdgcn_readfirstlane(chat[kk][g]);
-      // the thread's own column goes to LDS, where a wave-uniform digit indexes it (no compare
-      // and select per job and digit; each thread reads only what it wrote, so no barrier)
-#pragma unroll
-      for (int p = 0; p < CB_T; p++)
-#pragma unroll
-        for (int v = 0; v < 3; v++) tab[p][v + 1][tid] = kr[(size_t)(p * 3 + v) * CB_PKS_ROW];
-#pragma unroll
-      for (int p = 0; p < CB_T; p++)
-#pragma unroll
-        for (int g = 0; g < G; g++) a[g] += tab[p][(c[g] >> (CB_BB * (CB_T - 1 - p))) & 3u][tid];
-    }
-  }
-  for (int g = 0; g < ng; g++) {
-    const uint64_t job = j0 + g;
-    const int j = (int)(job % (uint64_t)gadget_l) + 1;
-    const int row = u == 0 ? j - 1 : gadget_l + j - 1;
-    out[((job / (uint64_t)gadget_l) * 2 * gadget_l + row) * CB_PKS_ROW + col] = a[g];
-  }
+  for (int b = 0; b < OH_PLANES; b++) dst[((rest * OH_PLANES + b) * 64 + lane) * 4 + w] = p[b];
 }
+
+// Digits of `jobs` TLWE2s, one word per thread; elements past them select nothing.
+__global__ __launch_bounds__(256) void k_cb_digits(const u64* __restrict__ tl2, u32* __restrict__ dst, uint64_t jobs,
+                                                   uint64_t words) {
+  const uint64_t id = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (id >= words) return;
+  const int lane = (int)(id & 63);
+  const uint64_t rest = id >> 6;
+  const uint64_t job = rest / CB_QUADS * 16 + (lane & 15);
+  constexpr int TB = CB_T * CB_BB;
+  u32 d = 0;
+#pragma unroll
+  for (int t = 0; t < 4; t++) {
+    const int i = (int)(rest % CB_QUADS) * 16 + 4 * t + (lane >> 4);
+    if (job >= jobs || i >= CB_DIGIT_BYTES) continue;
+    const u32 c = (u32)((tl2[job * CB_TLWE2 + i / 3] + (1ull << (64 - TB - 1))) >> (64 - TB));
+    d |= ((c >> (16 - 8 * (i % 3))) & 255u) << (8 * t);
+  }
+  dst[id] = ~d;
+}
+
+// One workgroup of eight waves per (16 T jobs, u, 16 columns), each wave an eighth of the digits. The
+// workgroups of a column tile follow each other on one XCD (of eight, dealt out in turn), so that its
+// key, 6.3 MB, is read from memory once for all jobs. Measured: 24 jobs 0.26 ms, the key's 1.6 GB at
+// 6.2 TB/s; 864 jobs 0.89 ms, 1.4 x 10^12 multiply-adds at 1.6 x 10^15/s, where the matrix cores and the
+// one-hot construction on the VALU share the issue slots. Selecting rows through LDS, a word per
+// thread, took 2.1 and 12.6 ms. Wider tiles of jobs build each operand for the same key loads, so the
+// widest that the batch fills is taken.
+template <int T>
+__global__ __launch_bounds__(OH_WAVES * 64, 2) void k_cb_privks(const oh_v4i* __restrict__ key, const u32* __restrict__ digits,
+                                                     u32* __restrict__ out, int gadget_l, uint64_t job0, uint64_t jobs,
+                                                     u32 job_tiles) {
+  __shared__ u32 red[OH_WAVES][T * 4][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const u32 seq = blockIdx.x / 8, jt = seq % job_tiles;
+  const int uc = (int)(seq / job_tiles * 8 + blockIdx.x % 8), u = uc / CB_COL_TILES, ct = uc % CB_COL_TILES;
+  u32 sum[T][4];
+  constexpr size_t TILE = (size_t)CB_QUADS * 64;
+  oh_products<T>((oh_key)key + (size_t)uc * CB_PKS_TILE + lane, (oh_digits)digits + (size_t)jt * T * TILE + lane, TILE, wave,
+                 OH_WAVES, CB_QUADS, sum);
+  oh_reduce<T>(sum, red, wave, lane, [&](int i, int x, u32 v) {
+    const uint64_t g = ((uint64_t)jt * T + i) * 16 + 4 * (lane >> 4) + x;
+    if (g >= jobs) return;
+    const uint64_t job = job0 + g;
+    const int row = u * gadget_l + (int)(job % (uint64_t)gadget_l);
+    out[((job / (uint64_t)gadget_l) * 2 * gadget_l + row) * CB_PKS_ROW + 16 * ct + (lane & 15)] = v;
+  });
+}
+static_assert(2 * CB_COL_TILES % 8 == 0, "column tiles are dealt out to eight XCDs");
+
+template <int T>
+static void launch_privks(const oh_v4i* key, const u32* digits, u32* out, uint64_t job0, uint64_t jobs, hipStream_t st) {
+  const uint64_t tiles = (jobs + 16 * T - 1) / (16 * T);
+  hipLaunchKernelGGL(k_cb_privks<T>, dim3((unsigned)(tiles * 2 * CB_COL_TILES)), dim3(OH_WAVES * 64), 0, st, key, digits, out,
+                     GADGET_L, job0, jobs, (u32)tiles);
+}
+static uint64_t digit_words(uint64_t jobs) { return (jobs + 127) / 128 * 128 / 16 * CB_QUADS * 64; }
 
 hipError_t init_cb_kernel_attributes() {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cb_rotate), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -436,8 +463,8 @@ struct vsp_cbkey {
   vsp_context* ctx = nullptr;
   c64* key = nullptr;   // transformed level-2 bootstrapping key
   c64* tab = nullptr;   // lane table of its transform
-  u32* pksk = nullptr;  // private key-switching keys
-  Scratch tl2;          // TLWE2 outputs of the blind rotations
+  oh_v4i* pksk = nullptr;  // byte planes of the private key-switching keys
+  Scratch tl2;          // TLWE2 outputs of the blind rotations, then digits of the key switch
 };
 
 extern "C" {
@@ -458,15 +485,13 @@ vsp_status vsp_cbkey_create(vsp_context* ctx, const uint64_t* bk2_host, const ui
     return st;
   };
   const size_t bk2_bytes = (size_t)LWE_N * CB_ROWS * 2 * CB_N2 * 8;
-  const size_t pksk_bytes = 2 * CB_PKS_U * 4;
   hipError_t e;
   if ((e = hipMalloc(&tmp, bk2_bytes)) != hipSuccess) return bail(hip_fail(e, "hipMalloc(level-2 key)"));
   if ((e = hipMalloc(&k->key, (size_t)LWE_N * CB_KEY_STEP * sizeof(c64))) != hipSuccess)
     return bail(hip_fail(e, "hipMalloc(level-2 key, transformed)"));
-  if ((e = hipMalloc(&k->pksk, pksk_bytes)) != hipSuccess) return bail(hip_fail(e, "hipMalloc(private key-switching keys)"));
+  if ((e = hipMalloc(&k->pksk, 2 * CB_COL_TILES * CB_PKS_TILE * sizeof(oh_v4i))) != hipSuccess)
+    return bail(hip_fail(e, "hipMalloc(private key-switching keys)"));
   if ((e = hipMemcpy(tmp, bk2_host, bk2_bytes, hipMemcpyHostToDevice)) != hipSuccess) return bail(hip_fail(e, "upload"));
-  if ((e = hipMemcpy(k->pksk, pksk_host, pksk_bytes, hipMemcpyHostToDevice)) != hipSuccess)
-    return bail(hip_fail(e, "upload"));
   const std::vector<c64> tab = make_cb_table();
   if ((e = hipMalloc(&k->tab, tab.size() * sizeof(c64))) != hipSuccess) return bail(hip_fail(e, "hipMalloc(table)"));
   if ((e = hipMemcpy(k->tab, tab.data(), tab.size() * sizeof(c64), hipMemcpyHostToDevice)) != hipSuccess)
@@ -475,6 +500,17 @@ vsp_status vsp_cbkey_create(vsp_context* ctx, const uint64_t* bk2_host, const ui
   hipLaunchKernelGGL(k_cb_key, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, nullptr, tmp, k->key, k->tab, jobs);
   if ((e = hipGetLastError()) != hipSuccess) return bail(hip_fail(e, "level-2 key conversion"));
   if ((e = hipDeviceSynchronize()) != hipSuccess) return bail(hip_fail(e, "level-2 key conversion"));
+  (void)hipFree(tmp);
+  tmp = nullptr;
+  if ((e = hipMalloc(&tmp, CB_PKS_U * 4)) != hipSuccess) return bail(hip_fail(e, "hipMalloc(private key-switching keys, staging)"));
+  for (int u = 0; u < 2; u++) {
+    if ((e = hipMemcpy(tmp, pksk_host + (size_t)u * CB_PKS_U, CB_PKS_U * 4, hipMemcpyHostToDevice)) != hipSuccess)
+      return bail(hip_fail(e, "upload"));
+    hipLaunchKernelGGL(k_cb_pkskey, dim3((unsigned)(CB_COL_TILES * CB_QUADS * 4)), dim3(256), 0, nullptr,
+                       reinterpret_cast<const u32*>(tmp), reinterpret_cast<u32*>(k->pksk + (size_t)u * CB_COL_TILES * CB_PKS_TILE));
+    if ((e = hipGetLastError()) != hipSuccess) return bail(hip_fail(e, "private key-switching key conversion"));
+    if ((e = hipDeviceSynchronize()) != hipSuccess) return bail(hip_fail(e, "private key-switching key conversion"));
+  }
   (void)hipFree(tmp);
   tmp = nullptr;
   *out = k;
@@ -510,27 +546,26 @@ vsp_status vsp_circuit_bootstrap(vsp_context* ctx, vsp_cbkey* key, const uint32_
   if ((s = check_device_range(ctx, d_out, ob, "d_out"))) return s;
   if ((s = check_no_overlap(d_out, ob, d_in, ib, "d_out and d_in"))) return s;
   const uint64_t jobs = R * GADGET_L;
-  if ((s = scratch_reserve(ctx, key->tl2, jobs * CB_TLWE2 * 8))) return s;
+  const size_t tl2_bytes = (jobs * CB_TLWE2 * 8 + 255) / 256 * 256;
+  if ((s = scratch_reserve(ctx, key->tl2, tl2_bytes + digit_words(std::min(jobs, CB_PKS_CHUNK)) * 4))) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
   u64* tl2 = static_cast<u64*>(key->tl2.ptr);
+  u32* digits = reinterpret_cast<u32*>(static_cast<char*>(key->tl2.ptr) + tl2_bytes);
   hipLaunchKernelGGL(k_cb_rotate, dim3((unsigned)jobs), dim3(CB_WAVES * 64), CB_LDS, st, key->key, key->tab, d_in, tl2,
                      GADGET_L, BG_BIT);
-  // tiles as large as keep about four workgroups per compute unit busy (16 per tile and u)
-  const uint64_t slices = CB_PKS_ROW / 256;
-  auto tiles = [&](uint64_t g) { return (jobs + g - 1) / g; };
-  const uint64_t want = 4ull * (uint64_t)(ctx->cus > 0 ? ctx->cus : 256);
-  if (tiles(32) * 2 * slices >= want)
-    hipLaunchKernelGGL(k_cb_privks<32>, dim3((unsigned)tiles(32), 2, (unsigned)slices), dim3(256), 0, st, key->pksk,
-                       tl2, d_out, GADGET_L, jobs);
-  else if (tiles(16) * 2 * slices >= want)
-    hipLaunchKernelGGL(k_cb_privks<16>, dim3((unsigned)tiles(16), 2, (unsigned)slices), dim3(256), 0, st, key->pksk,
-                       tl2, d_out, GADGET_L, jobs);
-  else if (tiles(8) * 2 * slices >= want)
-    hipLaunchKernelGGL(k_cb_privks<8>, dim3((unsigned)tiles(8), 2, (unsigned)slices), dim3(256), 0, st, key->pksk,
-                       tl2, d_out, GADGET_L, jobs);
-  else
-    hipLaunchKernelGGL(k_cb_privks<2>, dim3((unsigned)tiles(2), 2, (unsigned)slices), dim3(256), 0, st, key->pksk,
-                       tl2, d_out, GADGET_L, jobs);
+  for (uint64_t j0 = 0; j0 < jobs; j0 += CB_PKS_CHUNK) {
+    const uint64_t n = std::min(jobs - j0, CB_PKS_CHUNK), words = digit_words(n);
+    hipLaunchKernelGGL(k_cb_digits, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, tl2 + j0 * CB_TLWE2, digits, n,
+                       words);
+    if (n <= 16)
+      launch_privks<1>(key->pksk, digits, d_out, j0, n, st);
+    else if (n <= 32)
+      launch_privks<2>(key->pksk, digits, d_out, j0, n, st);
+    else if (n <= 64)
+      launch_privks<4>(key->pksk, digits, d_out, j0, n, st);
+    else
+      launch_privks<8>(key->pksk, digits, d_out, j0, n, st);
+  }
   VSP_HIP(hipGetLastError());
   return VSP_OK;
 }

@@ -126,3 +126,24 @@ def test_extreme_level2_key_equals_oracle(gpu, keys):
         np.testing.assert_array_equal(to_host(key.bootstrap(gpu.tensor(c)))[0].reshape(6, 2, N), want[0])
     finally:
         key.close()
+
+
+def test_private_key_switch_batches_equal_single_inputs(gpu, keys):
+    """Batch sizes on both sides of every tile width of the private key switch (three rows of it per input; 16, 32, 64 and 128
+    rows) and past one launch of it (8,192 rows): each input's output is what it gives alone, a batch of one the oracle's."""
+    g = W.rng(83)
+    bk2 = g.integers(0, 2 ** 64, size=(630, 8, 2, 2048), dtype=np.uint64)
+    pksk = g.integers(0, 2 ** 32, size=(2, 2049, 12, 3, 2, N), dtype=np.uint32)
+    c = g.integers(0, 2 ** 32, size=(2740, 631), dtype=np.uint32)
+    want = oracle.circuit_bootstraps(bk2, pksk, c[:1])
+    key = gpu.cbkey(bk2, pksk)
+    try:
+        d = gpu.tensor(c)
+        alone = {r: to_host(key.bootstrap(d[r:r + 1]))[0] for r in (0, 4, 5, 9, 10, 20, 21, 41, 42, 2729, 2730, 2731, 2739)}
+        np.testing.assert_array_equal(alone[0].reshape(6, 2, N), want[0])
+        for R in (5, 6, 10, 11, 21, 22, 42, 43, 2740):
+            out = to_host(key.bootstrap(d[:R]))
+            for r in (x for x in alone if x < R):
+                np.testing.assert_array_equal(out[r], alone[r], err_msg=f"input {r} of {R}")
+    finally:
+        key.close()
