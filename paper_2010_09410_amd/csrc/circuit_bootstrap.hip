@@ -402,6 +402,26 @@ __global__ __launch_bounds__(256) void k_cb_digits(const u64* __restrict__ tl2, 
   dst[id] = ~d;
 }
 
+// A wave's digits: every eighth quad, the next one's words loaded a step ahead.
+template <int T>
+struct CbDigits {
+  oh_digits at;
+  int wave;
+  u32 next[T];
+  __device__ __forceinline__ int quad(int n) const { return wave + OH_WAVES * n; }
+  __device__ __forceinline__ void load(int n) {
+#pragma unroll
+    for (int i = 0; i < T; i++) next[i] = at[((size_t)i * CB_QUADS + quad(n)) * 64];
+  }
+  __device__ __forceinline__ void start() { load(0); }
+  __device__ __forceinline__ void get(int, u32 (&d)[T]) {
+#pragma unroll
+    for (int i = 0; i < T; i++) d[i] = next[i];
+  }
+  __device__ __forceinline__ void issue(int n) { load(quad(n + 1) < CB_QUADS ? n + 1 : n); }
+  __device__ __forceinline__ void finish(int) {}
+};
+
 // One workgroup of eight waves per (16 T jobs, u, 16 columns), each wave an eighth of the digits. The
 // workgroups of a column tile follow each other on one XCD (of eight, dealt out in turn), so that its
 // key, 6.3 MB, is read from memory once for all jobs. Measured: 24 jobs 0.26 ms, the key's 1.6 GB at
@@ -418,10 +438,11 @@ __global__ __launch_bounds__(OH_WAVES * 64, 2) void k_cb_privks(const oh_v4i* __
   const u32 seq = blockIdx.x / 8, jt = seq % job_tiles;
   const int uc = (int)(seq / job_tiles * 8 + blockIdx.x % 8), u = uc / CB_COL_TILES, ct = uc % CB_COL_TILES;
   u32 sum[T][4];
-  constexpr size_t TILE = (size_t)CB_QUADS * 64;
-  oh_products<T>((oh_key)key + (size_t)uc * CB_PKS_TILE + lane, (oh_digits)digits + (size_t)jt * T * TILE + lane, TILE, wave,
-                 OH_WAVES, CB_QUADS, sum);
-  oh_reduce<T>(sum, red, wave, lane, [&](int i, int x, u32 v) {
+  CbDigits<T> source;
+  source.at = (oh_digits)digits + (size_t)jt * T * CB_QUADS * 64 + lane;
+  source.wave = wave;
+  oh_products<T>((oh_key)key + (size_t)uc * CB_PKS_TILE + lane, source, (CB_QUADS - wave + OH_WAVES - 1) / OH_WAVES, sum);
+  oh_reduce<T, OH_WAVES>(sum, red, wave, lane, [&](int i, int x, u32 v) {
     const uint64_t g = ((uint64_t)jt * T + i) * 16 + 4 * (lane >> 4) + x;
     if (g >= jobs) return;
     const uint64_t job = job0 + g;

@@ -446,8 +446,8 @@ hipError_t launch_keyswitch(const vsp_context* ctx, const uint8_t* ops, const ui
   if (ksk == nullptr) ksk = ctx->ksk;
   if (form < 0) form = ctx->tune.ks_form_for(B);
   if (form == 3) {
-    if (ksk == ctx->ksk && ctx->ks_mf != nullptr) return launch_keyswitch_mfma(ctx->ks_mf, ops, tlwe1, idxo, out, B, st);
-    if (ksk != ctx->ksk && ks_mf != nullptr) return launch_keyswitch_mfma(ks_mf, ops, tlwe1, idxo, out, B, st);
+    if (ksk == ctx->ksk && ctx->ks_mf != nullptr) return launch_keyswitch_mfma(ctx->ks_mf, ops, tlwe1, idxo, out, B, ctx->cus, st);
+    if (ksk != ctx->ksk && ks_mf != nullptr) return launch_keyswitch_mfma(ks_mf, ops, tlwe1, idxo, out, B, ctx->cus, st);
     form = 2;
   }
   if (form == 2) {

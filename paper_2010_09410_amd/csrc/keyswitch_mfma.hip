@@ -1,231 +1,211 @@
 // Identity key switch on the matrix cores (Sec. 2.1.2, Sample Extraction and Identity Key
 // Switching): out = (0, b') - sum_{j < N, p < t} KSK[j][p][v_{j,p}], v_{j,p} the p-th base-4
-// digit of a'_j rounded to 16 bits, written as a matrix product over the batch. For a gate g,
-// row (j, p, v) of its one-hot operand is 1 where v = v_{g,j,p}; the key rows (the v = 0 row is
-// zero) are the other operand, split into four balanced signed bytes and folded by Horner's
-// rule in the accumulators exactly as in the matrix-core blind rotation (int32 wrap-around is
-// arithmetic mod 2^32; per byte plane a sum has at most 8192 nonzero terms of magnitude at
-// most 128).
-//
-// The 32 rows (p, v) of one j form one 32-deep block of the product: lane (m, kh) of the
-// operand of gate m holds p = 4 kh .. 4 kh + 3 as four words 1 << (8 v_{g,j,p}), built from
-// a'_j in registers. The key bytes are stored in the lane order of the other operand,
-// [plane][j][column tile][lane][16], so a wave's load of one block is 1 KiB contiguous.
-// A workgroup of four waves takes 128 gates and 64 output columns; wave s takes j in
-// [256 s, 256 s + 256), and the four partial sums meet in LDS. The digits of a gate depend only
-// on the top 16 bits of a'_j + 2^15. Rows past the batch get digits of 0 (the zero key row);
-// a gate that does not bootstrap is computed like the others and its output is not written.
-#include "vsp_internal.h"
+// digit of a'_j rounded to 16 bits, as a product of one-hot digits with the key's byte planes
+// (onehot_mfma.h). A coefficient has two digit bytes, a quad of blocks eight coefficients.
+#include "onehot_mfma.h"
 
 namespace vsp {
 
-typedef int ks_v4i __attribute__((ext_vector_type(4)));
-typedef int ks_v16i __attribute__((ext_vector_type(16)));
+constexpr int KM_CT = (TLWE0 + 15) / 16;          // 40 column tiles of 16 (631 columns)
+constexpr int KM_QUADS = RING_N * KS_T / 64;      // 128
+constexpr size_t KM_TILE = (size_t)KM_QUADS * 4 * OH_BLOCK;  // 16-byte entries of a column tile
+constexpr size_t KM_KEY_BYTES = KM_CT * KM_TILE * 16;
+constexpr int KM_ROW = 68;                        // words of a staged quad: 64 lanes, padded to spread the banks
 
-constexpr int KM_CT = (TLWE0 + 31) / 32;           // 20 column tiles of 32 (631 columns)
-constexpr int KM_PLANES = 4;
-constexpr size_t KM_KEY_BYTES = (size_t)KM_PLANES * RING_N * KM_CT * 64 * 16;
-constexpr int KM_GATES = 128;                      // gates per workgroup (four tiles of 32)
-constexpr int KM_COLS = 2;                         // column tiles per workgroup
-constexpr int KM_SPLIT = 4;                        // waves per workgroup, one j range each
-constexpr int KM_JR = RING_N / KM_SPLIT;
-
-// KB[b][j][ct][lane][16]: lane (n, kh), byte 4 w + v holds byte b of KSK[j][4 kh + w][v][32 ct + n]
-// (zero for v = 0 and past column n).
-__global__ __launch_bounds__(256) void k_ks_mfkey(const u32* __restrict__ ksk, int8_t* __restrict__ KB) {
-  const uint64_t id = (uint64_t)blockIdx.x * 256 + threadIdx.x;  // one word (four bytes) each
-  if (id >= KM_KEY_BYTES / 4) return;
+// Key planes, one digit (a word per plane) per thread.
+__global__ __launch_bounds__(256) void k_ks_mfkey(const u32* __restrict__ ksk, u32* __restrict__ dst) {
+  const uint64_t id = (uint64_t)blockIdx.x * 256 + threadIdx.x;
   const int w = (int)(id & 3), lane = (int)((id >> 2) & 63);
   const uint64_t rest = id >> 8;
-  const int ct = (int)(rest % KM_CT);
-  const uint64_t bj = rest / KM_CT;
-  const int j = (int)(bj % RING_N), b = (int)(bj / RING_N);
-  const int n = lane & 31, kh = lane >> 5, c = 32 * ct + n, p = 4 * kh + w;
-  u32 word = 0;
+  const int block = (int)(rest % (KM_QUADS * 4)), ct = (int)(rest / (KM_QUADS * 4));
+  if (ct >= KM_CT) return;
+  const int i = 4 * block + (lane >> 4), c = 16 * ct + (lane & 15);  // digit byte, column
+  u32 x[3] = {0u, 0u, 0u}, p[OH_PLANES];
+  if (c < TLWE0)
 #pragma unroll
-  for (int v = 0; v < 4; v++) {
-    u32 x = (c < TLWE0) ? ksk[(((size_t)j * KS_T + p) * 4 + v) * TLWE0 + c] : 0u;
-    int8_t cb = 0;
-    for (int bb = 0; bb <= b; bb++) {
-      cb = (int8_t)(x & 255u);  // x = cb (mod 256), cb in [-128, 127]
-      x = (x - (u32)(int32_t)cb) >> 8;
-    }
-    word |= ((u32)(uint8_t)cb) << (8 * v);
-  }
-  reinterpret_cast<u32*>(KB)[id] = word;
+    for (int v = 0; v < 3; v++) x[v] = ksk[((size_t)(i * 4 + w) * 4 + v + 1) * TLWE0 + c];
+  oh_planes(x[0], x[1], x[2], p);
+#pragma unroll
+  for (int b = 0; b < OH_PLANES; b++) dst[((rest * OH_PLANES + b) * 64 + lane) * 4 + w] = p[b];
 }
 
-// The top 16 bits of each rounded a'_j (all the digits need) are staged per wave in LDS as
-// [j][gate] u16 for chunks of KM_JC coefficients, rows padded to spread the banks, with 32
-// gates' loads in flight at once; the key operands stream from global memory three blocks
-// ahead. Every load is unconditional (gate index clamped, the last three key blocks re-read
-// and unused): a guarded load becomes a branch, after which the compiler waits for it.
-constexpr int KM_JC = 64;
-constexpr int KM_HROW = KM_GATES + 2;  // u16 per staged row
-
-__global__ __launch_bounds__(256, 2) void k_ks_mfma(const int8_t* __restrict__ KB, const uint8_t* __restrict__ ops,
-                                                     const u32* __restrict__ tlwe1, const u32* __restrict__ idxo,
-                                                     u32* __restrict__ out, uint64_t B) {
-  __shared__ uint16_t hs[KM_SPLIT][KM_JC][KM_HROW];
-  static_assert(sizeof(hs) >= (size_t)4 * KM_COLS * 16 * 64 * 4, "the partial sums fit in the staging area");
-  const int s = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int m = lane & 31, kh = lane >> 5;
-  const uint64_t g0 = (uint64_t)blockIdx.x * KM_GATES;
-  const int ct0 = blockIdx.y * KM_COLS;
-  const int j0 = s * KM_JR;
-  const uint4* kb = reinterpret_cast<const uint4*>(KB) + lane;  // + ((b * N + j) * KM_CT + ct) * 64
-  ks_v16i acc[4][KM_COLS];
+// The digit words of a workgroup's 16 T gates, formed from a' in LDS a chunk of quads at a time and
+// shared by its waves. A thread's unit of that work is one gate, quad and half h: the coefficients
+// 8 Q + 2 t + h (t = 0..3) give the words of the lanes (gate, 2 h) and (gate, 2 h + 1). The next
+// chunk is formed during the steps of this one, in the other buffer, its loads issued before a
+// step's products. A gate past the batch selects nothing.
+template <int T, int SPLIT>
+struct KsDigits {
+  static constexpr int CHUNK = T >= 2 ? 256 / T : KM_QUADS;              // quads
+  static constexpr int CHUNKS = KM_QUADS / CHUNK;
+  static constexpr int STEPS = CHUNK / SPLIT;                            // a wave's steps per chunk
+  static constexpr int UNITS = 16 * T * CHUNK * 2 / (OH_WAVES * 64);     // per thread and chunk
+  static constexpr int PER_STEP = CHUNKS > 1 ? UNITS / STEPS : 1;
+  static constexpr int WORDS = T * CHUNK * KM_ROW;                       // of a buffer
+  static_assert(CHUNK <= KM_QUADS && CHUNKS * CHUNK == KM_QUADS && STEPS * SPLIT == CHUNK, "whole chunks and steps");
+  static_assert(CHUNKS == 1 || PER_STEP * STEPS == UNITS, "a chunk is formed in the steps of another");
+  const u32* __restrict__ tlwe1;
+  uint64_t g0, B;
+  u32* lds;   // [CHUNKS > 1 ? 2 : 1][WORDS]
+  int split, lane;
+  u32 x[PER_STEP][4];
+  // unit u of this thread: a wave covers 8 quads x 2 halves (64 consecutive coefficients) of four gates
+  __device__ __forceinline__ void place(int u, int& g, int& Q, int& h) const {
+    const int id = u * OH_WAVES * 64 + (int)threadIdx.x;
+    h = id & 1;
+    const int ql = (id >> 1) & 7, gl = (id >> 4) & 3, rest = id >> 6;
+    Q = rest % (CHUNK / 8) * 8 + ql;
+    g = rest / (CHUNK / 8) * 4 + gl;
+  }
+  __device__ __forceinline__ void fetch(int chunk, int u, u32 (&v)[4]) const {
+    int g, Q, h;
+    place(u, g, Q, h);
+    const u32* p = tlwe1 + (g0 + g < B ? g0 + g : 0) * TLWE1 + (chunk * CHUNK + Q) * 8 + h;
 #pragma unroll
-  for (int t = 0; t < 4; t++)
+    for (int t = 0; t < 4; t++) v[t] = p[2 * t];
+  }
+  __device__ __forceinline__ void put(int chunk, int u, const u32 (&v)[4]) const {
+    int g, Q, h;
+    place(u, g, Q, h);
+    u32 hi = 0, lo = 0;
 #pragma unroll
-    for (int u = 0; u < KM_COLS; u++)
-#pragma unroll
-      for (int x = 0; x < 16; x++) acc[t][u][x] = 0;
-  uint16_t(*h)[KM_HROW] = hs[s];
-  for (int b = KM_PLANES - 1; b >= 0; b--) {
-    const uint4* kp = kb + ((size_t)b * RING_N * KM_CT + ct0) * 64;
-    auto ldb = [&](int j, uint4 (&r)[KM_COLS]) {
-#pragma unroll
-      for (int u = 0; u < KM_COLS; u++) r[u] = kp[((size_t)j * KM_CT + u) * 64];
-    };
-    uint4 bq[4][KM_COLS];  // block j in slot (j - j0) mod 4
-    ldb(j0, bq[0]);
-    ldb(j0 + 1, bq[1]);
-    ldb(j0 + 2, bq[2]);
-    for (int jc = j0; jc < j0 + KM_JR; jc += KM_JC) {
-      // stage the digits' source bits of this wave's gates for jc .. jc + KM_JC - 1
-      wave_lds_sync();
+    for (int t = 0; t < 4; t++) {
+      const u32 r = v[t] + (1u << 15);
+      hi |= (r >> 24) << (8 * t);
+      lo |= ((r >> 16) & 255u) << (8 * t);
+    }
+    const bool live = g0 + g < B;
+    u32* w = lds + (chunk & 1) * WORDS + ((g >> 4) * CHUNK + Q) * KM_ROW + (g & 15) + 32 * h;
+    w[0] = live ? ~hi : ~0u;
+    w[16] = live ? ~lo : ~0u;
+  }
+  __device__ __forceinline__ int quad(int n) const { return n / STEPS * CHUNK + split * STEPS + n % STEPS; }
+  __device__ __forceinline__ void start() {
 #pragma unroll 1
-      for (int q0 = 0; q0 < KM_GATES; q0 += 32) {
-        u32 v[32];
+    for (int u = 0; u < UNITS; u += 4) {
+      u32 v[4][4];
 #pragma unroll
-        for (int q = 0; q < 32; q++) {
-          const uint64_t g = g0 + q0 + q;
-          v[q] = tlwe1[(g < B ? g : 0) * TLWE1 + jc + lane];
-        }
+      for (int k = 0; k < 4; k++) fetch(0, u + k, v[k]);
 #pragma unroll
-        for (int q = 0; q < 32; q++)
-          h[lane][q0 + q] = (g0 + q0 + q < B) ? (uint16_t)((v[q] + (1u << 15)) >> 16) : (uint16_t)0;
-      }
-      wave_lds_sync();
-      for (int jj = 0; jj < KM_JC; jj += 4) {
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-          const int j = jc + jj + r;
-          ldb(j + 3 < j0 + KM_JR ? j + 3 : j0 + KM_JR - 1, bq[(r + 3) & 3]);
-          ks_v4i bv[KM_COLS];
-#pragma unroll
-          for (int u = 0; u < KM_COLS; u++)
-            bv[u] = ks_v4i{(int)bq[r][u].x, (int)bq[r][u].y, (int)bq[r][u].z, (int)bq[r][u].w};
-#pragma unroll
-          for (int t = 0; t < 4; t++) {
-            const u32 hv = h[jj + r][32 * t + m];
-            ks_v4i av;
-#pragma unroll
-            for (int w = 0; w < 4; w++) av[w] = (int)(1u << (8 * ((hv >> (14 - 2 * (4 * kh + w))) & 3u)));
-#pragma unroll
-            for (int u = 0; u < KM_COLS; u++)
-              acc[t][u] = __builtin_amdgcn_mfma_i32_32x32x32_i8(av, bv[u], acc[t][u], 0, 0, 0);
-          }
-        }
-      }
-    }
-    if (b > 0) {
-#pragma unroll
-      for (int t = 0; t < 4; t++)
-#pragma unroll
-        for (int u = 0; u < KM_COLS; u++)
-#pragma unroll
-          for (int x = 0; x < 16; x++) acc[t][u][x] = (int)((u32)acc[t][u][x] << 8);
+      for (int k = 0; k < 4; k++) put(0, u + k, v[k]);
     }
   }
-  // the partial sums of waves 1..3 through LDS to wave 0, one wave at a time
-  int(*red)[64] = reinterpret_cast<int(*)[64]>(&hs[0][0][0]);
-  __syncthreads();  // every wave is done with its staging rows
-  for (int q = 1; q < KM_SPLIT; q++) {
-    if (s == q) {
+  __device__ __forceinline__ void get(int n, u32 (&d)[T]) const {
+    if (n % STEPS == 0) __syncthreads();  // the chunk is formed, and no wave reads the one before it any more
+    const u32* w = lds + (n / STEPS & 1) * WORDS + (split * STEPS + n % STEPS) * KM_ROW + lane;
 #pragma unroll
-      for (int t = 0; t < 4; t++)
-#pragma unroll
-        for (int u = 0; u < KM_COLS; u++)
-#pragma unroll
-          for (int x = 0; x < 16; x++) red[(t * KM_COLS + u) * 16 + x][lane] = acc[t][u][x];
-    }
-    __syncthreads();
-    if (s == 0) {
-#pragma unroll
-      for (int t = 0; t < 4; t++)
-#pragma unroll
-        for (int u = 0; u < KM_COLS; u++)
-#pragma unroll
-          for (int x = 0; x < 16; x++) acc[t][u][x] += red[(t * KM_COLS + u) * 16 + x][lane];
-    }
-    __syncthreads();
+    for (int i = 0; i < T; i++) d[i] = w[i * CHUNK * KM_ROW];
   }
-  if (s != 0) return;
-  // result (gate, column): lane n + 32 kh, register x: gate row 8 (x / 4) + 4 kh + x % 4 of the
-  // tile, column 32 ct + n. Per tile, the gate types, output rows and b' of the lane's 16 gates
-  // are loaded together first (unconditionally, gate index clamped).
-  const bool has_b = ct0 + KM_COLS > LWE_N / 32;  // this workgroup writes column n (the b part)
+  __device__ __forceinline__ void issue(int n) {
+    if (CHUNKS == 1 || n / STEPS + 1 == CHUNKS) return;
 #pragma unroll
-  for (int t = 0; t < 4; t++) {
-    uint8_t opv[16];
-    u32 rov[16], bv[16];
-#pragma unroll
-    for (int x = 0; x < 16; x++) {
-      const uint64_t g = g0 + 32 * t + 8 * (x >> 2) + 4 * kh + (x & 3);
-      opv[x] = 0;  // a bootstrapping gate type
-      rov[x] = (u32)g;
-      bv[x] = 0;
-    }
-    if (ops) {
-#pragma unroll
-      for (int x = 0; x < 16; x++) {
-        const uint64_t g = g0 + 32 * t + 8 * (x >> 2) + 4 * kh + (x & 3);
-        opv[x] = ops[g < B ? g : 0];
-      }
-    }
-    if (idxo) {
-#pragma unroll
-      for (int x = 0; x < 16; x++) {
-        const uint64_t g = g0 + 32 * t + 8 * (x >> 2) + 4 * kh + (x & 3);
-        rov[x] = idxo[g < B ? g : 0];
-      }
-    }
-    if (has_b) {
-#pragma unroll
-      for (int x = 0; x < 16; x++) {
-        const uint64_t g = g0 + 32 * t + 8 * (x >> 2) + 4 * kh + (x & 3);
-        bv[x] = tlwe1[(g < B ? g : 0) * TLWE1 + RING_N];
-      }
-    }
-#pragma unroll
-    for (int x = 0; x < 16; x++) {
-      const uint64_t g = g0 + 32 * t + 8 * (x >> 2) + 4 * kh + (x & 3);
-      if (g >= B || !op_bootstraps(opv[x])) continue;
-#pragma unroll
-      for (int u = 0; u < KM_COLS; u++) {
-        const int c = 32 * (ct0 + u) + m;
-        if (c >= TLWE0) continue;
-        out[(uint64_t)rov[x] * TLWE0 + c] = ((c == LWE_N) ? bv[x] : 0u) - (u32)acc[t][u][x];
-      }
-    }
+    for (int k = 0; k < PER_STEP; k++) fetch(n / STEPS + 1, n % STEPS * PER_STEP + k, x[k]);
   }
+  __device__ __forceinline__ void finish(int n) {
+    if (CHUNKS == 1 || n / STEPS + 1 == CHUNKS) return;
+#pragma unroll
+    for (int k = 0; k < PER_STEP; k++) put(n / STEPS + 1, n % STEPS * PER_STEP + k, x[k]);
+  }
+};
+
+template <int T, int SPLIT>
+constexpr size_t km_lds_bytes() {
+  using D = KsDigits<T, SPLIT>;
+  const size_t stage = (size_t)(D::CHUNKS > 1 ? 2 : 1) * D::WORDS * 4, red = (size_t)OH_WAVES * T * 4 * 64 * 4;
+  return stage > red ? stage : red;
+}
+
+// One workgroup of eight waves per 16 T gates and 8 / SPLIT column tiles, SPLIT waves sharing a column
+// tile's quads. Workgroups are dealt out to eight XCDs in turn: each XCD takes an eighth of the list
+// ordered by column group, so that the key of a group is read from memory once for all gates.
+template <int T, int SPLIT>
+__global__ __launch_bounds__(OH_WAVES * 64, 2) void k_ks_mfma(const oh_v4i* __restrict__ key, const uint8_t* __restrict__ ops,
+                                                   const u32* __restrict__ tlwe1, const u32* __restrict__ idxo,
+                                                   u32* __restrict__ out, uint64_t B, u32 gate_tiles) {
+  constexpr u32 COLS = OH_WAVES / SPLIT;
+  extern __shared__ u32 km_lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const u32 item = blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8;
+  if (item >= KM_CT / COLS * gate_tiles) return;  // the whole workgroup: no barrier is skipped by half
+  const int ct = (int)(item / gate_tiles * COLS) + wave / SPLIT;
+  KsDigits<T, SPLIT> source;
+  source.tlwe1 = tlwe1;
+  source.g0 = (uint64_t)(item % gate_tiles) * 16 * T;
+  source.B = B;
+  source.lds = km_lds;
+  source.split = wave % SPLIT;
+  source.lane = lane;
+  u32 sum[T][4];
+  oh_products<T>((oh_key)key + (size_t)ct * KM_TILE + lane, source, KM_QUADS / SPLIT, sum);
+  __syncthreads();  // the digits are read; the partial sums take their place
+  oh_reduce<T, SPLIT>(sum, reinterpret_cast<u32(*)[T * 4][64]>(km_lds) + wave / SPLIT * SPLIT, wave % SPLIT, lane,
+                      [&](int i, int x, u32 v) {
+    const uint64_t g = source.g0 + 16 * i + 4 * (lane >> 4) + x;
+    const int c = 16 * ct + (lane & 15);
+    if (g >= B || c >= TLWE0 || (ops && !op_bootstraps(ops[g]))) return;
+    out[(uint64_t)(idxo ? idxo[g] : (u32)g) * TLWE0 + c] = (c == LWE_N ? tlwe1[g * TLWE1 + RING_N] : 0u) - v;
+  });
 }
 
 size_t ks_mf_key_bytes() { return KM_KEY_BYTES; }
 
 hipError_t launch_ks_mfkey(const uint32_t* ksk, int8_t* KB, hipStream_t st) {
-  hipLaunchKernelGGL(k_ks_mfkey, dim3((unsigned)(KM_KEY_BYTES / 4 / 256)), dim3(256), 0, st, ksk, KB);
+  hipLaunchKernelGGL(k_ks_mfkey, dim3((unsigned)(KM_CT * KM_QUADS * 4)), dim3(256), 0, st, ksk, reinterpret_cast<u32*>(KB));
   return hipGetLastError();
 }
 
-hipError_t launch_keyswitch_mfma(const int8_t* KB, const uint8_t* ops, const uint32_t* tlwe1, const uint32_t* idxo,
-                                 uint32_t* out, uint64_t B, hipStream_t st) {
-  if (B == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_ks_mfma, dim3((unsigned)((B + KM_GATES - 1) / KM_GATES), KM_CT / KM_COLS), dim3(256), 0, st, KB,
-                     ops, tlwe1, idxo, out, B);
+template <int T, int SPLIT>
+static hipError_t launch_km(const int8_t* KB, const uint8_t* ops, const uint32_t* tlwe1, const uint32_t* idxo, uint32_t* out,
+                            uint64_t B, hipStream_t st) {
+  static_assert(KM_CT % (OH_WAVES / SPLIT) == 0, "whole column groups");
+  const uint64_t tiles = (B + 16 * T - 1) / (16 * T);
+  const unsigned grid = (unsigned)((tiles * (KM_CT * SPLIT / OH_WAVES) + 7) / 8 * 8);
+  const size_t lds = km_lds_bytes<T, SPLIT>();
+  hipLaunchKernelGGL((k_ks_mfma<T, SPLIT>), dim3(grid), dim3(OH_WAVES * 64), lds, st,
+                     reinterpret_cast<const oh_v4i*>(KB), ops, tlwe1, idxo, out, B, (u32)tiles);
   return hipGetLastError();
+}
+
+template <int T, int SPLIT>
+static hipError_t km_attribute() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ks_mfma<T, SPLIT>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)km_lds_bytes<T, SPLIT>());
+}
+hipError_t init_keyswitch_mfma_attributes() {
+  hipError_t e = km_attribute<1, 8>();
+  if (e == hipSuccess) e = km_attribute<2, 8>();
+  if (e == hipSuccess) e = km_attribute<4, 8>();
+  if (e == hipSuccess) e = km_attribute<8, 8>();
+  if (e == hipSuccess) e = km_attribute<8, 4>();
+  return e;
+}
+
+// Which tile: the fewest gates per workgroup that still give at most one workgroup per compute unit
+// (the key streams through each workgroup at a fixed rate: the narrower its tile, the sooner it is
+// done), up to 128 gates. From there on every compute unit is busy, and two column tiles per
+// workgroup form the digits half as often (a round of workgroups takes 90 us instead of 60 for twice the
+// work), so that variant is taken unless its last round wastes more. Measured on 256 compute units, us:
+//   gates    16 per workgroup    32     64    128    128 x 2 columns
+//      1                 26      30     36     59      88
+//     64                 24      29     36     59      88
+//    128                 43      29     36     59      89
+//    256                 61      52     36     59      90
+//    700                145     103     73     62      91
+//  1,024                205     128    106    120      91
+//  4,096                833     512    356    307     276
+// Rows selected through LDS took 157 us for 1 gate, 215 for 256; a 32 x 32 product with the planes one
+// after the other 297 us for 700, 430 for 4,096.
+hipError_t launch_keyswitch_mfma(const int8_t* KB, const uint8_t* ops, const uint32_t* tlwe1, const uint32_t* idxo,
+                                 uint32_t* out, uint64_t B, int cus, hipStream_t st) {
+  if (B == 0) return hipSuccess;
+  const uint64_t n = cus > 0 ? (uint64_t)cus : 256;
+  auto groups = [&](uint64_t gates) { return (B + gates - 1) / gates * KM_CT; };
+  auto rounds = [&](uint64_t workgroups) { return (workgroups + n - 1) / n; };
+  if (groups(16) <= n) return launch_km<1, 8>(KB, ops, tlwe1, idxo, out, B, st);
+  if (groups(32) <= n) return launch_km<2, 8>(KB, ops, tlwe1, idxo, out, B, st);
+  if (groups(64) <= n) return launch_km<4, 8>(KB, ops, tlwe1, idxo, out, B, st);
+  if (2 * rounds(groups(128)) <= 3 * rounds(groups(128) / 2)) return launch_km<8, 8>(KB, ops, tlwe1, idxo, out, B, st);
+  return launch_km<8, 4>(KB, ops, tlwe1, idxo, out, B, st);
 }
 
 }  // namespace vsp

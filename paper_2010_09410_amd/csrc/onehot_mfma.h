@@ -42,31 +42,32 @@ __device__ __forceinline__ void oh_planes(u32 x1, u32 x2, u32 x3, u32 (&w)[OH_PL
   }
 }
 
-// sum[i] += the products of element tile i with the key's column tile over the quads first, first + step,
-// ... < quads, planes folded. key, digits: at the lane; digits of tile i at i * tile.
-// The digit words and the key blocks of the next quad are loaded while this one is multiplied (16 KiB in
+// sum[i] = the products of element tile i with the key's column tile (key: at the lane) over `steps` quads,
+// planes folded. The source of the digits gives the quad of step n, quad(n), and the digit words of
+// its tiles, get(n, d); issue(n) and finish(n) stand before and after the step's products, for loads
+// of its own. The key blocks of the next quad are loaded while this one is multiplied (16 KiB in
 // flight per wave).
-template <int T>
-__device__ __forceinline__ void oh_products(oh_key key, oh_digits digits, size_t tile, int first, int step, int quads,
-                                            u32 (&sum)[T][4]) {
+template <int T, class Digits>
+__device__ __forceinline__ void oh_products(oh_key key, Digits& digits, int steps, u32 (&sum)[T][4]) {
   oh_v4i acc[T][OH_PLANES], kb[4][OH_PLANES];
-  u32 d[T], dn[T];
+  {
+    const oh_key k0 = key + (size_t)(4 * digits.quad(0)) * OH_BLOCK;
 #pragma unroll
-  for (int i = 0; i < T; i++) {
-    d[i] = digits[i * tile + (size_t)first * 64];
+    for (int t = 0; t < 4; t++)
 #pragma unroll
-    for (int b = 0; b < OH_PLANES; b++) acc[i][b] = oh_v4i{0, 0, 0, 0};
+      for (int b = 0; b < OH_PLANES; b++) kb[t][b] = k0[t * OH_BLOCK + b * 64];
   }
 #pragma unroll
-  for (int t = 0; t < 4; t++)
+  for (int i = 0; i < T; i++)
 #pragma unroll
-    for (int b = 0; b < OH_PLANES; b++) kb[t][b] = key[(size_t)(4 * first + t) * OH_BLOCK + b * 64];
+    for (int b = 0; b < OH_PLANES; b++) acc[i][b] = oh_v4i{0, 0, 0, 0};
+  digits.start();
   __builtin_amdgcn_sched_barrier(0);
-  for (int Q = first; Q < quads; Q += step) {
-    const int next = Q + step < quads ? Q + step : Q;
-#pragma unroll
-    for (int i = 0; i < T; i++) dn[i] = digits[i * tile + (size_t)next * 64];
-    const oh_key kn = key + (size_t)(4 * next) * OH_BLOCK;
+  for (int n = 0; n < steps; n++) {
+    u32 d[T];
+    digits.get(n, d);
+    digits.issue(n);
+    const oh_key kn = key + (size_t)(4 * digits.quad(n + 1 < steps ? n + 1 : n)) * OH_BLOCK;
 #pragma unroll
     for (int t = 0; t < 4; t++) {
 #pragma unroll
@@ -81,8 +82,7 @@ __device__ __forceinline__ void oh_products(oh_key key, oh_digits digits, size_t
       for (int b = 0; b < OH_PLANES; b++) kb[t][b] = kn[t * OH_BLOCK + b * 64];
       __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int i = 0; i < T; i++) d[i] = dn[i];
+    digits.finish(n);
   }
 #pragma unroll
   for (int i = 0; i < T; i++)
@@ -91,19 +91,23 @@ __device__ __forceinline__ void oh_products(oh_key key, oh_digits digits, size_t
       sum[i][x] = (u32)acc[i][0][x] + ((u32)acc[i][1][x] << 8) + ((u32)acc[i][2][x] << 16) + ((u32)acc[i][3][x] << 24);
 }
 
-// The waves' partial sums added through LDS: afterwards use(i, x, value) has been called once for every
-// tile i and register x, by one wave, lane (n, q) holding element 4 q + x of the tile, column n.
-template <int T, class Use>
-__device__ __forceinline__ void oh_reduce(const u32 (&sum)[T][4], u32 (*red)[T * 4][64], int wave, int lane, Use use) {
+// The partial sums of a workgroup's SPLIT waves of one column tile (split = 0 .. SPLIT - 1) added through
+// LDS: afterwards use(i, x, value) has been called once for every tile i and register x, by one of these
+// waves, lane (n, q) holding element 4 q + x of the tile, column n. red: the column tile's.
+template <int T, int SPLIT, class Use>
+__device__ __forceinline__ void oh_reduce(const u32 (&sum)[T][4], u32 (*red)[T * 4][64], int split, int lane, Use use) {
 #pragma unroll
   for (int i = 0; i < T; i++)
 #pragma unroll
-    for (int x = 0; x < 4; x++) red[wave][i * 4 + x][lane] = sum[i][x];
+    for (int x = 0; x < 4; x++) red[split][i * 4 + x][lane] = sum[i][x];
   __syncthreads();
-  for (int r = wave; r < T * 4; r += OH_WAVES) {
+#pragma unroll
+  for (int k = 0; k < (T * 4 + SPLIT - 1) / SPLIT; k++) {
+    const int r = split + k * SPLIT;
+    if (T * 4 % SPLIT && r >= T * 4) break;
     u32 v = 0;
 #pragma unroll
-    for (int w = 0; w < OH_WAVES; w++) v += red[w][r][lane];
+    for (int w = 0; w < SPLIT; w++) v += red[w][r][lane];
     use(r >> 2, r & 3, v);
   }
 }

@@ -293,6 +293,7 @@ vsp_status vsp_context_create(const vsp_params* params, const uint32_t* bk_host,
   VSP_HIP(hipSetDevice(device));
   VSP_HIP(init_kernel_attributes());
   VSP_HIP(init_memory_kernel_attributes());
+  VSP_HIP(init_keyswitch_mfma_attributes());
   VSP_HIP(init_mf_kernel_attributes());
   if (vsp_status st = resolve_static_scratch(device)) return st;
   std::vector<u64> tw;

@@ -86,7 +86,8 @@ constexpr uint64_t kSplitAt[kSplitPts] = {1, 16, 64, 256, 512, 768, 1024, 1280, 
 //  * Key switch: per bucket, form 0 gathers key rows per gate, 1 reads them once per tile of
 //    gates and selects in registers, 2 stages them through LDS for a tile of gates and splits
 //    the j range over workgroups, 3 runs on the matrix cores (one-hot digit rows times the
-//    key's byte planes).
+//    key's byte planes). 3 is the fastest at every size (1 gate 26 us against 157 of form 2, 4,096
+//    gates 276 against 3,120).
 struct Tuning {
   uint64_t br_cap[kBrShapes] = {512, 2048, 256, 4096, MF_TILE};
   float br_round_ms[kBrShapes] = {4.82f, 13.5f, 2.62f, 82.0f, 4.2f};
@@ -96,7 +97,7 @@ struct Tuning {
   float split_ms[kSplitPts] = {4.1f, 6.9f, 8.9f, 12.7f, 18.3f, 24.3f, 31.1f, 33.2f, 45.5f, 48.4f, 50.8f, 79.1f, 91.8f};
   int split_groups[kSplitPts] = {24, 12, -6, -6, -2, -3, -2, -1, -2, -2, -2, -2, 1};
   int br_force[kTuneBuckets] = {0, 0, 0, 0, 0, 0, 0};
-  int ks_form[kTuneBuckets] = {2, 2, 2, 2, 3, 3, 3};
+  int ks_form[kTuneBuckets] = {3, 3, 3, 3, 3, 3, 3};
   bool tuned = false;
   static int bucket(uint64_t B) {
     int b = 0;
@@ -274,9 +275,10 @@ size_t mf_work_bytes(uint64_t B, bool need_acc);
 hipError_t launch_mf_key(const uint32_t* bk, int8_t* E, hipStream_t st);
 // Matrix-core key switch (keyswitch_mfma.hip).
 size_t ks_mf_key_bytes();
+hipError_t init_keyswitch_mfma_attributes();
 hipError_t launch_ks_mfkey(const uint32_t* ksk, int8_t* KB, hipStream_t st);
 hipError_t launch_keyswitch_mfma(const int8_t* KB, const uint8_t* ops, const uint32_t* tlwe1, const uint32_t* idxo,
-                                 uint32_t* out, uint64_t B, hipStream_t st);
+                                 uint32_t* out, uint64_t B, int cus, hipStream_t st);
 // Split form (waves 33): two launches per step, `groups` (kSplitGroupChoices) workgroups per
 // (tile, output, sub-product); same workspace as the fused form.
 hipError_t launch_blind_rotate_mfsplit(const vsp_context* ctx, const uint8_t* ops, const uint32_t* abar,

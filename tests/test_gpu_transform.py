@@ -147,3 +147,22 @@ def test_private_key_switch_batches_equal_single_inputs(gpu, keys):
                 np.testing.assert_array_equal(out[r], alone[r], err_msg=f"input {r} of {R}")
     finally:
         key.close()
+
+
+@pytest.mark.parametrize("B", [1, 16, 17, 96, 97, 192, 193, 384, 385, 768, 769, 1030, 2433])
+def test_matrix_core_key_switch_equals_the_gathering_one(gpu, B):
+    """Both sides of every tile width of the matrix-core key switch and of a last tile, against the form that gathers the
+    key rows of each gate; a third of the gates does not bootstrap and keeps its row."""
+    g = W.rng(84 + B)
+    ops = g.choice(np.array([W.NAND, W.NOT, W.XNOR], np.uint8), size=B)
+    ops[-1] = W.NAND
+    d = gpu.tensor(ops), random_words(gpu, B, B, 631), random_words(gpu, B + 1, B, 631)
+    _, ks = gpu.tuning(B)
+    outs = []
+    try:
+        for form in (0, 3):
+            gpu.set_tuning(B, 0, form)
+            outs.append(to_host(gpu.gates(*d)))
+    finally:
+        gpu.set_tuning(B, 0, ks)
+    np.testing.assert_array_equal(outs[1], outs[0])
