@@ -1,7 +1,8 @@
-// Latency forms of the blind rotation: one gate per workgroup of eight waves. A step is four phases
-// between barriers:
+// Latency forms: a chain of external products on one workgroup of eight waves, and the blind rotation
+// of one gate by it. A step, ACC <- ACC + C_i (ext) D_i with D_i formed from ACC, is four phases between
+// barriers:
 //  1. all waves add the last step's small products into their four coefficients per thread of ACC and
-//     form the digit words of X^a ACC - ACC (the new ACC is stored in phase 2, when all have read it);
+//     form the digit words of D_i (the new ACC is stored in phase 2, when all have read it);
 //  2. wave r < 6 transforms TRGSW row r's digits (gadget level r mod 3 + 1 of ACC polynomial r / 3);
 //  3. wave w takes slot w of the transform, 64 values, and adds the six rows' products with the three
 //     key polynomials;
@@ -33,25 +34,21 @@ constexpr size_t brw_lds_bytes() {
   return (size_t)(BRW_ROWS + FFT_PRODUCTS) * FFT8_REGION_C64 * 16 + 2 * RING_N * 4;
 }
 
-template <int AHEAD, int PER_SIMD>
-__global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(const c64* __restrict__ bkf,
-                                                                      const c64* __restrict__ tab8,
-                                                                      const uint8_t* __restrict__ ops,
-                                                                      const u32* __restrict__ abar,
-                                                                      u32* __restrict__ tlwe1, u32* __restrict__ trlwe,
-                                                                      uint64_t B, const c64* const* __restrict__ keytab,
-                                                                      const uint16_t* __restrict__ kid) {
-  extern __shared__ c64 lds[];
-  const uint64_t g = blockIdx.x;  // the grid has exactly B workgroups
-  if (ops && !op_bootstraps(ops[g])) return;  // uniform over the workgroup: no barrier is skipped by half
-  if (keytab) bkf = keytab[kid[g]];           // per-gate key (same value in every wave)
+// The chain, on ACC that the caller has put in LDS at brw_acc(lds) and reads there afterwards. `chain` says what a step is: chain.begin(i) stands at its start,
+// chain.key(i) is TRGSW C_i, and chain.words(acc, small, p, j, own, word) takes coefficient j of
+// polynomial p (at index p N + j of acc and of the small products still to be added) and gives the
+// accumulator that stays (own) and the digit word of D_i.
+__device__ __forceinline__ u32* brw_acc(c64* lds) {
+  return reinterpret_cast<u32*>(lds + (BRW_ROWS + FFT_PRODUCTS) * FFT8_REGION_C64);
+}
+template <int AHEAD, int PER_SIMD, class Chain>
+__device__ __forceinline__ void brw_chain(c64* lds, const c64* __restrict__ tab8, int steps, Chain& chain) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane0 = tid & 63;
   c64* sums = lds + BRW_ROWS * FFT8_REGION_C64;
-  u32* acc = reinterpret_cast<u32*>(sums + FFT_PRODUCTS * FFT8_REGION_C64);
+  u32* acc = brw_acc(lds);
   u32* words = reinterpret_cast<u32*>(sums);                       // [2][N], in the first sum's place
   u32* small = reinterpret_cast<u32*>(sums + 2 * FFT8_REGION_C64);  // [2][N], in the packed sum's place
   c64* reg = lds + (wave < BRW_ROWS ? wave : 0) * FFT8_REGION_C64;
-  const u32* ab = abar + g * TLWE0;
   Fft8Lane tab;
   tab.load(tab8, lane0);
   // wait for the table here: a wait left to its first use, inside the loop, would count the key
@@ -60,11 +57,10 @@ __global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(
   // this wave's slot of the key, row r = k + 3 e, product q: [k][slot][e][q][entry]. For the products
   // lane m takes entry m (contiguous loads); lane L of a transform owns entry fft_half_lane(L). Values
   // pass between the two by LDS places that spread both over all banks.
-  const gkey key0 = (gkey)bkf + wave * FFT_PIECE_C64 + lane0;
   auto place = [](int m) { return m ^ ((m >> 1) & 8) ^ ((m >> 3) & 4); };
   c64 key[AHEAD][FFT_PRODUCTS];
   auto load_rows = [&](int i, int r0, c64(&kv)[AHEAD][FFT_PRODUCTS]) {
-    const gkey ks = key0 + (size_t)i * TRGSW_FFT_C64;
+    const gkey ks = chain.key(i) + wave * FFT_PIECE_C64 + lane0;
 #pragma unroll
     for (int j = 0; j < AHEAD; j++)
 #pragma unroll
@@ -74,18 +70,10 @@ __global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(
       }
   };
   load_rows(0, 0, key);
-  {
-    const int k0 = (2 * RING_N - (int)ab[LWE_N]) & (2 * RING_N - 1);
-    for (int j = tid; j < 2 * RING_N; j += BRW_WAVES * 64) {
-      acc[j] = j < RING_N ? 0u : rotated_testvector(j - RING_N, k0);
-      small[j] = 0;
-    }
-  }
-  int a_next = (int)__builtin_amdgcn_readfirstlane(ab[0]);
+  for (int j = tid; j < 2 * RING_N; j += BRW_WAVES * 64) small[j] = 0u;
   __syncthreads();
-  for (int i = 0; i < LWE_N; i++) {
-    const int a = a_next;
-    a_next = (int)__builtin_amdgcn_readfirstlane(ab[i + 1]);  // (the last one is b)
+  for (int i = 0; i < steps; i++) {
+    chain.begin(i);
     double re[8], im[8];
     // with 128 registers the lane's LDS addresses are formed anew in every step instead of being kept
     const int lane = PER_SIMD > 2 ? opaque_lane(lane0) : lane0;
@@ -94,10 +82,7 @@ __global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(
 #pragma unroll
     for (int q = 0; q < 4; q++) {
       const int p = (q >> 1) * RING_N, j = (q & 1) * (RING_N / 2) + wave * 64 + lane;
-      own[q] = acc[p + j] + small[p + j];
-      const int r = j - a, at = p + (r & (RING_N - 1));
-      const u32 v = acc[at] + small[at];
-      words[p + j] = digit_word((r & RING_N ? 0u - v : v) - own[q]);
+      chain.words(acc, small, p, j, own[q], words[p + j]);
     }
     __syncthreads();
 #pragma unroll
@@ -132,7 +117,7 @@ __global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(
         sums[q * FFT8_REGION_C64 + wave * 64 + pm] = make_double2(sr[q], si[q]);
     }
     __syncthreads();
-    const int next = i + 1 < LWE_N ? i + 1 : i;
+    const int next = i + 1 < steps ? i + 1 : i;
     if (wave < FFT_PRODUCTS) {
       __builtin_amdgcn_s_setprio(3);  // the chain, against the other waves' loads
 #pragma unroll
@@ -170,6 +155,54 @@ __global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(
   }
   for (int j = tid; j < 2 * RING_N; j += BRW_WAVES * 64) acc[j] += small[j];
   __syncthreads();
+}
+
+// D = X^a ACC - ACC: a step of a blind rotation.
+__device__ __forceinline__ void brw_rotated(const u32* acc, const u32* small, int p, int j, int a, u32& own, u32& word) {
+  own = acc[p + j] + small[p + j];
+  const int r = j - a, at = p + (r & (RING_N - 1));
+  const u32 v = acc[at] + small[at];
+  word = digit_word((r & RING_N ? 0u - v : v) - own);
+}
+
+struct BlindChain {
+  const u32* ab;
+  gkey keys;
+  int a, next;
+  __device__ __forceinline__ void start() { next = (int)__builtin_amdgcn_readfirstlane(ab[0]); }
+  __device__ __forceinline__ void begin(int i) {
+    a = next;
+    next = (int)__builtin_amdgcn_readfirstlane(ab[i + 1]);  // (the last one is b)
+  }
+  __device__ __forceinline__ gkey key(int i) const { return keys + (size_t)i * TRGSW_FFT_C64; }
+  __device__ __forceinline__ void words(const u32* acc, const u32* small, int p, int j, u32& own, u32& word) const {
+    brw_rotated(acc, small, p, j, a, own, word);
+  }
+};
+
+template <int AHEAD, int PER_SIMD>
+__global__ __launch_bounds__(BRW_WAVES * 64, PER_SIMD) void k_blind_rotate_wide(const c64* __restrict__ bkf,
+                                                                      const c64* __restrict__ tab8,
+                                                                      const uint8_t* __restrict__ ops,
+                                                                      const u32* __restrict__ abar,
+                                                                      u32* __restrict__ tlwe1, u32* __restrict__ trlwe,
+                                                                      uint64_t B, const c64* const* __restrict__ keytab,
+                                                                      const uint16_t* __restrict__ kid) {
+  extern __shared__ c64 lds[];
+  const uint64_t g = blockIdx.x;  // the grid has exactly B workgroups
+  if (ops && !op_bootstraps(ops[g])) return;  // uniform over the workgroup: no barrier is skipped by half
+  if (keytab) bkf = keytab[kid[g]];           // per-gate key (same value in every wave)
+  const int tid = threadIdx.x;
+  u32* acc = brw_acc(lds);
+  BlindChain chain;
+  chain.ab = abar + g * TLWE0;
+  chain.keys = (gkey)bkf;
+  chain.start();
+  {
+    const int k0 = (2 * RING_N - (int)chain.ab[LWE_N]) & (2 * RING_N - 1);
+    for (int j = tid; j < 2 * RING_N; j += BRW_WAVES * 64) acc[j] = j < RING_N ? 0u : rotated_testvector(j - RING_N, k0);
+  }
+  brw_chain<AHEAD, PER_SIMD>(lds, tab8, LWE_N, chain);
   if (trlwe) {
     for (int j = tid; j < 2 * RING_N; j += BRW_WAVES * 64) trlwe[g * 2 * RING_N + j] = acc[j];
   }

@@ -3,7 +3,7 @@
 
 #include <algorithm>
 
-#include "vsp_internal.h"
+#include "blind_rotate_wide.h"
 
 namespace vsp {
 
@@ -113,6 +113,57 @@ __global__ __launch_bounds__(WAVES * 64) void k_rom_rotate(const c64* __restrict
   for (int t = 0; t < 32; t++) p[l + 32 * t] = accs[l + 32 * t];
 }
 
+// The same three on one workgroup of eight waves per chain (blind_rotate_wide.h), for launches that leave
+// the GPU mostly idle: a product takes 4 us instead of 22, on a whole compute unit.
+struct TreeChain {
+  const u32 *x0, *x1;
+  gkey sel;
+  __device__ __forceinline__ void begin(int) const {}
+  __device__ __forceinline__ gkey key(int) const { return sel; }
+  __device__ __forceinline__ void words(const u32*, const u32*, int p, int j, u32& own, u32& word) const {
+    own = x0[p + j];
+    word = digit_word(x1[p + j] - own);
+  }
+};
+__global__ __launch_bounds__(BRW_WAVES * 64, 2) void k_cmux_tree_wide(const c64* __restrict__ sel, uint64_t sel_r_stride,
+                                                              int selbit, const u32* __restrict__ in, uint64_t s_r,
+                                                              uint64_t s_b, u32* __restrict__ out, uint64_t per,
+                                                              uint64_t half, const c64* __restrict__ tab8) {
+  extern __shared__ c64 lds[];
+  const uint64_t r = blockIdx.x / per, w = blockIdx.x - r * per, blk = w / half, m = w - blk * half;
+  TreeChain chain;
+  chain.x0 = in + r * s_r + blk * s_b + (2 * m) * TRLWE_WORDS;
+  chain.x1 = chain.x0 + TRLWE_WORDS;
+  chain.sel = (gkey)sel + (r * sel_r_stride + (uint64_t)selbit) * TRGSW_FFT_C64;
+  brw_chain<6, 2>(lds, tab8, 1, chain);
+  const u32* acc = brw_acc(lds);
+  u32* o = out + (uint64_t)blockIdx.x * TRLWE_WORDS;
+  for (int j = threadIdx.x; j < TRLWE_WORDS; j += BRW_WAVES * 64) o[j] = acc[j];
+}
+
+struct RotateChain {
+  gkey sel;
+  int w, k;
+  __device__ __forceinline__ void begin(int i) { k = w << i; }
+  __device__ __forceinline__ gkey key(int i) const { return sel + (size_t)i * TRGSW_FFT_C64; }
+  __device__ __forceinline__ void words(const u32* acc, const u32* small, int p, int j, u32& own, u32& word) const {
+    brw_rotated(acc, small, p, j, -k, own, word);
+  }
+};
+__global__ __launch_bounds__(BRW_WAVES * 64, 2) void k_rom_rotate_wide(const c64* __restrict__ sel, uint64_t sel_r_stride,
+                                                               u32* __restrict__ accbuf, int rotbits, int w,
+                                                               const c64* __restrict__ tab8) {
+  extern __shared__ c64 lds[];
+  u32* acc = brw_acc(lds);
+  u32* p = accbuf + (uint64_t)blockIdx.x * TRLWE_WORDS;
+  for (int j = threadIdx.x; j < TRLWE_WORDS; j += BRW_WAVES * 64) acc[j] = p[j];
+  RotateChain chain;
+  chain.sel = (gkey)sel + blockIdx.x * sel_r_stride * TRGSW_FFT_C64;
+  chain.w = w;
+  brw_chain<6, 2>(lds, tab8, rotbits, chain);
+  for (int j = threadIdx.x; j < TRLWE_WORDS; j += BRW_WAVES * 64) p[j] = acc[j];
+}
+
 // SampleExtract_h for h < W: out[r][h] (N + 1 words) from in[r] = (A, B).
 __global__ __launch_bounds__(256) void k_sample_extract(const u32* __restrict__ in, u32* __restrict__ out, uint64_t R,
                                                         int W) {
@@ -180,6 +231,37 @@ __global__ __launch_bounds__(WAVES * 64) void k_ram_bars(const c64* __restrict__
   }
 }
 
+struct BarChain {
+  gkey sel, selneg;
+  uint64_t A;
+  __device__ __forceinline__ void begin(int) const {}
+  __device__ __forceinline__ gkey key(int d) const { return (((A >> d) & 1) ? sel : selneg) + (size_t)d * TRGSW_FFT_C64; }
+  __device__ __forceinline__ void words(const u32* acc, const u32* small, int p, int j, u32& own, u32& word) const {
+    own = 0;
+    word = digit_word(acc[p + j] + small[p + j]);
+  }
+};
+__global__ __launch_bounds__(BRW_WAVES * 64, 2) void k_ram_bars_wide(const c64* __restrict__ sel, const c64* __restrict__ selneg,
+                                                             const u32* __restrict__ ram, const u32* __restrict__ u,
+                                                             u32* __restrict__ tlwe1, int v, const c64* __restrict__ tab8) {
+  extern __shared__ c64 lds[];
+  u32* acc = brw_acc(lds);
+  const uint64_t bar = blockIdx.x, i = bar >> v;
+  const u32 *old = ram + bar * TRLWE_WORDS, *ui = u + i * TRLWE_WORDS;
+  for (int j = threadIdx.x; j < TRLWE_WORDS; j += BRW_WAVES * 64) acc[j] = ui[j] - old[j];
+  BarChain chain;
+  chain.sel = (gkey)sel;
+  chain.selneg = (gkey)selneg;
+  chain.A = bar & ((1ull << v) - 1);
+  brw_chain<6, 2>(lds, tab8, v, chain);
+  u32* out = tlwe1 + bar * (RING_N + 1);
+  for (int j = threadIdx.x; j < RING_N; j += BRW_WAVES * 64) {
+    const u32 z = acc[j] + old[j];
+    out[(RING_N - j) & (RING_N - 1)] = (j == 0) ? z : 0u - z;
+  }
+  if (threadIdx.x == 0) out[RING_N] = acc[RING_N] + old[RING_N];
+}
+
 // G - C: negate every coefficient of C and add the gadget constants of the trivial TRGSW(1).
 __global__ __launch_bounds__(256) void k_gadget_minus(const u32* __restrict__ C, u32* __restrict__ out, uint64_t count) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -204,9 +286,9 @@ __global__ __launch_bounds__(256) void k_broadcast(const u32* __restrict__ src, 
 // ------------------------------------------------------------------ launchers
 static unsigned blocks_for(uint64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-// The CMUX kernels in two shapes: eight waves per workgroup (two waves per SIMD once every CU
+// The CMUX kernels in three shapes: eight waves per workgroup (two waves per SIMD once every CU
 // holds one workgroup) for wide launches, one wave per workgroup for narrow ones, where
-// spreading the few chains over all CUs shortens the launch.
+// spreading the few chains over all CUs shortens the launch, and a workgroup per chain for the fewest.
 hipError_t init_memory_kernel_attributes() {
   const struct {
     const void* fn;
@@ -216,12 +298,21 @@ hipError_t init_memory_kernel_attributes() {
            {reinterpret_cast<const void*>(&k_rom_rotate<8>), mem_lds_bytes(8, false, true)},
            {reinterpret_cast<const void*>(&k_rom_rotate<1>), mem_lds_bytes(1, false, true)},
            {reinterpret_cast<const void*>(&k_ram_bars<8>), mem_lds_bytes(8, false, false)},
-           {reinterpret_cast<const void*>(&k_ram_bars<1>), mem_lds_bytes(1, false, false)}};
+           {reinterpret_cast<const void*>(&k_ram_bars<1>), mem_lds_bytes(1, false, false)},
+           {reinterpret_cast<const void*>(&k_cmux_tree_wide), brw_lds_bytes()},
+           {reinterpret_cast<const void*>(&k_rom_rotate_wide), brw_lds_bytes()},
+           {reinterpret_cast<const void*>(&k_ram_bars_wide), brw_lds_bytes()}};
   for (const auto& x : k)
     if (hipError_t e = hipFuncSetAttribute(x.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)x.lds)) return e;
   return hipSuccess;
 }
 
+// Up to two chains per compute unit take a workgroup each: a round of them (one per unit) takes 5 us a
+// product where one wave takes 22, so four rounds would be even, and at three the selectors' stream
+// from memory, 147 KB each, bounds both. Measured, wide against one wave: 1 ROM read of 9 selectors
+// 0.11 and 0.21 ms; 256 (256 rotation chains, tree levels of 512 and 256) 0.90 and 0.98, with the level of
+// 1,024 wide too 0.92.
+static bool few_chains(const vsp_context* ctx, uint64_t chains) { return chains <= 2ull * (uint64_t)ctx->cus; }
 static bool wide_launch(const vsp_context* ctx, uint64_t chains) { return chains >= 8ull * (uint64_t)ctx->cus; }
 
 hipError_t launch_cmux_tree_level(const vsp_context* ctx, const c64* sel, uint64_t sel_r_stride, int selbit,
@@ -234,6 +325,9 @@ hipError_t launch_cmux_tree_level(const vsp_context* ctx, const c64* sel, uint64
     hipLaunchKernelGGL((k_cmux_tree_level<8, true>), dim3((unsigned)(R * ((per + 7) / 8))), dim3(512),
                        mem_lds_bytes(8, true, false), st, sel, sel_r_stride, selbit, in, s_r, s_b, out, R, per, W / 2,
                        ctx->ftab);
+  else if (few_chains(ctx, R * per))
+    hipLaunchKernelGGL(k_cmux_tree_wide, dim3((unsigned)(R * per)), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, sel,
+                       sel_r_stride, selbit, in, s_r, s_b, out, per, W / 2, ctx->ftab + FFT_TAB_C64);
   else
     hipLaunchKernelGGL((k_cmux_tree_level<1, false>), dim3(blocks_for(R * per, 1)), dim3(64),
                        mem_lds_bytes(1, false, false), st, sel, sel_r_stride, selbit, in, s_r, s_b, out, R, per, W / 2,
@@ -244,6 +338,11 @@ hipError_t launch_cmux_tree_level(const vsp_context* ctx, const c64* sel, uint64
 hipError_t launch_rom_rotate(const vsp_context* ctx, const c64* sel, uint64_t sel_r_stride, uint32_t* acc,
                              uint64_t R, int rotbits, int w, hipStream_t st) {
   if (R == 0 || rotbits == 0) return hipSuccess;
+  if (few_chains(ctx, R)) {
+    hipLaunchKernelGGL(k_rom_rotate_wide, dim3((unsigned)R), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, sel, sel_r_stride, acc,
+                       rotbits, w, ctx->ftab + FFT_TAB_C64);
+    return hipGetLastError();
+  }
   const int waves = wide_launch(ctx, R) ? 8 : 1;
   hipLaunchKernelGGL(waves == 8 ? &k_rom_rotate<8> : &k_rom_rotate<1>, dim3(blocks_for(R, waves)), dim3(64 * waves),
                      mem_lds_bytes(waves, false, true), st, sel, sel_r_stride, acc, R, rotbits, w, ctx->ftab);
@@ -265,6 +364,11 @@ hipError_t launch_ram_control(const uint32_t* acc2, uint32_t* u, int w, hipStrea
 hipError_t launch_ram_bars(const vsp_context* ctx, const c64* sel, const c64* selneg, const uint32_t* ram,
                            const uint32_t* u, uint32_t* tlwe1, int v, int w, hipStream_t st) {
   const uint64_t bars = (uint64_t)w << v;
+  if (v > 0 && few_chains(ctx, bars)) {
+    hipLaunchKernelGGL(k_ram_bars_wide, dim3((unsigned)bars), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, sel, selneg, ram, u,
+                       tlwe1, v, ctx->ftab + FFT_TAB_C64);
+    return hipGetLastError();
+  }
   const int waves = wide_launch(ctx, bars) ? 8 : 1;
   hipLaunchKernelGGL(waves == 8 ? &k_ram_bars<8> : &k_ram_bars<1>, dim3(blocks_for(bars, waves)), dim3(64 * waves),
                      mem_lds_bytes(waves, false, false), st, sel, selneg, ram, u, tlwe1, v, w, ctx->ftab);

@@ -166,3 +166,19 @@ def test_matrix_core_key_switch_equals_the_gathering_one(gpu, B):
     finally:
         gpu.set_tuning(B, 0, ks)
     np.testing.assert_array_equal(outs[1], outs[0])
+
+
+def test_chains_on_a_workgroup_equal_those_on_a_wave(gpu):
+    """Up to two CMUX chains per compute unit (512 here) take a workgroup each: reads and write bars just above the line,
+    one wave each, give what the same ones give below it (pinned by the oracle in test_gpu_memory.py)."""
+    v, w = 7, 64                                        # two cells a ROM polynomial pair, rotations of 64 << j
+    rom, addr = random_words(gpu, 5, 8, 2, N), random_words(gpu, 6, 513, v, 6, 2, N)
+    out = to_host(gpu.rom_read(rom, addr, v, w))
+    for a, b in ((0, 512), (1, 513), (511, 512)):       # tree levels of 4, 2 and 1 per read, rotations
+        np.testing.assert_array_equal(out[a:b], to_host(gpu.rom_read(rom, addr[a:b].contiguous(), v, w)))
+    ram, sel = random_words(gpu, 7, 3, 256, 2, N), random_words(gpu, 8, 8, 6, 2, N)       # 768 bars against 512
+    flag, data = random_words(gpu, 9, 631), random_words(gpu, 10, 3, 631)
+    whole, part = ram.clone(), ram[:2].contiguous().clone()
+    gpu.ram_write(whole, sel, flag, data)
+    gpu.ram_write(part, sel, flag, data[:2].contiguous())
+    np.testing.assert_array_equal(to_host(whole)[:2], to_host(part))
