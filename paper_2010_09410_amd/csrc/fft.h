@@ -172,6 +172,80 @@ __device__ __forceinline__ void fft_pass_inverse(double (&re)[M], double (&im)[M
   }
 }
 
+// The two with the constants of a lane in LDS: those of the next splitting are read while one is
+// computed. first: the one of the first splitting (of the last four, for the inverse: read before).
+template <int S>
+__device__ __forceinline__ void fft_lane_constants(c64 (&w)[(1 << S) > 1 ? (1 << S) >> 1 : 1], const c64* tab) {
+  constexpr int n = (1 << S) > 1 ? (1 << S) >> 1 : 1;
+#pragma unroll
+  for (int e = 0; e < n; e++) w[e] = tab[(((1 << S) >> 1) + e) * 32];
+}
+template <int S>
+__device__ __forceinline__ void fft_lane_level(double (&re)[16], double (&im)[16], const c64 (&w)[(1 << S) > 1 ? (1 << S) >> 1 : 1]) {
+  constexpr int H = 8 >> S;
+#pragma unroll
+  for (int b = 0; b < (1 << S); b++) {
+    const c64 v = w[b >> 1];
+#pragma unroll
+    for (int j = 0; j < H; j++) {
+      const int i = 2 * H * b + j;
+      if (b & 1)
+        fft_split(re[i], im[i], re[i + H], im[i + H], -v.y, v.x);
+      else
+        fft_split(re[i], im[i], re[i + H], im[i + H], v.x, v.y);
+    }
+  }
+}
+__device__ __forceinline__ void fft_pass_lane(double (&re)[16], double (&im)[16], const c64* tab, const c64 (&w0)[1]) {
+  c64 w1[1], w2[2], w3[4];
+  fft_lane_constants<1>(w1, tab);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_level<0>(re, im, w0);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_constants<2>(w2, tab);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_level<1>(re, im, w1);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_constants<3>(w3, tab);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_level<2>(re, im, w2);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_level<3>(re, im, w3);
+}
+
+template <int S>
+__device__ __forceinline__ void fft_lane_level_inverse(double (&re)[16], double (&im)[16], const c64 (&w)[(1 << S) > 1 ? (1 << S) >> 1 : 1]) {
+  constexpr int H = 8 >> S;
+#pragma unroll
+  for (int b = 0; b < (1 << S); b++) {
+    const c64 v = w[b >> 1];
+#pragma unroll
+    for (int j = 0; j < H; j++) {
+      const int i = 2 * H * b + j;
+      if (b & 1)
+        fft_join(re[i], im[i], re[i + H], im[i + H], -v.y, v.x);
+      else
+        fft_join(re[i], im[i], re[i + H], im[i + H], v.x, v.y);
+    }
+  }
+}
+__device__ __forceinline__ void fft_pass_lane_inverse(double (&re)[16], double (&im)[16], const c64* tab) {
+  c64 w0[1], w1[1], w2[2], w3[4];
+  fft_lane_constants<3>(w3, tab);
+  fft_lane_constants<2>(w2, tab);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_level_inverse<3>(re, im, w3);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_constants<1>(w1, tab);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_level_inverse<2>(re, im, w2);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_constants<0>(w0, tab);
+  __builtin_amdgcn_sched_barrier(0);
+  fft_lane_level_inverse<1>(re, im, w1);
+  fft_lane_level_inverse<0>(re, im, w0);
+}
+
 // v_permlane16_swap / v_permlane32_swap on 64-bit values: the odd rows of 16 lanes of a change
 // places with the even rows of b; the upper 32 lanes of a with the lower 32 of b.
 __device__ __forceinline__ void swap16(double& a, double& b) {
@@ -225,6 +299,9 @@ __device__ __forceinline__ void fft_forward(double (&re)[16], double (&im)[16], 
   fft_exchange(re, reg, l);
   fft_exchange(im, reg, l);
   const c64 w = tab[8 * 32 + l];
+  c64 w0[1];
+  fft_lane_constants<0>(w0, tab + l);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int q = 0; q < 8; q++) fft_split(re[q], im[q], re[8 + q], im[8 + q], w.x, w.y);
 #pragma unroll
@@ -232,12 +309,12 @@ __device__ __forceinline__ void fft_forward(double (&re)[16], double (&im)[16], 
     swap16(re[q], re[8 + q]);
     swap16(im[q], im[8 + q]);
   }
-  fft_pass(re, im, FftLane{tab + l});
+  fft_pass_lane(re, im, tab + l, w0);
 }
 // Inverse transform, times 512.
 __device__ __forceinline__ void fft_inverse(double (&re)[16], double (&im)[16], const c64* tab, double* reg, int l) {
-  fft_pass_inverse(re, im, FftLane{tab + l});
   const c64 w = tab[8 * 32 + l];
+  fft_pass_lane_inverse(re, im, tab + l);
 #pragma unroll
   for (int q = 0; q < 8; q++) {
     swap16(re[q], re[8 + q]);
