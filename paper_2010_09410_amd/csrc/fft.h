@@ -395,9 +395,38 @@ __device__ __forceinline__ void fft8_transpose(double (&re)[8], double (&im)[8],
   }
   wave_lds_sync();
 }
+// Register bits against lane bits 3-5, the same exchange without LDS (and its own inverse): bit 2 with lane
+// bit 5, bit 1 with lane bit 4 by swaps, bit 0 with lane bit 3 by rotations of the rows by 8.
+__device__ __forceinline__ void swap8(double& a, double& b) {
+  const u64 x = __builtin_bit_cast(u64, a), y = __builtin_bit_cast(u64, b);
+  u32 p[2], q[2];
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const int u = (int)(x >> (32 * i)), v = (int)(y >> (32 * i));
+    p[i] = (u32)__builtin_amdgcn_update_dpp(u, v, 0x128, 0xf, 0xc, false);  // row_ror:8 into lanes 8-15
+    q[i] = (u32)__builtin_amdgcn_update_dpp(v, u, 0x128, 0xf, 0x3, false);  // into lanes 0-7
+  }
+  a = __builtin_bit_cast(double, ((u64)p[1] << 32) | p[0]);
+  b = __builtin_bit_cast(double, ((u64)q[1] << 32) | q[0]);
+}
+__device__ __forceinline__ void fft8_rows(double (&v)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; i++) swap32(v[i], v[i + 4]);
+#pragma unroll
+  for (int i = 0; i < 4; i++) swap16(v[i + (i & 2)], v[i + (i & 2) + 2]);
+#pragma unroll
+  for (int i = 0; i < 8; i += 2) swap8(v[i], v[i + 1]);
+}
+// LDS: the first exchange goes through LDS (with free LDS it is the shorter one), else through the VALU.
+template <bool LDS>
 __device__ __forceinline__ void fft8_forward(double (&re)[8], double (&im)[8], const Fft8Lane& tab, c64* reg, int lane) {
   fft_pass(re, im, FftConst{});
-  fft8_to_rows(re, im, reg, lane);
+  if (LDS) {
+    fft8_to_rows(re, im, reg, lane);
+  } else {
+    fft8_rows(re);
+    fft8_rows(im);
+  }
   fft_pass(re, im, Fft8Pass{tab.w});
   fft8_transpose(re, im, reg, lane);
   fft_pass(re, im, Fft8Pass{tab.w + 4});

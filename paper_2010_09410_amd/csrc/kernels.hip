@@ -176,8 +176,8 @@ hipError_t init_kernel_attributes() {
     size_t lds;
   } k[] = {{reinterpret_cast<const void*>(&k_blind_rotate<8, true>), br_lds_bytes(8, true)},
            {reinterpret_cast<const void*>(&k_blind_rotate<8, false>), br_lds_bytes(8, false)},
-           {reinterpret_cast<const void*>(&k_blind_rotate_wide<1, 4>), brw_lds_bytes()},
-           {reinterpret_cast<const void*>(&k_blind_rotate_wide<6, 2>), brw_lds_bytes()}};
+           {reinterpret_cast<const void*>(&k_blind_rotate_wide<1>), brw_lds_bytes(1)},
+           {reinterpret_cast<const void*>(&k_blind_rotate_wide<2>), brw_lds_bytes(2)}};
   for (const auto& x : k)
     if (hipError_t e = hipFuncSetAttribute(x.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)x.lds)) return e;
   return hipSuccess;
@@ -187,19 +187,19 @@ hipError_t blind_rotate_capacity(int device, uint64_t (&cap)[kBrShapes]) {
   int cus = 0, n4 = 0, n8 = 0, nw = 0;
   hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n4, reinterpret_cast<const void*>(&k_blind_rotate_wide<1, 4>),
-                                                     BRW_WAVES * 64, brw_lds_bytes());
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n4, reinterpret_cast<const void*>(&k_blind_rotate_wide<2>),
+                                                     BRW_WAVES * 64, brw_lds_bytes(2));
   if (e == hipSuccess)
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n8, reinterpret_cast<const void*>(&k_blind_rotate<8, true>), 512,
                                                      br_lds_bytes(8, true));
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nw, reinterpret_cast<const void*>(&k_blind_rotate_wide<6, 2>),
-                                                     BRW_WAVES * 64, brw_lds_bytes());
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nw, reinterpret_cast<const void*>(&k_blind_rotate_wide<1>),
+                                                     BRW_WAVES * 64, brw_lds_bytes(1));
   if (e != hipSuccess) return e;
   static_assert(kBrWaveChoices[0] == 4 && kBrWaveChoices[1] == 8 && kBrWaveChoices[2] == 3 && kBrWaveChoices[3] == 32 &&
                     kBrWaveChoices[4] == 33,
                 "shape order");
-  cap[0] = (uint64_t)(n4 > 0 ? n4 : 1) * (uint64_t)cus;
+  cap[0] = (uint64_t)(n4 > 0 ? n4 : 1) * (uint64_t)cus * 2;
   cap[1] = (uint64_t)(n8 > 0 ? n8 : 1) * (uint64_t)cus * 8;
   cap[2] = (uint64_t)(nw > 0 ? nw : 1) * (uint64_t)cus;
   // matrix-core form: one workgroup per compute unit holds half a tile of MF_TILE gates
@@ -226,9 +226,22 @@ hipError_t launch_blind_rotate(const vsp_context* ctx, const uint8_t* ops, const
     waves = ctx->tune.br_waves(B, true);
   }
   if (waves == 3 || waves == 4) {
-    auto* kern = waves == 3 ? &k_blind_rotate_wide<6, 2> : &k_blind_rotate_wide<1, 4>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, bkf,
-                       ctx->ftab + FFT_TAB_C64, ops, abar, tlwe1, trlwe, B, keytab, kid);
+    // Whole rounds of two gates per compute unit as pairs (4.04 ms for 512 gates, 4.75 one by one). The rest,
+    // for form 3 and where it leaves a compute unit to each gate (2.38 ms), one per workgroup, else as
+    // pairs too. Per-gate keys: one gate per workgroup.
+    uint64_t pairs = 0;
+    if (keytab == nullptr) {
+      const uint64_t cus = ctx->cus > 0 ? (uint64_t)ctx->cus : 256, last = B % (2 * cus);
+      pairs = waves == 3 || last <= cus ? B - last : B;
+      if (pairs)
+        hipLaunchKernelGGL(k_blind_rotate_wide<2>, dim3((unsigned)((pairs + 1) / 2)), dim3(BRW_WAVES * 64), brw_lds_bytes(2), st,
+                           bkf, ctx->ftab + FFT_TAB_C64, ops, abar, tlwe1, trlwe, pairs, keytab, kid);
+    }
+    if (B > pairs)
+      hipLaunchKernelGGL(k_blind_rotate_wide<1>, dim3((unsigned)(B - pairs)), dim3(BRW_WAVES * 64), brw_lds_bytes(1), st, bkf,
+                         ctx->ftab + FFT_TAB_C64, ops ? ops + pairs : nullptr, abar + pairs * TLWE0,
+                         tlwe1 ? tlwe1 + pairs * TLWE1 : nullptr, trlwe ? trlwe + pairs * 2 * RING_N : nullptr, B - pairs,
+                         keytab, kid);
   } else {
     // one key for all gates: the workgroup shares it; per-gate keys: each wave reads its own
     auto* kern = keytab ? &k_blind_rotate<8, false> : &k_blind_rotate<8, true>;

@@ -120,7 +120,7 @@ struct TreeChain {
   gkey sel;
   __device__ __forceinline__ void begin(int) const {}
   __device__ __forceinline__ gkey key(int) const { return sel; }
-  __device__ __forceinline__ void words(const u32*, const u32*, int p, int j, u32& own, u32& word) const {
+  __device__ __forceinline__ void words(int, const u32*, const u32*, int p, int j, u32& own, u32& word) const {
     own = x0[p + j];
     word = digit_word(x1[p + j] - own);
   }
@@ -135,8 +135,8 @@ __global__ __launch_bounds__(BRW_WAVES * 64, 2) void k_cmux_tree_wide(const c64*
   chain.x0 = in + r * s_r + blk * s_b + (2 * m) * TRLWE_WORDS;
   chain.x1 = chain.x0 + TRLWE_WORDS;
   chain.sel = (gkey)sel + (r * sel_r_stride + (uint64_t)selbit) * TRGSW_FFT_C64;
-  brw_chain<6, 2>(lds, tab8, 1, chain);
-  const u32* acc = brw_acc(lds);
+  brw_chain<1>(lds, tab8, 1, chain);
+  const u32* acc = brw_acc<1>(lds, 0);
   u32* o = out + (uint64_t)blockIdx.x * TRLWE_WORDS;
   for (int j = threadIdx.x; j < TRLWE_WORDS; j += BRW_WAVES * 64) o[j] = acc[j];
 }
@@ -146,7 +146,7 @@ struct RotateChain {
   int w, k;
   __device__ __forceinline__ void begin(int i) { k = w << i; }
   __device__ __forceinline__ gkey key(int i) const { return sel + (size_t)i * TRGSW_FFT_C64; }
-  __device__ __forceinline__ void words(const u32* acc, const u32* small, int p, int j, u32& own, u32& word) const {
+  __device__ __forceinline__ void words(int, const u32* acc, const u32* small, int p, int j, u32& own, u32& word) const {
     brw_rotated(acc, small, p, j, -k, own, word);
   }
 };
@@ -154,13 +154,13 @@ __global__ __launch_bounds__(BRW_WAVES * 64, 2) void k_rom_rotate_wide(const c64
                                                                u32* __restrict__ accbuf, int rotbits, int w,
                                                                const c64* __restrict__ tab8) {
   extern __shared__ c64 lds[];
-  u32* acc = brw_acc(lds);
+  u32* acc = brw_acc<1>(lds, 0);
   u32* p = accbuf + (uint64_t)blockIdx.x * TRLWE_WORDS;
   for (int j = threadIdx.x; j < TRLWE_WORDS; j += BRW_WAVES * 64) acc[j] = p[j];
   RotateChain chain;
   chain.sel = (gkey)sel + blockIdx.x * sel_r_stride * TRGSW_FFT_C64;
   chain.w = w;
-  brw_chain<6, 2>(lds, tab8, rotbits, chain);
+  brw_chain<1>(lds, tab8, rotbits, chain);
   for (int j = threadIdx.x; j < TRLWE_WORDS; j += BRW_WAVES * 64) p[j] = acc[j];
 }
 
@@ -236,7 +236,7 @@ struct BarChain {
   uint64_t A;
   __device__ __forceinline__ void begin(int) const {}
   __device__ __forceinline__ gkey key(int d) const { return (((A >> d) & 1) ? sel : selneg) + (size_t)d * TRGSW_FFT_C64; }
-  __device__ __forceinline__ void words(const u32* acc, const u32* small, int p, int j, u32& own, u32& word) const {
+  __device__ __forceinline__ void words(int, const u32* acc, const u32* small, int p, int j, u32& own, u32& word) const {
     own = 0;
     word = digit_word(acc[p + j] + small[p + j]);
   }
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(BRW_WAVES * 64, 2) void k_ram_bars_wide(const c64* 
                                                              const u32* __restrict__ ram, const u32* __restrict__ u,
                                                              u32* __restrict__ tlwe1, int v, const c64* __restrict__ tab8) {
   extern __shared__ c64 lds[];
-  u32* acc = brw_acc(lds);
+  u32* acc = brw_acc<1>(lds, 0);
   const uint64_t bar = blockIdx.x, i = bar >> v;
   const u32 *old = ram + bar * TRLWE_WORDS, *ui = u + i * TRLWE_WORDS;
   for (int j = threadIdx.x; j < TRLWE_WORDS; j += BRW_WAVES * 64) acc[j] = ui[j] - old[j];
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(BRW_WAVES * 64, 2) void k_ram_bars_wide(const c64* 
   chain.sel = (gkey)sel;
   chain.selneg = (gkey)selneg;
   chain.A = bar & ((1ull << v) - 1);
-  brw_chain<6, 2>(lds, tab8, v, chain);
+  brw_chain<1>(lds, tab8, v, chain);
   u32* out = tlwe1 + bar * (RING_N + 1);
   for (int j = threadIdx.x; j < RING_N; j += BRW_WAVES * 64) {
     const u32 z = acc[j] + old[j];
@@ -299,9 +299,9 @@ hipError_t init_memory_kernel_attributes() {
            {reinterpret_cast<const void*>(&k_rom_rotate<1>), mem_lds_bytes(1, false, true)},
            {reinterpret_cast<const void*>(&k_ram_bars<8>), mem_lds_bytes(8, false, false)},
            {reinterpret_cast<const void*>(&k_ram_bars<1>), mem_lds_bytes(1, false, false)},
-           {reinterpret_cast<const void*>(&k_cmux_tree_wide), brw_lds_bytes()},
-           {reinterpret_cast<const void*>(&k_rom_rotate_wide), brw_lds_bytes()},
-           {reinterpret_cast<const void*>(&k_ram_bars_wide), brw_lds_bytes()}};
+           {reinterpret_cast<const void*>(&k_cmux_tree_wide), brw_lds_bytes(1)},
+           {reinterpret_cast<const void*>(&k_rom_rotate_wide), brw_lds_bytes(1)},
+           {reinterpret_cast<const void*>(&k_ram_bars_wide), brw_lds_bytes(1)}};
   for (const auto& x : k)
     if (hipError_t e = hipFuncSetAttribute(x.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)x.lds)) return e;
   return hipSuccess;
@@ -326,7 +326,7 @@ hipError_t launch_cmux_tree_level(const vsp_context* ctx, const c64* sel, uint64
                        mem_lds_bytes(8, true, false), st, sel, sel_r_stride, selbit, in, s_r, s_b, out, R, per, W / 2,
                        ctx->ftab);
   else if (few_chains(ctx, R * per))
-    hipLaunchKernelGGL(k_cmux_tree_wide, dim3((unsigned)(R * per)), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, sel,
+    hipLaunchKernelGGL(k_cmux_tree_wide, dim3((unsigned)(R * per)), dim3(BRW_WAVES * 64), brw_lds_bytes(1), st, sel,
                        sel_r_stride, selbit, in, s_r, s_b, out, per, W / 2, ctx->ftab + FFT_TAB_C64);
   else
     hipLaunchKernelGGL((k_cmux_tree_level<1, false>), dim3(blocks_for(R * per, 1)), dim3(64),
@@ -339,7 +339,7 @@ hipError_t launch_rom_rotate(const vsp_context* ctx, const c64* sel, uint64_t se
                              uint64_t R, int rotbits, int w, hipStream_t st) {
   if (R == 0 || rotbits == 0) return hipSuccess;
   if (few_chains(ctx, R)) {
-    hipLaunchKernelGGL(k_rom_rotate_wide, dim3((unsigned)R), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, sel, sel_r_stride, acc,
+    hipLaunchKernelGGL(k_rom_rotate_wide, dim3((unsigned)R), dim3(BRW_WAVES * 64), brw_lds_bytes(1), st, sel, sel_r_stride, acc,
                        rotbits, w, ctx->ftab + FFT_TAB_C64);
     return hipGetLastError();
   }
@@ -365,7 +365,7 @@ hipError_t launch_ram_bars(const vsp_context* ctx, const c64* sel, const c64* se
                            const uint32_t* u, uint32_t* tlwe1, int v, int w, hipStream_t st) {
   const uint64_t bars = (uint64_t)w << v;
   if (v > 0 && few_chains(ctx, bars)) {
-    hipLaunchKernelGGL(k_ram_bars_wide, dim3((unsigned)bars), dim3(BRW_WAVES * 64), brw_lds_bytes(), st, sel, selneg, ram, u,
+    hipLaunchKernelGGL(k_ram_bars_wide, dim3((unsigned)bars), dim3(BRW_WAVES * 64), brw_lds_bytes(1), st, sel, selneg, ram, u,
                        tlwe1, v, ctx->ftab + FFT_TAB_C64);
     return hipGetLastError();
   }

@@ -182,3 +182,22 @@ def test_chains_on_a_workgroup_equal_those_on_a_wave(gpu):
     gpu.ram_write(whole, sel, flag, data)
     gpu.ram_write(part, sel, flag, data[:2].contiguous())
     np.testing.assert_array_equal(to_host(whole)[:2], to_host(part))
+
+
+@pytest.mark.parametrize("B", [511, 512, 513, 769, 1023])
+def test_pairs_of_gates_equal_single_ones(gpu, B):
+    """Workgroups of two gates (whole rounds of two per compute unit, an odd last pair) and the mixture with workgroups of
+    one gate give what the key-sharing form gives; a third of the gates does not bootstrap."""
+    g = W.rng(85 + B)
+    ops = g.choice(np.array([W.NAND, W.NOT, W.XNOR], np.uint8), size=B)
+    d = gpu.tensor(ops), random_words(gpu, B + 2, B, 631), random_words(gpu, B + 3, B, 631)
+    _, ks = gpu.tuning(B)
+    outs = []
+    try:
+        for form in (8, 4, 3):
+            gpu.set_tuning(B, form, ks)
+            outs.append(to_host(gpu.gates(*d)))
+    finally:
+        gpu.set_tuning(B, 0, ks)
+    for o in outs[1:]:
+        np.testing.assert_array_equal(o, outs[0])
