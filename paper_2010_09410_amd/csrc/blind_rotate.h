@@ -34,7 +34,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_blind_rotate(const c64* __restri
   c64* tabs = lds;
   c64* ring = lds + FFT_TAB_C64;
   for (int i = threadIdx.x; i < FFT_TAB_C64; i += WAVES * 64) tabs[i] = tab[i];
-  SharedKey<WAVES> shared;
+  SharedKey<WAVES, false> shared;
   if (SHARED) shared.start((gkey)bkf, ring, LWE_N * FFT_PIECES);
   __syncthreads();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -662,12 +662,14 @@ struct GlobalKey {
 // transformed key, 147 KB a step, through the vector cache for every gate. The threads past a
 // piece's 384 entries load and write the first ones a second time (the same values): waves that
 // branch around it cost more.
-template <int WAVES>
+// ROUNDS: the pieces come round again after the last one, for several products with the same TRGSW.
+template <int WAVES, bool ROUNDS>
 struct SharedKey {
   static constexpr int PER = (FFT_PIECE_C64 + WAVES * 64 - 1) / (WAVES * 64);  // 16-byte entries per thread
   gkey src;    // start of the next piece to load
   c64* ring;   // [2][FFT_PIECE_C64]
   int left;    // pieces still to load
+  int cycle;   // of so many
   c64 r[2][PER];  // piece n in r[n mod 2]
   __device__ __forceinline__ int entry(int q) const {
     const int i = (int)threadIdx.x + q * WAVES * 64;
@@ -676,7 +678,15 @@ struct SharedKey {
   __device__ __forceinline__ void load(c64 (&x)[PER]) {
 #pragma unroll
     for (int q = 0; q < PER; q++) x[q] = gkey_load(src + entry(q));
-    if (--left > 0) src += FFT_PIECE_C64;  // past the end the last piece is loaded again, unused
+    if (!ROUNDS) {
+      if (--left > 0) src += FFT_PIECE_C64;  // past the end the last piece is loaded again, unused
+    } else {
+      src += FFT_PIECE_C64;
+      if (--left == 0) {
+        src -= (size_t)cycle * FFT_PIECE_C64;
+        left = cycle;
+      }
+    }
   }
   __device__ __forceinline__ void store(int slot, const c64 (&x)[PER]) {
 #pragma unroll
@@ -685,7 +695,7 @@ struct SharedKey {
   __device__ __forceinline__ void start(gkey key, c64* lds, int pieces) {
     src = key;
     ring = lds;
-    left = pieces;
+    left = cycle = pieces;
     load(r[0]);
     store(0, r[0]);
     load(r[1]);

@@ -26,29 +26,29 @@ __device__ __forceinline__ void stage_tables(c64* tabs, const c64* __restrict__ 
 }
 
 // One wave per CMUX: out = x0 + C (ext) (x1 - x0), for the `per` CMUXes of one tree level of each of R
-// reads (job = r per + (blk half + m)). SHARED: a workgroup takes eight CMUXes of one read, which use the
-// same selector and stream it together; a wave past the read's last CMUX repeats that one. Otherwise
-// each wave reads its selector by itself. A level of 65,536 CMUXes reads 147 KB of selector for each:
-// through the caches alone that bounds it.
+// reads (job = r per + (blk half + m)). SHARED: a workgroup takes eight CMUXes of one read at a time, which
+// use the same selector and stream it together, `rounds` times in turn; a wave past the read's last CMUX
+// repeats that one. Otherwise each wave reads its selector by itself. A level of 65,536 CMUXes reads 147 KB
+// of selector for each: through the caches alone that bounds it. The rounds keep the selector's
+// stream going from one product to the next and stage the tables once: 64 reads of 256 cells of 8 bits
+// take 1.60 ms, 1.75 with one round per workgroup.
 template <int WAVES, bool SHARED>
 __global__ __launch_bounds__(WAVES * 64) void k_cmux_tree_level(const c64* __restrict__ sel, uint64_t sel_r_stride,
                                                                 int selbit, const u32* __restrict__ in, uint64_t s_r,
                                                                 uint64_t s_b, u32* __restrict__ out, uint64_t R,
-                                                                uint64_t per, uint64_t half,
+                                                                uint64_t per, uint64_t half, uint32_t rounds,
                                                                 const c64* __restrict__ tab) {
   extern __shared__ c64 lds[];
   c64* ring = lds + FFT_TAB_C64;
   stage_tables<WAVES>(lds, tab);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint64_t r, w;
-  bool live = true;
-  SharedKey<WAVES> shared;
+  SharedKey<WAVES, true> shared;
+  GlobalKey key;
   if (SHARED) {
-    const uint64_t bpr = (per + WAVES - 1) / WAVES;
-    r = blockIdx.x / bpr;
-    w = (blockIdx.x - r * bpr) * WAVES + wave;
-    live = w < per;
-    if (!live) w = per - 1;
+    const uint64_t wpr = (per + WAVES * rounds - 1) / (WAVES * rounds);  // workgroups per read
+    r = blockIdx.x / wpr;
+    w = (blockIdx.x - r * wpr) * WAVES * rounds + wave;
     shared.start((gkey)sel + (r * sel_r_stride + (uint64_t)selbit) * TRGSW_FFT_C64, ring, FFT_PIECES);
   } else {
     const uint64_t job = (uint64_t)blockIdx.x * WAVES + wave;
@@ -58,23 +58,24 @@ __global__ __launch_bounds__(WAVES * 64) void k_cmux_tree_level(const c64* __res
   __syncthreads();
   if (!SHARED && r >= R) return;
   const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
-  const uint64_t blk = w / half, m = w - blk * half;
-  const u32* x0 = in + r * s_r + blk * s_b + (2 * m) * TRLWE_WORDS + h * RING_N + l;
-  const u32* x1 = x0 + TRLWE_WORDS;
+  if (!SHARED) key.base = (gkey)sel + (r * sel_r_stride + (uint64_t)selbit) * TRGSW_FFT_C64 + lane;
   double* reg = reinterpret_cast<double*>(ring + (SHARED ? 2 * FFT_PIECE_C64 : 0)) + wave * FFT_WAVE_F64 + h * FFT_REGION;
-  auto word = [&](int t) { return digit_word(x1[32 * t] - x0[32 * t]); };
-  u32 z[32];
-  if constexpr (SHARED) {
-    fft_external_product(word, shared, lds, reg, lane, z);
-  } else {
-    GlobalKey key;
-    key.base = (gkey)sel + (r * sel_r_stride + (uint64_t)selbit) * TRGSW_FFT_C64 + lane;
-    fft_external_product(word, key, lds, reg, lane, z);
-  }
-  if (!live) return;
-  u32* o = out + (r * per + w) * TRLWE_WORDS + h * RING_N + l;
+  for (uint32_t it = 0; it < (SHARED ? rounds : 1u); it++, w += WAVES) {
+    const uint64_t job = w < per ? w : per - 1;
+    const uint64_t blk = job / half, m = job - blk * half;
+    const u32* x0 = in + r * s_r + blk * s_b + (2 * m) * TRLWE_WORDS + h * RING_N + l;
+    const u32* x1 = x0 + TRLWE_WORDS;
+    auto word = [&](int t) { return digit_word(x1[32 * t] - x0[32 * t]); };
+    u32 z[32];
+    if constexpr (SHARED)
+      fft_external_product(word, shared, lds, reg, lane, z);
+    else
+      fft_external_product(word, key, lds, reg, lane, z);
+    if (w >= per) continue;
+    u32* o = out + (r * per + w) * TRLWE_WORDS + h * RING_N + l;
 #pragma unroll
-  for (int t = 0; t < 32; t++) o[32 * t] = x0[32 * t] + z[t];
+    for (int t = 0; t < 32; t++) o[32 * t] = x0[32 * t] + z[t];
+  }
 }
 
 // One wave per read: R <- CMUX(C_j, R, X^{-w 2^j} R) = R + C_j (ext) (X^{-w 2^j} R - R), j
@@ -315,23 +316,40 @@ hipError_t init_memory_kernel_attributes() {
 static bool few_chains(const vsp_context* ctx, uint64_t chains) { return chains <= 2ull * (uint64_t)ctx->cus; }
 static bool wide_launch(const vsp_context* ctx, uint64_t chains) { return chains >= 8ull * (uint64_t)ctx->cus; }
 
+// Rounds per workgroup for a level of R reads of `groups` eights of CMUXes each, one workgroup per compute
+// unit at a time: a workgroup's start costs a fifth of a product (5 us of 26), rounds that do not
+// divide the level leave units idle at its end; the shortest sum of both.
+static uint64_t tree_rounds(uint64_t R, uint64_t groups, uint64_t cus) {
+  uint64_t best = 1, best_cost = ~0ull;
+  for (uint64_t n = 1; n <= groups && n <= 64; n++) {
+    const uint64_t cost = (R * ((groups + n - 1) / n) + cus - 1) / cus * (5 * n + 1);
+    if (cost < best_cost) {
+      best = n;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 hipError_t launch_cmux_tree_level(const vsp_context* ctx, const c64* sel, uint64_t sel_r_stride, int selbit,
                                   const uint32_t* in, uint64_t s_r, uint64_t s_b, uint32_t* out, uint64_t R,
                                   uint64_t nb, uint64_t W, hipStream_t st) {
   const uint64_t per = nb * (W / 2);
   if (R * per == 0) return hipSuccess;
   // eight CMUXes of a read share its selector while that leaves enough workgroups
-  if (per >= 8 && wide_launch(ctx, R * per))
-    hipLaunchKernelGGL((k_cmux_tree_level<8, true>), dim3((unsigned)(R * ((per + 7) / 8))), dim3(512),
+  if (per >= 8 && wide_launch(ctx, R * per)) {
+    const uint64_t rounds = tree_rounds(R, (per + 7) / 8, (uint64_t)ctx->cus);
+    hipLaunchKernelGGL((k_cmux_tree_level<8, true>), dim3((unsigned)(R * ((per + 8 * rounds - 1) / (8 * rounds)))), dim3(512),
                        mem_lds_bytes(8, true, false), st, sel, sel_r_stride, selbit, in, s_r, s_b, out, R, per, W / 2,
-                       ctx->ftab);
-  else if (few_chains(ctx, R * per))
+                       (uint32_t)rounds, ctx->ftab);
+  } else if (few_chains(ctx, R * per)) {
     hipLaunchKernelGGL(k_cmux_tree_wide, dim3((unsigned)(R * per)), dim3(BRW_WAVES * 64), brw_lds_bytes(1), st, sel,
                        sel_r_stride, selbit, in, s_r, s_b, out, per, W / 2, ctx->ftab + FFT_TAB_C64);
-  else
+  } else {
     hipLaunchKernelGGL((k_cmux_tree_level<1, false>), dim3(blocks_for(R * per, 1)), dim3(64),
-                       mem_lds_bytes(1, false, false), st, sel, sel_r_stride, selbit, in, s_r, s_b, out, R, per, W / 2,
+                       mem_lds_bytes(1, false, false), st, sel, sel_r_stride, selbit, in, s_r, s_b, out, R, per, W / 2, 1u,
                        ctx->ftab);
+  }
   return hipGetLastError();
 }
 
