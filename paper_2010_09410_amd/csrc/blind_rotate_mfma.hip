@@ -1,6 +1,6 @@
 // Blind rotation on the matrix cores: every external product of a step is an exact integer
 // matrix product over the whole batch, computed with int8 MFMA (Sec. 2.1.2, TRGSW and CMUX;
-// the same accumulator recurrence as the NTT kernels, with the polynomial products done
+// the same accumulator recurrence as the transform kernels, with the polynomial products done
 // without a transform).
 //
 // For one TRGSW row r (gadget level k of ACC polynomial h, r = 3h + k) and output polynomial

@@ -110,10 +110,6 @@ __device__ constexpr FftPass1 kP1 = make_fft_pass1();
 struct FftConst {  // pass 1: known at compile time
   __device__ __forceinline__ c64 operator()(int e) const { return make_double2(kP1.c[e], kP1.s[e]); }
 };
-struct FftLane {  // pass 2: the lane's table
-  const c64* tab;
-  __device__ __forceinline__ c64 operator()(int e) const { return tab[e * 32]; }
-};
 
 // (xr, xi), (yr, yi) -> x + w y, x - w y.
 __device__ __forceinline__ void fft_split(double& xr, double& xi, double& yr, double& yi, double wr, double wi) {
@@ -172,8 +168,8 @@ __device__ __forceinline__ void fft_pass_inverse(double (&re)[M], double (&im)[M
   }
 }
 
-// The two with the constants of a lane in LDS: those of the next splitting are read while one is
-// computed. first: the one of the first splitting (of the last four, for the inverse: read before).
+// Pass 2 and its inverse: four splittings (joinings) with the lane's constants in LDS, those of the
+// next one read while one is computed. w0: the first splitting's, read before.
 template <int S>
 __device__ __forceinline__ void fft_lane_constants(c64 (&w)[(1 << S) > 1 ? (1 << S) >> 1 : 1], const c64* tab) {
   constexpr int n = (1 << S) > 1 ? (1 << S) >> 1 : 1;

@@ -374,7 +374,7 @@ static vsp_status check_gate_args(vsp_context* ctx, const uint8_t* d_ops, const 
 
 // Enqueues prologue -> blind rotation -> key switch (or the TRLWE output) for B gates in
 // chunks of `chunk`, with the modulus-switched inputs in abar (chunk rows), the extracted rows
-// in t1 (chunk rows) and the matrix-core workspace mfw (NULL: the NTT forms).
+// in t1 (chunk rows) and the matrix-core workspace mfw (NULL: the transform forms).
 static vsp_status gates_enqueue(vsp_context* ctx, const uint8_t* d_ops, const uint32_t* d_in0, const uint32_t* d_in1,
                                 uint32_t* d_out, uint64_t B, uint64_t chunk, bool trlwe_out, uint32_t* abar,
                                 uint32_t* t1, void* mfw, hipStream_t st, bool prof) {
@@ -459,7 +459,7 @@ vsp_status vsp_gates_noalloc(vsp_context* ctx, const uint8_t* d_ops, const uint3
   uint8_t* base = static_cast<uint8_t*>(static_scratch(ctx->device));
   if (base == nullptr) return fail(VSP_E_STATE, "the static scratch of this device was not resolved");
   const uint64_t chunk = (mode == VSP_BATCHED) ? B : 1;
-  // no matrix-core workspace: the NTT forms of the blind rotation (the key switch needs none)
+  // no matrix-core workspace: the transform forms of the blind rotation (the key switch needs none)
   return gates_enqueue(ctx, d_ops, d_in0, d_in1, d_out, B, chunk, false, reinterpret_cast<uint32_t*>(base),
                        reinterpret_cast<uint32_t*>(base + kStaticAbarBytes), nullptr,
                        static_cast<hipStream_t>(stream), false);

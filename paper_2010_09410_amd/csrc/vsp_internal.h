@@ -104,15 +104,15 @@ struct Tuning {
     while (b + 1 < kTuneBuckets && B > kBucket[b]) b++;
     return b;
   }
-  // with ntt_only, the best of the NTT forms (for launches that cannot take the matrix-core
+  // with transform_only, the best of the transform forms (for launches that cannot take the matrix-core
   // forms: another key, or no workspace)
-  int br_waves(uint64_t B, bool ntt_only = false) const {
+  int br_waves(uint64_t B, bool transform_only = false) const {
     const int f = br_force[bucket(B)];
-    if (f && !(ntt_only && br_matrix_form(f))) return f;
+    if (f && !(transform_only && br_matrix_form(f))) return f;
     int best = 1;
     double best_ms = 0;
     for (int s : {1, 0, 2, 3, 4}) {
-      if (ntt_only && s >= 3) continue;
+      if (transform_only && s >= 3) continue;
       const uint64_t cap = br_cap[s] ? br_cap[s] : 1;
       double ms = (double)((B + cap - 1) / cap) * br_round_ms[s];
       // above 1,280 gates the split form's time deviates from the interpolation by a few
@@ -258,7 +258,7 @@ hipError_t launch_mux_combine(uint32_t* t, uint64_t B, hipStream_t st);
 // bkf: the bootstrapping key to use (NULL: the context's); with keytab non-NULL gate g uses
 // keytab[kid[g]] instead (device arrays). The matrix-core forms (waves 32 and 33) need the
 // context's own key and a workspace of mf_work_bytes(B, trlwe == NULL) bytes in mf_work;
-// without them the best NTT form for B runs instead.
+// without them the best transform form for B runs instead.
 // tile_mfkeys (device, one pointer per tile of MF_TILE gates, NULL for none): the byte-plane
 // key of each tile's key set, for batches whose key-set ranges start on tile boundaries; with
 // it the matrix-core forms also run batches of other key sets.
