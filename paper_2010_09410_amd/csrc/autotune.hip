@@ -51,7 +51,9 @@ std::string device_key(int dev) {
 
 // Cache file: {"<device>": {"br_waves": [4, 8, ..], "br_cap": [..], "br_round_ms": [..],
 //                          "buckets": [..], "ks_form": [..], "split_at": [..],
-//                          "split_ms": [..], "split_groups": [..]}}
+//                          "split_ms": [..], "split_groups": [..], "kernels": [kTunedKernels]}}
+// An entry measured with other kernels is measured again: its times would pick the wrong forms.
+constexpr int kTunedKernels = 2;  // 2: float64 transform, one-hot key switch
 bool read_numbers(const std::string& s, size_t from, const char* name, double* out, int count) {
   const size_t p = s.find(std::string("\"") + name + "\"", from);
   if (p == std::string::npos) return false;
@@ -78,11 +80,12 @@ bool read_cache(const std::string& path, const std::string& key, Tuning& t) {
   const size_t at = s.find("\"" + key + "\"");
   if (at == std::string::npos) return false;
   double shapes[kBrShapes], cap[kBrShapes], ms[kBrShapes], ks[kTuneBuckets], buckets[kTuneBuckets];
-  double sms[kSplitPts], sg[kSplitPts], spts[kSplitPts];
+  double sms[kSplitPts], sg[kSplitPts], spts[kSplitPts], kernels;
   if (!read_numbers(s, at, "br_waves", shapes, kBrShapes) || !read_numbers(s, at, "br_cap", cap, kBrShapes) ||
       !read_numbers(s, at, "br_round_ms", ms, kBrShapes) || !read_numbers(s, at, "buckets", buckets, kTuneBuckets) ||
       !read_numbers(s, at, "ks_form", ks, kTuneBuckets) || !read_numbers(s, at, "split_at", spts, kSplitPts) ||
-      !read_numbers(s, at, "split_ms", sms, kSplitPts) || !read_numbers(s, at, "split_groups", sg, kSplitPts))
+      !read_numbers(s, at, "split_ms", sms, kSplitPts) || !read_numbers(s, at, "split_groups", sg, kSplitPts) ||
+      !read_numbers(s, at, "kernels", &kernels, 1) || kernels != kTunedKernels)
     return false;
   for (int i = 0; i < kBrShapes; i++)
     if (shapes[i] != kBrWaveChoices[i]) return false;  // written for another list of forms
@@ -135,7 +138,7 @@ bool write_cache(const std::string& path, const std::string& key, const Tuning& 
   list([&](int i) { return t.split_ms[i]; }, kSplitPts);
   f << ", \"split_groups\": ";
   list([&](int i) { return t.split_groups[i]; }, kSplitPts);
-  f << "}}\n";
+  f << ", \"kernels\": [" << kTunedKernels << "]}}\n";
   return (bool)f;
 }
 

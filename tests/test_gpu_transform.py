@@ -201,3 +201,23 @@ def test_pairs_of_gates_equal_single_ones(gpu, B):
         gpu.set_tuning(B, 0, ks)
     for o in outs[1:]:
         np.testing.assert_array_equal(o, outs[0])
+
+
+def test_a_tuning_measured_with_other_kernels_is_measured_again(gpu, tmp_path):
+    """A cache entry without the mark of these kernels, or with another one, is ignored and rewritten."""
+    import json
+    buckets = (1, 16, 64, 256, 1024, 2048, 4096)
+    saved = {b: gpu.tuning(b)[1] for b in buckets}
+    path = tmp_path / "tune.json"
+    try:
+        gpu.autotune(max_batch=64, cache_path=str(path))
+        (key, entry), = json.loads(path.read_text()).items()
+        mark = entry.pop("kernels")
+        for other in ({}, {"kernels": [mark[0] - 1]}):
+            path.write_text(json.dumps({key: {**entry, **other, "br_round_ms": [99.0] * 5}}))
+            gpu.autotune(max_batch=64, cache_path=str(path))
+            again = json.loads(path.read_text())[key]
+            assert again["kernels"] == mark and again["br_round_ms"] != [99.0] * 5
+    finally:
+        for b, t in saved.items():
+            gpu.set_tuning(b, 0, t)
