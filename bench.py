@@ -11,8 +11,8 @@ Prints one JSON line (rank 0). Extra fields: the per-gate rate (one launch seque
 gate), the batched / per-gate ratio, per-level p50/p99 latency of the 64-level circuit, a
 serving run (Poisson arrivals of layered circuits from 64 clients: throughput and p50/p99
 circuit latency), the roofline of the dominant kernel (the matrix-core step kernel against the
-int8 MFMA peak, or the NTT blind-rotation kernel against the integer-ALU peak, whichever form
-the autotuner picks for the batch) with the HBM side, and the CPU oracle baseline.
+int8 MFMA peak, or the transform blind-rotation kernel against the float64 vector peak, whichever
+form the autotuner picks for the batch) with the HBM side, and the CPU oracle baseline.
 """
 from __future__ import annotations
 
@@ -33,48 +33,21 @@ B_GATES = 4096
 N_LWE, N_RING, GL, STEPS_BR = 630, 1024, 3, 630
 
 # ---------------------------------------------------------------- work model
-# 32-bit VALU lane-operations of one blind-rotation step: the modular operations of the
-# algorithm (per lane of a wave; lanes 0-31 and 32-63 each carry one polynomial) priced at
-# the instruction counts of the compiled gfx950 routines they use. Butterflies multiply
-# their second input by 2^E (canonical result) and then add and subtract with one carry fix:
-# 17.5 instructions for E mod 96 below 32, 25 in [32, 64), 20 in [64, 96), 14 for E = 0,
-# 8 for the first stage on small digits. A general product mod p is 22, a canonical 2^E
-# product 9 / 15 / 10 by the same classes, an add mod p 7, a gadget digit with its rotation
-# 8, an exact lift 4; the key MAC adds two products with one reduction (40) and the two
-# half-wave swaps (2) to the accumulator (7).
-C_MUL, C_ADD, C_DIGIT, C_LIFT, C_DOT2, C_SWAP = 22, 7, 8, 4, 40, 2
-BF_LO, BF_MID, BF_HI, BF_TRIV, BF_SMALL = 17.5, 25, 20, 14, 8
-P2_LO, P2_MID, P2_HI = 9, 15, 10
-
-
-def _exp_class(E: int) -> int:
-    e = E % 96
-    return 3 if e == 0 else (0 if e < 32 else (1 if e < 64 else 2))
-
-
-def _brv5(k: int) -> int:
-    return int(f"{k:05b}"[::-1], 2)
-
-
+# Float64 lane-operations of one blind-rotation step by the complex transform, one fused
+# multiply-add (or addition or product) each, per lane of a wave whose halves carry one polynomial
+# each, 16 complex points a lane: nine splittings of 8 pairs at 6 per forward transform, nine
+# joinings at 8 for the inverse, one more inverse of a single polynomial on all 64 lanes (4 pairs a
+# lane), the products with the key (8 slot pairs, 2 rows, 3 products, 4 each) and the rounding of the
+# 48 results a lane.
 def br_step_lane_ops() -> int:
-    cost = {0: BF_LO, 1: BF_MID, 2: BF_HI, 3: BF_TRIV}
-    # pass 1 (negacyclic, twiddle 2^(3 brv5(m)) at stage s for blocks m in [2^s, 2^(s+1)))
-    pass1 = 16 * BF_SMALL + sum((16 >> s) * cost[_exp_class(3 * _brv5(m))]
-                                for s in range(1, 5) for m in range(1 << s, 2 << s))
-    # cyclic DFT32 with w = 2^6 (decimation in time: span H uses w^(j 16 / H))
-    dft = sum(cost[_exp_class(6 * j * (16 // H))] * (32 // (2 * H)) for H in (1, 2, 4, 8, 16) for j in range(H))
-    table = 31 * C_MUL
-    twist = sum({0: P2_LO, 1: P2_MID, 2: P2_HI}[_exp_class(96 - 3 * t)] for t in range(1, 32))
-    forward = pass1 + table + dft
-    inverse = dft + table + dft + twist + 32 * C_LIFT
-    mac = GL * 32 * (C_DOT2 + C_SWAP + C_ADD)    # per lane: 32 slots, 3 rounds
-    digits = GL * 32 * C_DIGIT
-    return int(round(64 * (GL * forward + inverse + mac + digits)))
+    forward, inverse, packed_inverse = 9 * 8 * 6, 9 * 8 * 8, 9 * 4 * 8
+    mac = 8 * 2 * 3 * 4
+    return 64 * (GL * (forward + mac) + inverse + packed_inverse + 48)
 
 
 LANE_OPS_PER_GATE = STEPS_BR * br_step_lane_ops()
-PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9            # CUs x SIMDs x lanes/clk x clock: 39.3 T/s
-BK_NTT_BYTES = N_LWE * 2 * GL * 2 * N_RING * 8  # key stream read by every gate (61.93 MB)
+PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9            # CUs x SIMDs x lanes/clk x clock: 39.3 T/s (float64 at full rate)
+BK_FFT_BYTES = N_LWE * GL * 8 * 2 * 3 * 64 * 16  # key stream read by every gate (92.90 MB)
 HBM_PEAK = 8.0e12                               # bytes/s
 
 
@@ -115,7 +88,7 @@ def cpu_model() -> str:
 def br_hbm_bytes(B: int) -> int:
     """Algorithmic HBM bytes of one blind-rotation launch over B gates: the key once, the
     opcodes and modulus-switched inputs read, the extracted TLWE rows written."""
-    return BK_NTT_BYTES + B * (1 + (N_LWE + 1) * 4 + (N_RING + 1) * 4)
+    return BK_FFT_BYTES + B * (1 + (N_LWE + 1) * 4 + (N_RING + 1) * 4)
 
 
 # ---------------------------------------------------------------- matrix-core form
@@ -153,7 +126,7 @@ def src_fingerprint(files) -> str:
 
 
 def br_fingerprint() -> str:
-    return src_fingerprint(("gl64.h", "ntt.h", "blind_rotate.h"))
+    return src_fingerprint(("fft.h", "blind_rotate.h"))
 
 
 def mf_fingerprint() -> str:
@@ -192,10 +165,10 @@ def parse():
     ap.add_argument("--serving-light", type=float, default=0.7, metavar="FRACTION",
                     help="also serve about 30 circuits offered at this fraction of the measured batched "
                          "throughput (0 skips it)")
-    ap.add_argument("--no-ntt-form", action="store_true",
-                    help="skip timing the 4096-gate batch in the NTT form when the tuning picks the matrix form")
+    ap.add_argument("--no-transform-form", "--no-ntt-form", dest="no_transform_form", action="store_true",
+                    help="skip timing the 4096-gate batch in the transform form when the tuning picks the matrix form")
     ap.add_argument("--no-key-reuse", action="store_true",
-                    help="skip the 4096-gate NTT-form batch without key reuse (one key copy per resident gate)")
+                    help="skip the 4096-gate transform-form batch without key reuse (one key copy per resident gate)")
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="MIB",
                     help="also run one plain device copy of MIB MiB (reference for HBM byte counters)")
     return ap.parse_args()
@@ -477,10 +450,9 @@ def main():
     # register-resident throughput of a product and of a sum mod p on the whole chip
     ceiling = nv.vsp_measure_modp(0, 4096)
 
-    # the same batch in the NTT form (the transform-domain method), when the tuning picked the
-    # matrix-core form for it
-    ntt_form = None
-    if br_waves == 32 and not args.no_ntt_form:
+    # the same batch in the transform form, when the tuning picked the matrix-core form for it
+    transform_form = None
+    if br_waves == 32 and not args.no_transform_form:
         ctx.set_tuning(B_GATES, 8, ks_form)
         ctx.gates(ops_d, a_d, b_d, out=out)
         ctx.sync()
@@ -500,10 +472,10 @@ def main():
         navg = nbr_ms / max(nbr_n, 1)
         nach = B_GATES * LANE_OPS_PER_GATE / (navg * 1e-3)
         ntraffic, nsrc = measured_traffic(br_fingerprint())
-        ntt_form = {"kernel": "k_blind_rotate<8>", "value": round(nrate, 1), "unit": "gate bootstraps/s",
+        transform_form = {"kernel": "k_blind_rotate<8>", "value": round(nrate, 1), "unit": "gate bootstraps/s",
                     "ms_per_step": round(ndt * 1e3 / reps, 3), "blind_rotation_avg_ms": round(navg, 3),
                     "alu": {"achieved": round(nach / 1e12, 3), "peak": round(PEAK_LANE_OPS / 1e12, 3),
-                            "unit": "T int32 lane-ops/s (compiled-routine instruction model)",
+                            "unit": "T float64 lane-ops/s",
                             "frac": round(nach / PEAK_LANE_OPS, 4)},
                     "algorithmic": algorithmic(B_GATES / (navg * 1e-3), ceiling),
                     "hbm": {"algorithmic_bytes_per_launch": br_hbm_bytes(B_GATES),
@@ -511,18 +483,18 @@ def main():
                             "measured_bytes_per_launch": ntraffic, "traffic_source": nsrc,
                             "measured_GBps": None if ntraffic is None else round(ntraffic / (navg * 1e-3) / 1e9, 1)}}
 
-    # What key reuse contributes: the same batch in the eight-wave NTT form with one shared key,
+    # What key reuse contributes: the same batch in the eight-wave transform form with one shared key,
     # then with gate g reading its own device copy g mod C, C = the gates the form holds at once
     # (eight per CU), so that no resident gate shares key bytes with another; and one gate alone
-    # in the three-wave latency form (occupancy: one workgroup on the chip).
+    # in the latency form (occupancy: one workgroup on the chip).
     key_reuse = None
     if not args.no_key_reuse:
         resident = 8 * torch.cuda.get_device_properties(ctx.device).multi_processor_count
-        kr = {"form": "k_blind_rotate<8>", "gates": B_GATES, "key_bytes_per_gate": BK_NTT_BYTES}
+        kr = {"form": "k_blind_rotate<8>", "gates": B_GATES, "key_bytes_per_gate": BK_FFT_BYTES}
         for name, copies in (("shared", 1), ("unshared", resident)):
             ctx.gates_key_copies(ops_d[:16], a_d[:16], b_d[:16], waves=8, copies=1)
             _, ms = ctx.gates_key_copies(ops_d, a_d, b_d, waves=8, copies=copies, out=out)
-            kb = B_GATES * BK_NTT_BYTES if copies > 1 else BK_NTT_BYTES
+            kb = B_GATES * BK_FFT_BYTES if copies > 1 else BK_FFT_BYTES
             kr[name] = {"copies": copies, "blind_rotation_ms": round(ms, 3),
                         "gates_per_s": round(B_GATES / (ms * 1e-3), 1),
                         "key_bytes_requested": kb, "key_GBps": round(kb / (ms * 1e-3) / 1e9, 1),
@@ -530,7 +502,7 @@ def main():
         _, one = ctx.gates_key_copies(ops_d[:1], a_d[:1], b_d[:1], waves=3, copies=1)
         kr["one_gate"] = {"form": "k_blind_rotate_wide", "blind_rotation_ms": round(one, 3),
                           "gates_per_s": round(1e3 / one, 2),
-                          "key_GBps": round(BK_NTT_BYTES / (one * 1e-3) / 1e9, 2)}
+                          "key_GBps": round(BK_FFT_BYTES / (one * 1e-3) / 1e9, 2)}
         kr["occupancy_gain"] = round(kr["unshared"]["gates_per_s"] / kr["one_gate"]["gates_per_s"], 1)
         kr["reuse_gain"] = round(kr["shared"]["gates_per_s"] / kr["unshared"]["gates_per_s"], 3)
         key_reuse = kr
@@ -623,9 +595,9 @@ def main():
     per_gate_key = None
     if per_gate is not None:
         # each gate of the per-gate path streams the whole key of its form once: the byte-plane
-        # key in the matrix-core forms, the NTT-domain key otherwise
+        # key in the matrix-core forms, the transformed key otherwise
         pg_form = ctx.tuning(1)[0]
-        pg_bytes = N_LWE * MF_KEY_STEP_BYTES if pg_form in (32, 33) else BK_NTT_BYTES
+        pg_bytes = N_LWE * MF_KEY_STEP_BYTES if pg_form in (32, 33) else BK_FFT_BYTES
         per_gate_key = {"GBps": round(per_gate * pg_bytes / 1e9, 2),
                         "frac_of_hbm": round(per_gate * pg_bytes / HBM_PEAK, 6), "gates_timed": pg,
                         "form": pg_form, "key_bytes_per_gate": pg_bytes}
@@ -657,13 +629,13 @@ def main():
         hbm = br_hbm_bytes(B_GATES) / (br_avg_ms * 1e-3)
         roof = {"bound": "alu", "kernel": f"k_blind_rotate<{br_waves}>", "achieved": round(achieved, 3),
                 "algorithmic": algorithmic(B_GATES / (br_avg_ms * 1e-3), ceiling),
-                "peak": round(PEAK_LANE_OPS / 1e12, 3), "unit": "T int32 lane-ops/s",
+                "peak": round(PEAK_LANE_OPS / 1e12, 3), "unit": "T float64 lane-ops/s",
                 "frac": round(achieved * 1e12 / PEAK_LANE_OPS, 4), "traffic": traffic, "traffic_source": traffic_src,
                 "avg_launch_ms": round(br_avg_ms, 3), "lane_ops_per_gate": LANE_OPS_PER_GATE,
                 "hbm": {"achieved": round(hbm / 1e9, 1), "peak": HBM_PEAK / 1e9, "unit": "GB/s",
                         "frac": round(hbm / HBM_PEAK, 4), "algorithmic_bytes_per_launch": br_hbm_bytes(B_GATES),
                         "measured_GBps": None if traffic is None else round(traffic / (br_avg_ms * 1e-3) / 1e9, 1)},
-                "key_stream_GBps_requested": round(B_GATES * BK_NTT_BYTES / (br_avg_ms * 1e-3) / 1e9, 1),
+                "key_stream_GBps_requested": round(B_GATES * BK_FFT_BYTES / (br_avg_ms * 1e-3) / 1e9, 1),
                 "keyswitch_avg_ms": round(ks_ms / max(ks_n, 1), 3), "launch": launch}
     cpu = None
     if not args.no_cpu:
@@ -676,13 +648,13 @@ def main():
         "warmup": args.warmup, "ms_per_step": round(ms_per_step, 3), "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": "u32", "data": "synthetic",
         "dtype_note": "exact torus arithmetic mod 2^32; " + ("int8 byte-plane MFMA operands with int32 "
-                      "accumulation" if br_waves == 32 else "NTT mod 2^64 - 2^32 + 1 in u64"),
+                      "accumulation" if br_waves == 32 else "exact integer products by a complex float64 transform with proven rounding"),
         "config": {"workload": "4096 independent random gates (NAND/AND/OR/XOR/XNOR) on fresh TLWE, "
                                "n=630 N=1024 l=3 Bg=64 ks t=8 base=4, one batched launch",
                    "batch": B_GATES, "parallelism": "single GPU"},
         "per_gate_value": None if per_gate is None else round(per_gate, 2),
         "batched_over_per_gate": None if per_gate is None else round(value / per_gate, 1),
-        "per_gate_key_stream": per_gate_key, "ntt_form_4096": ntt_form, "key_reuse": key_reuse,
+        "per_gate_key_stream": per_gate_key, "transform_form_4096": transform_form, "key_reuse": key_reuse,
         "mux_per_s": None if mux_rate is None else round(mux_rate, 1),
         "per_level": levels, "clocked_netlist": machine, "cmux_memory": memory, "circuit_bootstrapping": cbs, "serving": serving, "roofline": roof, "cpu_baseline": cpu,
     }
