@@ -88,9 +88,9 @@ const char* vsp_last_error(void);
 /* Create a context on HIP device `device`: validates params, uploads the bootstrapping key
  * bk_host [n][2l][2][N] (BK[i] = TRGSW_{s1}(s0[i]), Sec. 2.1.2 "Bootstrapping Key") and the
  * key-switching key ksk_host [N][t][base-1][n+1] (entry [j][p][v-1] = TLWE_{s0}(v s1[j] /
- * base^(p+1))), converts the bootstrapping key to the NTT domain and to the byte-plane forms
- * of the matrix-core blind rotation and key switch on the device (about 330 MB of device
- * memory in all: 62 MB NTT-domain, 98 MB byte-plane and 84 MB key-switch byte-plane forms, and
+ * base^(p+1))), converts the bootstrapping key to the transform domain and to the byte-plane
+ * forms of the matrix-core blind rotation and key switch on the device (about 360 MB of device
+ * memory in all: 93 MB transformed, 98 MB byte-plane and 84 MB key-switch byte-plane forms, and
  * the 83 MB key-switching key), and returns it in *out. Host arrays are copied; the caller keeps them.
  * Synchronous. */
 vsp_status vsp_context_create(const vsp_params* params, const uint32_t* bk_host, const uint32_t* ksk_host,
@@ -117,7 +117,7 @@ vsp_status vsp_gates(vsp_context* ctx, const uint8_t* d_ops, const uint32_t* d_i
  * results and errors as vsp_gates, bit for bit, with B <= 2048 (larger B: VSP_E_ARG, nothing
  * enqueued). The intermediate ciphertexts live in one fixed 13.6 MB device array per GPU
  * (2048 modulus-switched inputs and 2048 extracted TLWE rows), held until the process ends;
- * the blind rotation runs in its NTT forms (the matrix-core form needs a larger workspace).
+ * the blind rotation runs in its transform forms (the matrix-core forms need a larger workspace).
  * Every call on one GPU shares that array, so calls that overlap on a GPU (other streams,
  * other contexts or threads) race and must be ordered by the caller. */
 vsp_status vsp_gates_noalloc(vsp_context* ctx, const uint8_t* d_ops, const uint32_t* d_in0, const uint32_t* d_in1,
@@ -128,13 +128,15 @@ vsp_status vsp_gates_noalloc(vsp_context* ctx, const uint8_t* d_ops, const uint3
  * each gate to a worker as a task of its own (Sec. 6.2(d), list scheduling), so every gate's
  * bootstrap makes its own pass over the key; a batch here shares one pass among all its gates
  * (Sec. 2.3: gates of one level are independent). Same results as vsp_gates in batched mode, bit for bit, with
- * the blind rotation in the NTT form `waves` (3, 4 or 8) and gate g reading device copy
+ * the blind rotation in the transform form `waves` (3, 4 or 8) and gate g reading device copy
  * g mod `copies` of the converted key: once `copies` reaches the number of gates the form
  * holds at once, no two resident gates read the same key bytes and nothing of the key is
  * reused through the caches; copies = 1 is the ordinary shared key. 1 <= copies <= 65536,
  * B <= 2^22; *br_ms receives the blind rotation's time (HIP events on `stream`). Allocates
- * copies x 61.9 MB (copies > 1) for the duration of the call (VSP_E_NOMEM when the device
- * lacks it, nothing enqueued) and returns only after the stream has drained. */
+ * 92.9 MB per copy (copies > 1) for the duration of the call, for at most eight copies per compute
+ * unit: more gates than that are never held at once, and copies asked for beyond them are the
+ * same ones again. VSP_E_NOMEM, nothing enqueued, when the device lacks that or 61.9 MB for every
+ * copy asked for. Returns only after the stream has drained. */
 vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const uint32_t* d_in0, const uint32_t* d_in1,
                                 uint32_t* d_out, uint64_t B, int waves, uint32_t copies, void* stream,
                                 double* br_ms);
@@ -245,7 +247,7 @@ vsp_status vsp_server_poll(vsp_server* s, uint64_t ticket, uint32_t* h_wires, in
 
 /* A further client's key set on the context's GPU (the protocol gives every client its own
  * keys, Sec. 4.1): bk_host [n][2l][2][N] and ksk_host [N][t][base-1][n+1] as for
- * vsp_context_create, converted and copied to the device in the same forms (about 330 MB); the
+ * vsp_context_create, converted and copied to the device in the same forms (about 360 MB); the
  * caller keeps its arrays. Synchronous. A key set must outlive every request submitted with it. */
 vsp_status vsp_keyset_create(vsp_context* ctx, const uint32_t* bk_host, const uint32_t* ksk_host, vsp_keyset** out);
 vsp_status vsp_keyset_destroy(vsp_keyset* k);
@@ -273,10 +275,11 @@ vsp_status vsp_mux(vsp_context* ctx, const uint32_t* d_sel, const uint32_t* d_in
                    uint32_t* d_out, uint64_t B, void* stream);
 
 /* Autotuner for the batched launches (the level executor's tile and batch shapes). A gate's
- * blind rotation runs on one wave (or, in the latency shape, on three waves that split each
- * external product by gadget level), so a batch of B gates runs in ceil(B / cap) rounds, cap
- * being the gates the GPU holds at once for a workgroup shape (4 or 8 gates per workgroup, or
- * one gate per three-wave workgroup). The matrix-core form (32) instead runs each step as int8
+ * blind rotation runs on one wave (8: eight gates per workgroup, which stream the key together) or
+ * on a workgroup of eight waves (3: one gate per workgroup; 4: two gates that share each key load,
+ * and one per workgroup in a last round that leaves a compute unit to each; 3 runs whole rounds
+ * of two per compute unit like 4), so a batch of B gates runs in ceil(B / cap) rounds, cap being the
+ * gates the GPU holds at once for a shape. The matrix-core form (32) instead runs each step as int8
  * MFMA products of the batch's digit rows with the key's Toeplitz blocks (tiles of 32 gates;
  * one round holds 16 gates per compute unit; used by vsp_gates and vsp_bootstrap_trlwe with the
  * context's own key, the other callers run the 8-gate form in its place; it needs a workspace
@@ -285,20 +288,21 @@ vsp_status vsp_mux(vsp_context* ctx, const uint32_t* d_sel, const uint32_t* d_in
  * key rows; 1: tiles of 16 gates reading each key row once and selecting in registers;
  * 2: tiles of 16 gates staging key rows through LDS, with the j range split over workgroups
  * and atomic accumulation; 3: int8 MFMA products of one-hot digit rows with the key's byte
- * planes, for the context's own key, other keys running form 2) for each batch-size bucket up
+ * planes, for key sets that hold them, other keys running form 2) for each batch-size bucket up
  * to max_batch (buckets end at 1, 16,
  * 64, 256, 1024, 2048, 4096 gates; larger batches share the last). Every candidate must give
  * bit-identical outputs (else VSP_E_HIP). Later launches pick the shape with the fewest
  * rounds x round time, and the faster key switch for their bucket. With cache_path non-NULL
- * the measurements are read from that JSON file when it holds an entry for this GPU, and
- * otherwise measured and written there. Synchronous; allocates and frees its own buffers. */
+ * the measurements are read from that JSON file when it holds an entry for this GPU and these
+ * kernels, and otherwise measured and written there. Synchronous; allocates and frees its own buffers. */
 vsp_status vsp_autotune(vsp_context* ctx, uint64_t max_batch, const char* cache_path);
 
-/* The launch choice for a batch of B gates: *br_waves (4 or 8 gates per workgroup at one wave
- * per gate, 3 for one gate per workgroup on three waves, 32 for the matrix-core form),
+/* The launch choice for a batch of B gates: *br_waves (8 for eight gates per workgroup at
+ * one wave per gate, 3 and 4 for one and two gates per workgroup of eight waves, 32 and 33 for the
+ * matrix-core forms),
  * *ks_form (0, 1, 2 or 3). Before vsp_autotune (or after it returned a bucket to the model),
  * the blind-rotation shape comes from the round-time model with default round times, and the
- * key switch is form 2 up to 256 gates and form 3 above. */
+ * key switch is form 3. */
 vsp_status vsp_tuning_get(const vsp_context* ctx, uint64_t B, int* br_waves, int* ks_form);
 
 /* Pin the launch choice for the bucket containing B: br_waves 3, 4, 8 or 32 (0 returns that
@@ -333,8 +337,8 @@ vsp_status vsp_profile_enable(vsp_context* ctx, int on);
 vsp_status vsp_profile_read(vsp_context* ctx, int which, double* total_ms, uint64_t* launches);
 
 /* Measurement entry: the device's throughput of the arithmetic modulo the NTT prime
- * p = 2^64 - 2^32 + 1 that the transform-domain blind rotation is built from (the polynomial
- * products of the external product, Sec. 2.1.2, computed by NTT over the prime of Sec. 6.2(a)):
+ * p = 2^64 - 2^32 + 1 of Sec. 6.2(a), which prices the method's polynomial products (the external
+ * product's, Sec. 2.1.2) computed by NTT over it:
  * general products and lazy sums mod p, each in independent register-resident chains at full
  * occupancy with `iters` operations per chain (16 <= iters <= 2^24), timed with HIP events.
  * Writes operations per second to *mulmod_per_s and *addmod_per_s. Allocates and frees its
@@ -363,17 +367,16 @@ vsp_status vsp_debug_polymul(vsp_context* ctx, const int32_t* d_a, const uint32_
  * torus words; BK2[i] = TRGSW2_{s2}(s0[i]), rows as the level-1 TRGSW) and the two private
  * key-switching keys pksk_host [2][N2+1][t2][3][2][N] (uint32; entry [u][k][p][v-1] is a
  * level-1 TRLWE of f_u(v z_k / 4^(p+1)) with z = (-s2[0..N2-1], 1), f_0(x) = -s1 x and
- * f_1(x) = x), converts the first to its transformed layout on the device (about 645 MB; the
- * second takes 1.2 GB) and returns the key in *out. Host arrays are copied. Synchronous.
+ * f_1(x) = x), converts the first to its transformed layout (about 495 MB) and the second to the
+ * operand order of the matrix cores (1.6 GB) on the device and returns the key in *out. Host arrays are copied. Synchronous.
  * Destroy it before its context. */
 vsp_status vsp_cbkey_create(vsp_context* ctx, const uint64_t* bk2_host, const uint32_t* pksk_host, vsp_cbkey** out);
 vsp_status vsp_cbkey_destroy(vsp_cbkey* key);
 
 /* The level-2 blind rotation's form for later vsp_circuit_bootstrap calls with this key: 0 (the
- * default) picks by batch size, 1 forces one workgroup of four waves per (conversion, gadget
- * level) job, two per compute unit (throughput), 2 forces eight waves per job, one per compute
- * unit, with a step's eight digit rows transformed at once (latency). Results are the same
- * for every form; form outside [0, 2] is VSP_E_ARG. */
+ * default), 1 or 2. One form serves every batch size now, a workgroup of eight waves per
+ * (conversion, gadget level) job with a step's eight digit rows transformed at once, so the choice
+ * has no effect; form outside [0, 2] is VSP_E_ARG. */
 vsp_status vsp_cbkey_set_form(vsp_cbkey* key, int form);
 
 /* d_out[r] [2l][2][N] = the level-1 TRGSW of the bit that the level-0 TLWE d_in[r] [n+1]

@@ -475,7 +475,7 @@ vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const ui
                                 double* br_ms) {
   vsp_status s = check_ctx(ctx);
   if (s) return s;
-  if (waves != 3 && waves != 4 && waves != 8) return fail(VSP_E_ARG, "waves must be 3, 4 or 8 (an NTT form)");
+  if (waves != 3 && waves != 4 && waves != 8) return fail(VSP_E_ARG, "waves must be 3, 4 or 8 (a transform form)");
   if (copies == 0 || copies > 65536) return fail(VSP_E_ARG, "copies must be in [1, 65536]");
   if (br_ms == nullptr) return fail(VSP_E_ARG, "br_ms must be non-NULL");
   if (B > kMaxLaunch) return fail(VSP_E_ARG, "B above one launch (" + std::to_string(kMaxLaunch) + " gates)");
@@ -484,11 +484,16 @@ vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const ui
   VSP_HIP(hipSetDevice(ctx->device));
   if ((s = check_gate_args(ctx, d_ops, d_in0, d_in1, d_out, B, VSP_BATCHED, false))) return s;
   const size_t key_bytes = (size_t)LWE_N * TRGSW_FFT_C64 * sizeof(c64);
-  const size_t copy_bytes = copies > 1 ? (size_t)copies * key_bytes : 0;
+  // No form holds more than eight gates per compute unit at once, so more copies than that add nothing and
+  // are not made. What a call may ask for is held to 61.9 MB for each copy asked for all the same.
+  const uint32_t held = 8u * (uint32_t)(ctx->cus > 0 ? ctx->cus : 256), made = copies < held ? copies : held;
+  const size_t copy_bytes = copies > 1 ? (size_t)made * key_bytes : 0;
+  const size_t asked_bytes = copies > 1 ? (size_t)copies * LWE_N * 2 * GADGET_L * 2 * RING_N * 8 : 0;
+  const size_t need = copy_bytes > asked_bytes ? copy_bytes : asked_bytes;
   size_t free_b = 0, total_b = 0;
   VSP_HIP(hipMemGetInfo(&free_b, &total_b));
-  if (copy_bytes + (1ull << 30) > free_b)
-    return fail(VSP_E_NOMEM, std::to_string(copies) + " key copies need " + std::to_string(copy_bytes >> 20) +
+  if (need + (1ull << 30) > free_b)
+    return fail(VSP_E_NOMEM, std::to_string(copies) + " key copies need " + std::to_string(need >> 20) +
                                  " MiB; " + std::to_string(free_b >> 20) + " MiB free on the device");
   if ((s = scratch_reserve(ctx, ctx->abar, B * (LWE_N + 1) * 4))) return s;
   if ((s = scratch_reserve(ctx, ctx->tlwe1, B * (RING_N + 1) * 4))) return s;
@@ -507,10 +512,10 @@ vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const ui
     return r;
   };
   hipError_t e;
-  std::vector<const c64*> tab(copies, ctx->bkf);
+  std::vector<const c64*> tab(made, ctx->bkf);
   if (copies > 1) {
     if ((e = hipMalloc(&keys, copy_bytes)) != hipSuccess) return undo(hip_fail(e, "hipMalloc(key copies)"));
-    for (uint32_t c = 0; c < copies; c++) {
+    for (uint32_t c = 0; c < made; c++) {
       tab[c] = keys + (size_t)c * LWE_N * TRGSW_FFT_C64;
       if ((e = hipMemcpyAsync(keys + (size_t)c * LWE_N * TRGSW_FFT_C64, ctx->bkf, key_bytes, hipMemcpyDeviceToDevice,
                               st)) != hipSuccess)
@@ -518,10 +523,10 @@ vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const ui
     }
   }
   std::vector<uint16_t> kid(B);
-  for (uint64_t g = 0; g < B; g++) kid[g] = (uint16_t)(g % copies);
-  if ((e = hipMalloc(&d_tab, copies * sizeof(void*))) != hipSuccess) return undo(hip_fail(e, "hipMalloc(key table)"));
+  for (uint64_t g = 0; g < B; g++) kid[g] = (uint16_t)(g % made);
+  if ((e = hipMalloc(&d_tab, made * sizeof(void*))) != hipSuccess) return undo(hip_fail(e, "hipMalloc(key table)"));
   if ((e = hipMalloc(&d_kid, B * sizeof(uint16_t))) != hipSuccess) return undo(hip_fail(e, "hipMalloc(key index)"));
-  if ((e = hipMemcpyAsync(d_tab, tab.data(), copies * sizeof(void*), hipMemcpyHostToDevice, st)) != hipSuccess ||
+  if ((e = hipMemcpyAsync(d_tab, tab.data(), made * sizeof(void*), hipMemcpyHostToDevice, st)) != hipSuccess ||
       (e = hipMemcpyAsync(d_kid, kid.data(), B * sizeof(uint16_t), hipMemcpyHostToDevice, st)) != hipSuccess)
     return undo(hip_fail(e, "key table upload"));
   if ((e = hipEventCreate(&e0)) != hipSuccess || (e = hipEventCreate(&e1)) != hipSuccess)
