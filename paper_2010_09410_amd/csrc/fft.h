@@ -524,9 +524,10 @@ struct DigitWords {
 // representative) of the rotated coefficient, whose sign is bit 12 (the wrap X^1024 = -1).
 __device__ __forceinline__ u32 rotated_word(const u32* p, int bt, u32 own) {
   const u32 raw = *reinterpret_cast<const u32*>(reinterpret_cast<const char*>(p) + (bt & (4 * RING_N - 4)));
-  u32 m;
+  u32 m, x;
   asm("v_bfe_i32 %0, %1, 12, 1" : "=v"(m) : "v"(bt));  // 0, or all ones: (raw ^ m) - m = -raw
-  return ((raw ^ m) + (DECOMP_OFFSET - own - m)) ^ DIGIT_FLIP;
+  asm("v_xad_u32 %0, %1, %2, %3" : "=v"(x) : "v"(raw), "v"(m), "s"(DECOMP_OFFSET));  // (raw ^ m) + offset
+  return (x - (own + m)) ^ DIGIT_FLIP;
 }
 
 // Sums of a wave's products in the transform domain: [product][slot pair p]; lane l + 32 s holds
