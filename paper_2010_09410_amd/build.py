@@ -19,13 +19,21 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
+# The compiler's instruction order, where another than its default measured faster: 2,048 gates in the
+# one-wave form 12.57 ms instead of 12.83 (the latency forms lose 2% by it), a step of the level-2
+# blind rotation 17.6 us instead of 18.0.
+SCHED = {"blind_rotate.hip": "max-ilp", "circuit_bootstrap.hip": "max-memory-clause"}
+
+
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
 
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj]
+    strategy = SCHED.get(os.path.basename(src))
+    sched = ["-mllvm", f"-amdgpu-sched-strategy={strategy}"] if strategy else []
+    cmd = [HIPCC, *FLAGS, *sched, "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")

@@ -2,7 +2,6 @@
 // prologue (linear combination + modulus switch), blind rotation with SampleExtract,
 // identity key switching, and test kernels for the external product and polynomial product.
 #include "vsp_internal.h"
-#include "blind_rotate.h"
 #include "blind_rotate_wide.h"
 
 namespace vsp {
@@ -174,13 +173,11 @@ hipError_t init_kernel_attributes() {
   const struct {
     const void* fn;
     size_t lds;
-  } k[] = {{reinterpret_cast<const void*>(&k_blind_rotate<8, true>), br_lds_bytes(8, true)},
-           {reinterpret_cast<const void*>(&k_blind_rotate<8, false>), br_lds_bytes(8, false)},
-           {reinterpret_cast<const void*>(&k_blind_rotate_wide<1>), brw_lds_bytes(1)},
+  } k[] = {{reinterpret_cast<const void*>(&k_blind_rotate_wide<1>), brw_lds_bytes(1)},
            {reinterpret_cast<const void*>(&k_blind_rotate_wide<2>), brw_lds_bytes(2)}};
   for (const auto& x : k)
     if (hipError_t e = hipFuncSetAttribute(x.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)x.lds)) return e;
-  return hipSuccess;
+  return init_blind_rotate_waves();
 }
 
 hipError_t blind_rotate_capacity(int device, uint64_t (&cap)[kBrShapes]) {
@@ -190,8 +187,7 @@ hipError_t blind_rotate_capacity(int device, uint64_t (&cap)[kBrShapes]) {
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n4, reinterpret_cast<const void*>(&k_blind_rotate_wide<2>),
                                                      BRW_WAVES * 64, brw_lds_bytes(2));
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n8, reinterpret_cast<const void*>(&k_blind_rotate<8, true>), 512,
-                                                     br_lds_bytes(8, true));
+    e = blind_rotate_waves_per_cu(&n8);
   if (e == hipSuccess)
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nw, reinterpret_cast<const void*>(&k_blind_rotate_wide<1>),
                                                      BRW_WAVES * 64, brw_lds_bytes(1));
@@ -242,13 +238,9 @@ hipError_t launch_blind_rotate(const vsp_context* ctx, const uint8_t* ops, const
                          ctx->ftab + FFT_TAB_C64, ops ? ops + pairs : nullptr, abar + pairs * TLWE0,
                          tlwe1 ? tlwe1 + pairs * TLWE1 : nullptr, trlwe ? trlwe + pairs * 2 * RING_N : nullptr, B - pairs,
                          keytab, kid);
-  } else {
-    // one key for all gates: the workgroup shares it; per-gate keys: each wave reads its own
-    auto* kern = keytab ? &k_blind_rotate<8, false> : &k_blind_rotate<8, true>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((B + 7) / 8)), dim3(512), br_lds_bytes(8, keytab == nullptr), st, bkf,
-                       ctx->ftab, ops, abar, tlwe1, trlwe, B, keytab, kid);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  return launch_blind_rotate_waves(ctx, bkf, ops, abar, tlwe1, trlwe, B, keytab, kid, st);
 }
 
 // ------------------------------------------------------------------ key switching

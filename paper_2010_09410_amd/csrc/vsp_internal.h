@@ -90,7 +90,7 @@ constexpr uint64_t kSplitAt[kSplitPts] = {1, 16, 64, 256, 512, 768, 1024, 1280, 
 //    gates 276 against 3,120).
 struct Tuning {
   uint64_t br_cap[kBrShapes] = {512, 2048, 256, 4096, MF_TILE};
-  float br_round_ms[kBrShapes] = {4.04f, 13.0f, 2.38f, 82.0f, 4.2f};
+  float br_round_ms[kBrShapes] = {4.04f, 12.8f, 2.36f, 82.0f, 4.2f};
   // split form, at the sizes kSplitAt: time in the same units as br_round_ms, and row groups
   // (0: the count that fills the chip, mf_split_groups). The defaults are milliseconds measured
   // on an MI355X.
@@ -235,6 +235,12 @@ struct ProfScope {
 
 // ---------------------------------------------------------------- launchers (kernels.hip)
 hipError_t init_kernel_attributes();
+// One-wave form of the blind rotation (blind_rotate.hip).
+hipError_t init_blind_rotate_waves();
+hipError_t blind_rotate_waves_per_cu(int* workgroups);
+hipError_t launch_blind_rotate_waves(const vsp_context* ctx, const c64* bkf, const uint8_t* ops, const uint32_t* abar,
+                                     uint32_t* tlwe1, uint32_t* trlwe, uint64_t B, const c64* const* keytab,
+                                     const uint16_t* kid, hipStream_t st);
 // Gates the device runs at once with each blind-rotation shape (resident groups x CUs x waves).
 hipError_t blind_rotate_capacity(int device, uint64_t (&cap)[kBrShapes]);
 // Torus TRGSW [count][2l][2][N] -> the complex transform's key layout [count][TRGSW_FFT_C64].
