@@ -20,9 +20,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 
 
 # The compiler's instruction order, where another than its default measured faster: 2,048 gates in the
-# one-wave form 12.57 ms instead of 12.83 (the latency forms lose 2% by it), a step of the level-2
-# blind rotation 17.6 us instead of 18.0.
-SCHED = {"blind_rotate.hip": "max-ilp", "circuit_bootstrap.hip": "max-memory-clause"}
+# one-wave form 12.36 ms instead of 12.87 (12.55 by the first of its options alone; the latency forms
+# lose by both), a step of the level-2 blind rotation 17.6 us instead of 18.0.
+ORDER = {"blind_rotate.hip": ["-amdgpu-sched-strategy=max-ilp", "-amdgpu-use-amdgpu-trackers=1"],
+         "circuit_bootstrap.hip": ["-amdgpu-sched-strategy=max-memory-clause"]}
 
 
 def sources():
@@ -31,9 +32,8 @@ def sources():
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    strategy = SCHED.get(os.path.basename(src))
-    sched = ["-mllvm", f"-amdgpu-sched-strategy={strategy}"] if strategy else []
-    cmd = [HIPCC, *FLAGS, *sched, "-c", src, "-o", obj]
+    order = [x for option in ORDER.get(os.path.basename(src), []) for x in ("-mllvm", option)]
+    cmd = [HIPCC, *FLAGS, *order, "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")
