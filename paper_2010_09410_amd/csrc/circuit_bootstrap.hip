@@ -218,8 +218,8 @@ __global__ __launch_bounds__(256) void k_cb_key(const u64* __restrict__ bk2, c64
 // every row has been read, the sums take the rows' place, waves 0-5 invert one each and leave its
 // integers, shifted by their limb, in its region, and all waves add the three of each output to ACC.
 // The rows and the accumulator fill the 160 KiB of LDS. The key, 786 KB a step, is read once per job,
-// two rows' entries (12 each per lane) ahead of use. A step takes 17.8 us: 12.7 without the key loads
-// (VALU issue, 27,000 cycles, and LDS), the rest is the key's stream, 50 to 64 bytes a clock, past the two
+// two rows' entries (12 each per lane) ahead of use. A step takes 17.6 us: 12.7 without the key loads
+// (transforms and LDS in turn), the rest is the key's stream, 50 to 64 bytes a clock, past the two
 // rows that the registers hold. Those two are loaded beside the inverse transform; asked for among
 // the last products, where the stream is the bound, a step took 18.9 us. The result is
 // SampleExtract_0 + 1/(2 Bg^j) as a TLWE2.

@@ -438,8 +438,8 @@ __device__ __forceinline__ void fft8_inverse(double (&re)[8], double (&im)[8], c
 // The inverse of a sum that lies as fft_key_round leaves it: lane m holds entry m of the slot pairs, so
 // it plays the whole-wave lane L with fft_half_lane(L) = m. Afterwards lane m holds the coefficients
 // m + 64 t. One polynomial on all 64 lanes, where the half-wave inverse would leave half of them idle (288
-// float64 instructions a wave instead of 576; a round of 2,048 gates, bound by their issue, takes 13.5 ms
-// instead of 14.8). The exchanges XOR a residue's words with a number that spreads these lanes over all banks.
+// float64 instructions a wave instead of 576, which brought a round of 2,048 gates, bound by their issue,
+// from 14.8 to 13.5 ms). The exchanges XOR a residue's words with a number that spreads these lanes over all banks.
 __host__ __device__ constexpr int fft_wave_role(int m) { return 4 * (m & 15) + 2 * ((m >> 4) & 1) + (m >> 5); }
 struct FftWavePass {
   const c64* tab;  // [entry][lane], at the lane
