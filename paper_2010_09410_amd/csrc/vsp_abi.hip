@@ -1,6 +1,7 @@
 // C ABI of libvsp: status codes, the context, batched / per-gate homomorphic gates,
 // TRLWE-output bootstrapping and the test entry points. CMUX memory, circuits and the
 // server have their own files.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -670,12 +671,18 @@ vsp_status vsp_debug_external_product(vsp_context* ctx, const uint32_t* d_trgsw,
   if ((s = check_device_range(ctx, d_out, xb, "d_out"))) return s;
   if ((s = check_no_overlap(d_out, xb, d_x, xb, "d_out and d_x"))) return s;
   if ((s = check_no_overlap(d_out, xb, d_trgsw, cb, "d_out and d_trgsw"))) return s;
-  if ((s = scratch_reserve(ctx, ctx->sel, (size_t)J * TRGSW_FFT_C64 * sizeof(c64)))) return s;
+  const uint64_t chunk = std::min<uint64_t>(J, 1ull << 14);  // transformed TRGSWs held at once: 2.4 GB
+  if ((s = scratch_reserve(ctx, ctx->sel, (size_t)chunk * TRGSW_FFT_C64 * sizeof(c64)))) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
   c64* cn = static_cast<c64*>(ctx->sel.ptr);
   hipError_t e;
-  if ((e = launch_trgsw_to_fft(ctx, d_trgsw, cn, J, st)) != hipSuccess) return hip_fail(e, "trgsw conversion");
-  if ((e = launch_ext_product(ctx, cn, d_x, d_out, J, st)) != hipSuccess) return hip_fail(e, "external product");
+  for (uint64_t j0 = 0; j0 < J; j0 += chunk) {
+    const uint64_t n = std::min(chunk, J - j0);
+    if ((e = launch_trgsw_to_fft(ctx, d_trgsw + j0 * 4 * GADGET_L * RING_N, cn, n, st)) != hipSuccess)
+      return hip_fail(e, "trgsw conversion");
+    if ((e = launch_ext_product(ctx, cn, d_x + j0 * 2 * RING_N, d_out + j0 * 2 * RING_N, n, st)) != hipSuccess)
+      return hip_fail(e, "external product");
+  }
   return VSP_OK;
 }
 

@@ -33,8 +33,8 @@ __host__ __device__ inline bool op_bootstraps(uint32_t op) { return op < 8 || op
 constexpr int DEVERR_BAD_OP = 1;
 
 // Blind-rotation forms: 8 for one wave per gate, eight gates per workgroup and compute unit; 3 and 4
-// for one workgroup of eight waves per gate, one (3) or two (4) of them per compute unit (the
-// latency forms); 32 for the matrix-core form (int8 MFMA products over tiles of MF_TILE gates, one
+// for workgroups of eight waves, one per compute unit, of one gate (3) or two (4), 3 in whole rounds
+// of two gates per compute unit like 4 (the latency forms); 32 for the matrix-core form (int8 MFMA products over tiles of MF_TILE gates, one
 // workgroup per tile and output polynomial, one launch per step), and 33 for its split form (the
 // products of a step cut into workgroups per tile, output polynomial, sub-product and group of
 // TRGSW rows, and for single rows also per range of byte planes; two launches per step).
@@ -74,7 +74,7 @@ constexpr uint64_t kSplitAt[kSplitPts] = {1, 16, 64, 256, 512, 768, 1024, 1280, 
 
 // Launch choices, set by vsp_autotune or left at the defaults. Every choice gives
 // bit-identical results.
-//  * Blind rotation: a gate is one wave from start to end, so a batch of B gates takes
+//  * Blind rotation: a gate stays on one workgroup from start to end, so a batch of B gates takes
 //    ceil(B / br_cap[s]) rounds of br_round_ms[s] with shape s, where br_cap[s] is the number
 //    of gates the whole GPU holds at once (occupancy x compute units x gates per group) and
 //    br_round_ms[s] the time of one full round. The split matrix-core form is timed instead

@@ -243,7 +243,7 @@ class CbKey:
                                           np.ascontiguousarray(pksk, dtype=np.uint32))
 
     def set_form(self, form: int) -> None:
-        """Level-2 blind rotation: 0 by batch size, 1 four-wave form, 2 eight-wave form."""
+        """0, 1 or 2, without effect: one form of the level-2 blind rotation serves every batch size."""
         nv.vsp_cbkey_set_form(self.handle, form)
 
     def bootstrap(self, tlwe: torch.Tensor, out=None) -> torch.Tensor:

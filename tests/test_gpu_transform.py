@@ -221,3 +221,12 @@ def test_a_tuning_measured_with_other_kernels_is_measured_again(gpu, tmp_path):
     finally:
         for b, t in saved.items():
             gpu.set_tuning(b, 0, t)
+
+
+def test_external_products_past_one_chunk(gpu):
+    """More external products than are transformed at once (2^14): each is what it is alone."""
+    J = (1 << 14) + 3
+    C, x = random_words(gpu, 11, J, 6, 2, N), random_words(gpu, 12, J, 2, N)
+    out = to_host(gpu.debug_external_product(C, x))
+    for j in (0, (1 << 14) - 1, 1 << 14, J - 1):
+        np.testing.assert_array_equal(out[j], to_host(gpu.debug_external_product(C[j:j + 1].contiguous(), x[j:j + 1].contiguous()))[0])
