@@ -218,10 +218,10 @@ __global__ __launch_bounds__(256) void k_cb_key(const u64* __restrict__ bk2, c64
 // every row has been read, the sums take the rows' place, waves 0-5 invert one each and leave its
 // integers, shifted by their limb, in its region, and all waves add the three of each output to ACC.
 // The rows and the accumulator fill the 160 KiB of LDS. The key, 786 KB a step, is read once per job,
-// two rows' entries (12 each per lane) ahead of use. A step takes 17.6 us: 12.7 without the key loads
+// two rows' entries (12 each per lane) ahead of use. A step takes 17.1 us: 12.2 without the key loads
 // (transforms and LDS in turn), the rest is the key's stream, 50 to 64 bytes a clock, past the two
 // rows that the registers hold. Those two are loaded beside the inverse transform; asked for among
-// the last products, where the stream is the bound, a step took 18.9 us. The result is
+// the last products, where the stream is the bound, a step took 1 us more. The result is
 // SampleExtract_0 + 1/(2 Bg^j) as a TLWE2.
 constexpr size_t CB_LDS = (size_t)CB_ROWS * CB_REGION_C64 * 16 + 2 * CB_N2 * 8;
 static_assert(CB_ROWS == CB_WAVES && CB_PRODUCTS <= CB_WAVES, "one wave per row and per sum");
@@ -263,6 +263,9 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cb_rotate(const c64* __restri
   }
   u32 c_next = __builtin_amdgcn_readfirstlane(c[0]);
   __syncthreads();
+  u64 own[2 * CB_N2 / (CB_WAVES * 64)];  // this thread's words of ACC, from the end of a step to the next one's start
+#pragma unroll
+  for (int q = 0; q < 2 * CB_N2 / (CB_WAVES * 64); q++) own[q] = acc[tid + CB_WAVES * 64 * q];
   for (int i = 0; i < LWE_N; i++) {
     const int abar = (int)(((c_next + (1u << 19)) >> 20) & (2 * CB_N2 - 1));
     c_next = __builtin_amdgcn_readfirstlane(c[i + 1]);  // (the last one is b)
@@ -277,7 +280,7 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cb_rotate(const c64* __restri
       const u64* P = acc + (q / (CB_N2 / (CB_WAVES * 64))) * CB_N2;
       const int src = m - abar;
       const u64 raw = P[src & (CB_N2 - 1)], neg = (u64)((int64_t)((int)((u32)src << 20) >> 31));
-      words[tid + CB_WAVES * 64 * q] = ((raw ^ neg) + (CB_DECOMP_OFFSET - P[m] - neg)) ^ CB_DIGIT_FLIP;
+      words[tid + CB_WAVES * 64 * q] = ((raw ^ neg) + (CB_DECOMP_OFFSET - own[q] - neg)) ^ CB_DIGIT_FLIP;
     }
     __syncthreads();
     {
@@ -345,7 +348,8 @@ __global__ __launch_bounds__(CB_WAVES * 64) void k_cb_rotate(const c64* __restri
       constexpr int PER = CB_N2 / (CB_WAVES * 64), REGION = CB_REGION_C64 * 2;
       const int m = opaque_lane(tid) + CB_WAVES * 64 * (q % PER);
       const u64* z = reinterpret_cast<const u64*>(cb_lds) + (q / PER) * CB_LIMBS * REGION + m;
-      acc[(q / PER) * CB_N2 + m] += z[0] + z[REGION] + z[2 * REGION];
+      own[q] = acc[(q / PER) * CB_N2 + m] + (z[0] + z[REGION] + z[2 * REGION]);
+      acc[(q / PER) * CB_N2 + m] = own[q];
     }
     __syncthreads();
   }
