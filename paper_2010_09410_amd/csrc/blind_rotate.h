@@ -21,8 +21,9 @@ constexpr size_t br_lds_bytes(int waves, bool shared) {
 
 // What bounds it is VALU issue, 73% busy: 3,912 instructions a wave and step, 2,784 of them float64, with
 // the two waves a SIMD that 256 registers and 17 KiB of LDS per gate allow; LDS is 42% busy, barriers and
-// key stream cost 6%. 2,048 gates, one round, take 12.5 ms; the transform modulo a 64-bit prime took 54,
-// the int8 matrix products 41.
+// key stream cost 6%. 2,048 gates, one round, take 12.2 ms (12.5 with LDS atomics into ACC and its
+// words read again in the next step); the transform modulo a 64-bit prime took 54, the int8 matrix
+// products 41.
 // SHARED: every gate uses the key bkf, which the workgroup streams through LDS; its waves meet at
 // every piece, so a wave without a gate takes part as well (on a zero accumulator). Otherwise gate g
 // reads the key keytab[kid[g]] by itself (clients with their own keys in one launch), or bkf with
@@ -56,6 +57,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_blind_rotate(const c64* __restri
     for (int t = 0; t < 32; t++) accs[l + 32 * t] = (h && live) ? rotated_testvector(l + 32 * t, k0) : 0u;
   }
   wave_lds_sync();
+  u32 own[32];  // the lane's coefficients of ACC, from the end of a step to the start of the next
+#pragma unroll
+  for (int t = 0; t < 32; t++) own[t] = wbase[h * RING_N + l + 32 * t];
   for (int i = 0; i < LWE_N; i++) {
     const int a = (int)__builtin_amdgcn_readfirstlane(ab[i]);
     if (!SHARED && a == 0) continue;
@@ -64,7 +68,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_blind_rotate(const c64* __restri
     u32* accs = wbase + hi * RING_N;
     double* reg = reinterpret_cast<double*>(wbase + 2 * RING_N) + hi * FFT_REGION;
     const int bt = 4 * (li - a);
-    auto word = [&](int t) { return rotated_word(accs, bt + 128 * t, accs[li + 32 * t]); };
+    auto word = [&](int t) { return rotated_word(accs, bt + 128 * t, own[t]); };
     u32 z[32];
     if constexpr (SHARED) {
       fft_external_product(word, shared, tabs, reg, ln, z);
@@ -74,8 +78,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_blind_rotate(const c64* __restri
       fft_external_product(word, key, tabs, reg, ln, z);
     }
 #pragma unroll
-    for (int t = 0; t < 32; t++)
-      __hip_atomic_fetch_add(&accs[li + 32 * t], z[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    for (int t = 0; t < 32; t++) own[t] = accs[li + 32 * t];
+#pragma unroll
+    for (int t = 0; t < 32; t++) accs[li + 32 * t] = own[t] += z[t];
     wave_lds_sync();
   }
   if (!live) return;

@@ -90,7 +90,7 @@ constexpr uint64_t kSplitAt[kSplitPts] = {1, 16, 64, 256, 512, 768, 1024, 1280, 
 //    gates 276 against 3,120).
 struct Tuning {
   uint64_t br_cap[kBrShapes] = {512, 2048, 256, 4096, MF_TILE};
-  float br_round_ms[kBrShapes] = {4.04f, 12.5f, 2.36f, 82.0f, 4.2f};
+  float br_round_ms[kBrShapes] = {4.04f, 12.2f, 2.36f, 82.0f, 4.2f};
   // split form, at the sizes kSplitAt: time in the same units as br_round_ms, and row groups
   // (0: the count that fills the chip, mf_split_groups). The defaults are milliseconds measured
   // on an MI355X.
