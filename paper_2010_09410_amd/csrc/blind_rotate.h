@@ -19,7 +19,7 @@ constexpr size_t br_lds_bytes(int waves, bool shared) {
   return FFT_TAB_C64 * 16 + (shared ? 2 * FFT_PIECE_C64 * 16 : 0) + (size_t)waves * BR_WAVE_U32 * 4;
 }
 
-// What bounds it is VALU issue, 73% busy: 3,912 instructions a wave and step, 2,784 of them float64, with
+// What bounds it is VALU issue, 75% busy: 3,944 instructions a wave and step, 2,784 of them float64, with
 // the two waves a SIMD that 256 registers and 17 KiB of LDS per gate allow; LDS is 42% busy, barriers and
 // key stream cost 6%. 2,048 gates, one round, take 12.2 ms (12.5 with LDS atomics into ACC and its
 // words read again in the next step); the transform modulo a 64-bit prime took 54, the int8 matrix
