@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "blind_rotate_wide.h"
+#include "launch_rules.h"
 
 namespace vsp {
 
@@ -461,11 +462,6 @@ __global__ void k_ram_control_tables(uint32_t* __restrict__ idx, uint8_t* __rest
 static hipError_t launch_ram_control_tables(uint32_t* idx, uint8_t* ops, uint32_t w, hipStream_t st) {
   hipLaunchKernelGGL(k_ram_control_tables, dim3((w + 255) / 256), dim3(256), 0, st, idx, ops, w);
   return hipGetLastError();
-}
-
-// Reads per launch sequence: at most 2^14 transformed selectors (2.4 GB of scratch) at a time.
-static uint64_t read_chunk(uint64_t R, uint32_t v) {
-  return std::min<uint64_t>(R, std::max<uint64_t>(1, (1ull << 14) / v));
 }
 
 }  // namespace vsp

@@ -150,3 +150,16 @@ def test_memory_size_limits_rejected(gpu):
         nv.vsp_ram_read(gpu.handle, ptr, 8, 1024, ptr, ptr, 1 << 13, gpu.stream())
     with pytest.raises(VspError):
         nv.vsp_ram_write(gpu.handle, ptr, 16, 128, ptr, ptr, ptr, gpu.stream())
+
+
+def test_rom_of_one_word(gpu, keys):
+    """A ROM of one 1,024-bit word has no address bits (v = 0, P = 1): every read is the extraction and key switch of
+    the one polynomial."""
+    g = W.rng(601)
+    rom = W.uniform_u32(g, (1, 2, N))
+    for R in (1, 3):
+        addr = gpu.tensor(np.zeros((R, 1), np.uint32))                      # a buffer, of which nothing is read
+        out = to_host(gpu.rom_read(gpu.tensor(rom), addr, 0, 1024))
+        ref = oracle.rom_read(keys["ksk"], rom, np.zeros((0, 6, 2, N), np.uint32), wbits=1024)
+        for r in range(R):
+            np.testing.assert_array_equal(out[r], ref, err_msg=f"read {r} of {R}")
