@@ -230,3 +230,41 @@ def test_external_products_past_one_chunk(gpu):
     out = to_host(gpu.debug_external_product(C, x))
     for j in (0, (1 << 14) - 1, 1 << 14, J - 1):
         np.testing.assert_array_equal(out[j], to_host(gpu.debug_external_product(C[j:j + 1].contiguous(), x[j:j + 1].contiguous()))[0])
+
+
+def test_workgroups_without_a_bootstrap_end_at_once(gpu):
+    """Workgroups of the key-sharing form none of whose gates bootstraps: no pass over the key for 2,048 NOT gates through
+    the allocation-free entry point (0.3 ms with launches, where a round of the blind rotation takes 12), and among others
+    the words of the form with a gate per workgroup."""
+    import torch
+    from paper_2010_09410_amd import _native as nv
+    B = 2048
+    a, b = random_words(gpu, 13, B, 631), random_words(gpu, 14, B, 631)
+    out = torch.empty_like(a)
+    times = {}
+    for op in (W.NOT, W.NAND):
+        ops = torch.full((B,), int(op), dtype=torch.uint8, device="cuda")
+        for _ in range(3):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            nv.vsp_gates_noalloc(gpu.handle, ops.data_ptr(), a.data_ptr(), b.data_ptr(), out.data_ptr(), B, nv.VSP_BATCHED,
+                                 gpu.stream())
+            t1.record()
+            t1.synchronize()
+            times[op] = min(times.get(op, 1e9), t0.elapsed_time(t1))
+        if op == W.NOT:
+            np.testing.assert_array_equal(to_host(out), (0 - to_host(a).astype(np.int64)).astype(np.uint32))
+    assert times[W.NOT] < times[W.NAND] / 8, times
+    ops = np.full(61, W.NAND, np.uint8)
+    for lo, hi in ((0, 8), (10, 32), (40, 48), (56, 61)):      # whole workgroups of eight, parts of others, the ragged last
+        ops[lo:hi] = W.NOT
+    d = gpu.tensor(ops), a[:61].contiguous(), b[:61].contiguous()
+    _, ks = gpu.tuning(61)
+    outs = []
+    try:
+        for form in (3, 8):
+            gpu.set_tuning(61, form, ks)
+            outs.append(to_host(gpu.gates(*d)))
+    finally:
+        gpu.set_tuning(61, 0, ks)
+    np.testing.assert_array_equal(outs[1], outs[0])
