@@ -128,15 +128,14 @@ vsp_status vsp_gates_noalloc(vsp_context* ctx, const uint8_t* d_ops, const uint3
  * each gate to a worker as a task of its own (Sec. 6.2(d), list scheduling), so every gate's
  * bootstrap makes its own pass over the key; a batch here shares one pass among all its gates
  * (Sec. 2.3: gates of one level are independent). Same results as vsp_gates in batched mode, bit for bit, with
- * the blind rotation in the transform form `waves` (3, 4 or 8) and gate g reading device copy
- * g mod `copies` of the converted key: once `copies` reaches the number of gates the form
- * holds at once, no two resident gates read the same key bytes and nothing of the key is
- * reused through the caches; copies = 1 is the ordinary shared key. 1 <= copies <= 65536,
- * B <= 2^22; *br_ms receives the blind rotation's time (HIP events on `stream`). Allocates
- * 92.9 MB per copy (copies > 1) for the duration of the call, for at most eight copies per compute
- * unit: more gates than that are never held at once, and copies asked for beyond them are the
- * same ones again. VSP_E_NOMEM, nothing enqueued, when the device lacks that or 61.9 MB for every
- * copy asked for. Returns only after the stream has drained. */
+ * the blind rotation in the transform form `waves` (3, 4 or 8) and gate g reading device copy g mod M of
+ * the converted key, 92.9 MB each, made for the duration of the call when copies > 1. M is the smallest
+ * of `copies`, eight per compute unit (no form holds more gates at once, so from there on no two
+ * resident gates read the same key bytes and nothing of the key is reused through the caches) and what the free
+ * device memory holds; copies = 1 is the context's key, which every gate still reads for itself.
+ * 1 <= copies <= 65536, B <= 2^22; *br_ms receives the blind rotation's time (HIP events on `stream`).
+ * VSP_E_NOMEM, nothing enqueued, unless 61.9 MB for every copy asked for (copies > 1) and 1 GiB are free.
+ * Returns only after the stream has drained. */
 vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const uint32_t* d_in0, const uint32_t* d_in1,
                                 uint32_t* d_out, uint64_t B, int waves, uint32_t copies, void* stream,
                                 double* br_ms);

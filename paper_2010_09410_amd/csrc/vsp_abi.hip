@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "launch_rules.h"
 #include "vsp_internal.h"
 
 namespace vsp {
@@ -485,19 +486,15 @@ vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const ui
   VSP_HIP(hipSetDevice(ctx->device));
   if ((s = check_gate_args(ctx, d_ops, d_in0, d_in1, d_out, B, VSP_BATCHED, false))) return s;
   const size_t key_bytes = (size_t)LWE_N * TRGSW_FFT_C64 * sizeof(c64);
-  // No form holds more than eight gates per compute unit at once, so more copies than that add nothing and
-  // are not made. What a call may ask for is held to 61.9 MB for each copy asked for all the same.
-  const uint32_t held = 8u * (uint32_t)(ctx->cus > 0 ? ctx->cus : 256), made = copies < held ? copies : held;
-  const size_t copy_bytes = copies > 1 ? (size_t)made * key_bytes : 0;
-  const size_t asked_bytes = copies > 1 ? (size_t)copies * LWE_N * 2 * GADGET_L * 2 * RING_N * 8 : 0;
-  const size_t need = copy_bytes > asked_bytes ? copy_bytes : asked_bytes;
   size_t free_b = 0, total_b = 0;
   VSP_HIP(hipMemGetInfo(&free_b, &total_b));
-  if (need + (1ull << 30) > free_b)
-    return fail(VSP_E_NOMEM, std::to_string(copies) + " key copies need " + std::to_string(need >> 20) +
+  if (!key_copies_accepted(copies, free_b))
+    return fail(VSP_E_NOMEM, std::to_string(copies) + " key copies need " + std::to_string((copies * kKeyCopyAsked) >> 20) +
                                  " MiB; " + std::to_string(free_b >> 20) + " MiB free on the device");
   if ((s = scratch_reserve(ctx, ctx->abar, B * (LWE_N + 1) * 4))) return s;
   if ((s = scratch_reserve(ctx, ctx->tlwe1, B * (RING_N + 1) * 4))) return s;
+  VSP_HIP(hipMemGetInfo(&free_b, &total_b));  // what the scratch has left
+  const uint32_t made = (uint32_t)key_copies_made(copies, 8ull * (uint64_t)(ctx->cus > 0 ? ctx->cus : 256), free_b, key_bytes);
   hipStream_t st = static_cast<hipStream_t>(stream);
   c64* keys = nullptr;
   const c64** d_tab = nullptr;
@@ -515,7 +512,7 @@ vsp_status vsp_gates_key_copies(vsp_context* ctx, const uint8_t* d_ops, const ui
   hipError_t e;
   std::vector<const c64*> tab(made, ctx->bkf);
   if (copies > 1) {
-    if ((e = hipMalloc(&keys, copy_bytes)) != hipSuccess) return undo(hip_fail(e, "hipMalloc(key copies)"));
+    if ((e = hipMalloc(&keys, made * key_bytes)) != hipSuccess) return undo(hip_fail(e, "hipMalloc(key copies)"));
     for (uint32_t c = 0; c < made; c++) {
       tab[c] = keys + (size_t)c * LWE_N * TRGSW_FFT_C64;
       if ((e = hipMemcpyAsync(keys + (size_t)c * LWE_N * TRGSW_FFT_C64, ctx->bkf, key_bytes, hipMemcpyDeviceToDevice,

@@ -74,7 +74,8 @@ class Context:
         return out
 
     def gates_key_copies(self, ops, in0, in1, waves: int, copies: int, out=None):
-        """(outputs, blind-rotation ms) of gates whose gate g reads its own key copy g mod copies."""
+        """(outputs, blind-rotation ms) of gates whose gate g reads key copy g mod M, M = copies as far as gates
+        are held at once and the memory holds them (include/vsp.h)."""
         B = ops.numel()
         if out is None:
             out = self.empty(B, self.N_LWE + 1)

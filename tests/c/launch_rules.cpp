@@ -22,5 +22,24 @@ int main() {
       check(n * v <= 1ull << 14 || n == 1, "selectors above 2^14", R, v);
       check(n == R || (n + 1) * (v ? v : 1) > 1ull << 14, "fewer reads than fit", R, v);
     }
+  // every count of key copies (92.9 MB each), at free memories around each count's line: taken when 61.9 MB for every
+  // copy and 1 GiB are free; then at least one, no more than asked for or held, within what is left when up to
+  // 1 GiB of scratch has been taken, and all of them where they fit
+  const uint64_t asked = 61931520, key = 92897280, GiB = 1ull << 30;
+  check(vsp::key_copies_accepted(1, GiB) && !vsp::key_copies_accepted(1, GiB - 1), "one copy", 1, GiB);
+  for (uint64_t held : {256ull, 2048ull})
+    for (uint64_t copies = 2; copies <= 65536; copies++)
+      for (int64_t off : {-1, 0, 1}) {
+        const uint64_t line = copies * asked + GiB, free_b = line + off;
+        check(vsp::key_copies_accepted(copies, free_b) == (off >= 0), "accepted", copies, free_b);
+        if (off < 0) continue;
+        for (uint64_t left : {free_b, free_b - GiB, (uint64_t)288 << 30}) {
+          const uint64_t n = vsp::key_copies_made(copies, held, left, key);
+          check(n >= 1 && n <= copies && n <= held, "copies outside [1, min(copies, held)]", copies, left);
+          check(n * key <= left, "copies beyond the memory left", copies, left);
+          if ((copies < held ? copies : held) * key + (64ull << 20) <= left)
+            check(n == (copies < held ? copies : held), "fewer copies than fit", copies, left);
+        }
+      }
   return 0;
 }
