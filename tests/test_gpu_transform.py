@@ -268,3 +268,63 @@ def test_workgroups_without_a_bootstrap_end_at_once(gpu):
     finally:
         gpu.set_tuning(61, 0, ks)
     np.testing.assert_array_equal(outs[1], outs[0])
+
+
+@pytest.mark.parametrize("pattern", ["constant", "alternating", "wave", "random"])
+def test_extreme_keys_in_workgroups_of_two_gates(keys, pattern):
+    """One gate more than compute units in form 4: all of them, an odd last one too, run on workgroups of two gates, whose
+    first exchange goes through registers."""
+    import torch
+    bk = extreme_key(pattern)
+    g = W.rng(86)
+    ops = np.array([W.NAND, W.XOR, W.ORNOT], np.uint8)
+    x = client.tlwe_encrypt_bits(keys["s0"], g.integers(0, 2, 6), *W.tlwe_draws(g, 6))
+    ref = oracle.gates(bk, keys["ksk"], ops, x[:3], x[3:])
+    B = torch.cuda.get_device_properties(0).multi_processor_count + 1
+    of = np.arange(B) % 3
+    with Context(bk, keys["ksk"]) as ctx:
+        ctx.set_tuning(B, 4, 3)
+        out = to_host(ctx.gates(ctx.tensor(ops[of]), ctx.tensor(x[of]), ctx.tensor(x[3 + of])))
+        ctx.sync()
+    np.testing.assert_array_equal(out, ref[of])
+
+
+def test_extreme_words_in_every_shape_of_the_cmux_memory(gpu, keys):
+    """Selectors and cell differences at the ends of their ranges through CMUXes that share a selector, on a workgroup and
+    on a wave each, and through ROM rotations in workgroups of eight waves (2,049 reads), of one, and on a workgroup."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    g = W.rng(87)
+    j = np.arange(N)
+    signs = [np.ones(N, bool), j % 2 == 0, np.cos(np.pi * (j + 0.5) / N) >= 0, g.integers(0, 2, N) == 1]
+    sel = np.stack([np.broadcast_to(np.where(s, np.uint32(0x7FFFFFF7), np.uint32(0x80000000)), (6, 2, N)) for s in signs])
+    word = np.stack([np.broadcast_to(np.where(s, HIGH, LOW), (2, N)) for s in signs])
+    ram = np.zeros((8, 2, 2, N), np.uint32)             # bits 0-3: cells 0 and x, bits 4-7: -x and 0
+    ram[:4, 1], ram[4:, 0] = word, (1 << 32) - word.astype(np.uint64)
+    addr = gpu.tensor(np.ascontiguousarray(sel[np.arange(cus + 1) % 4, None]))
+    ref = oracle.ram_reads(keys["ksk"], ram, sel[:, None])
+    for R in (cus + 1, cus // 2, 4):                    # 8 CMUXes a read
+        out = to_host(gpu.ram_read(gpu.tensor(ram), addr[:R].contiguous()))
+        np.testing.assert_array_equal(out, ref[np.arange(R) % 4], err_msg=f"{R} RAM reads")
+    v, w = 5, 32                                        # blocks of 32 that change sign: X^-32 P - P = -2 P = LOW, -LOW
+    half = np.uint32(((1 << 32) - int(LOW)) // 2)
+    rom = np.broadcast_to(np.where((j // 32) % 2 == 0, half, (0 - half.astype(np.int64)).astype(np.uint32)), (1, 2, N))
+    rom = np.ascontiguousarray(rom)
+    R = 8 * cus + 1
+    sels = np.ascontiguousarray(np.broadcast_to(sel[:, None], (4, v, 6, 2, N)))
+    addr = gpu.tensor(sels)[torch.arange(R, device="cuda") % 4].contiguous()
+    ref = oracle.rom_reads(keys["ksk"], rom, sels)
+    for n in (R, 2 * cus + 1, 4):
+        out = to_host(gpu.rom_read(gpu.tensor(rom), addr[:n].contiguous(), v, w))
+        np.testing.assert_array_equal(out, ref[np.arange(n) % 4], err_msg=f"{n} ROM reads")
+
+
+def test_shared_selectors_in_several_rounds(gpu):
+    """Tree levels whose workgroups take several groups of eight CMUXes in turn, with a remainder: 52 per read in four rounds
+    of two workgroups, then 26 in two rounds (on 256 compute units), against reads alone, whose CMUXes take a workgroup each."""
+    import torch
+    R = torch.cuda.get_device_properties(0).multi_processor_count // 2
+    ram, addr = random_words(gpu, 15, 13, 8, 2, N), random_words(gpu, 16, R, 3, 6, 2, N)
+    out = to_host(gpu.ram_read(ram, addr))
+    for r in (0, 1, R // 2, R - 1):
+        np.testing.assert_array_equal(out[r], to_host(gpu.ram_read(ram, addr[r:r + 1].contiguous()))[0], err_msg=f"read {r}")
