@@ -280,10 +280,10 @@ vsp_status vsp_mux(vsp_context* ctx, const uint32_t* d_sel, const uint32_t* d_in
  * of two per compute unit like 4), so a batch of B gates runs in ceil(B / cap) rounds, cap being the
  * gates the GPU holds at once for a shape. The matrix-core form (32) instead runs each step as int8
  * MFMA products of the batch's digit rows with the key's Toeplitz blocks (tiles of 32 gates;
- * one round holds 16 gates per compute unit; used by vsp_gates and vsp_bootstrap_trlwe with the
- * context's own key, the other callers run the 8-gate form in its place; it needs a workspace
- * of 26 KiB per gate (18 KiB when the output is the TRLWE accumulator), grown on demand). This call times one full round of each shape on random
- * ciphertexts, and times the four key-switch forms (0: one workgroup per gate gathering its
+ * one round holds 16 gates per compute unit; it needs byte planes of the key and a workspace of
+ * 26 KiB per gate (18 KiB when the output is the TRLWE accumulator), grown on demand; launches without them,
+ * as those of vsp_gates_noalloc, run the best of 3, 4 and 8 in its place). This call times one full round of
+ * each shape on random ciphertexts, and times the four key-switch forms (0: one workgroup per gate gathering its
  * key rows; 1: tiles of 16 gates reading each key row once and selecting in registers;
  * 2: tiles of 16 gates staging key rows through LDS, with the j range split over workgroups
  * and atomic accumulation; 3: int8 MFMA products of one-hot digit rows with the key's byte

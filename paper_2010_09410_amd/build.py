@@ -21,7 +21,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 
 # The compiler's instruction order, where another than its default measured faster: 2,048 gates in the
 # one-wave form 12.36 ms instead of 12.87 (12.55 by the first of its options alone; the latency forms
-# lose by both), a step of the level-2 blind rotation 17.6 us instead of 18.0 (17.1 since).
+# lose by both), a step of the level-2 blind rotation 17.6 us instead of 18.0 (17.0 since).
 ORDER = {"blind_rotate.hip": ["-amdgpu-sched-strategy=max-ilp", "-amdgpu-use-amdgpu-trackers=1"],
          "circuit_bootstrap.hip": ["-amdgpu-sched-strategy=max-memory-clause"]}
 

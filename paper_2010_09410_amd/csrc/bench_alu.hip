@@ -1,5 +1,5 @@
-// Register-resident throughput of the arithmetic modulo p = 2^64 - 2^32 + 1 that the NTT form
-// of the blind rotation is built from: the general product (gl_mul) and the lazy sum (gl_add),
+// Register-resident throughput of the arithmetic modulo p = 2^64 - 2^32 + 1 that polynomial products
+// by NTT are built from: the general product (gl_mul) and the lazy sum (gl_add),
 // each in eight independent chains per lane at full occupancy, no memory traffic inside the
 // loop. Their rates are the integer-VALU ceiling against which the method's own work per gate
 // (products and sums modulo p of its transforms and key products) is priced.

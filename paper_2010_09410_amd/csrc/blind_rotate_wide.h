@@ -9,9 +9,10 @@
 //     key polynomials;
 //  4. a wave per sum inverts it; those of the K_hi products add it into ACC, the others leave the small
 //     products in LDS. No LDS atomics: 64 lanes of one take about 34 cycles.
-// What bounds a step is the latency of that chain, for one gate about 9,600 cycles: 800, 3,300 (three LDS
-// writes of 8 KiB by each of six waves, at 39 B/clk per pair of SIMDs, are 1,900 of it), 1,200 and 4,000;
-// for two gates 15,000. A wave's whole share of the next step's key is loaded where that delays no one: in
+// What bounds a step is the latency of that chain, for one gate about 9,000 cycles: phases of 800, 3,300
+// (three LDS writes of 8 KiB by each of six waves, at 39 B/clk per pair of SIMDs, are 1,900 of it), 1,200 and
+// 4,000, a little more with the clock reads that told them apart; VALU issue is 41% busy, LDS 44%. For two
+// gates 15,200 cycles, 58% and 44%. A wave's whole share of the next step's key is loaded where that delays no one: in
 // phase 4, by the waves without a sum while the others invert, and by those after they have stored their
 // results (its 18 KiB take 290 cycles to issue; among the products they delayed the sums, in the inverse
 // transform the transform). With two gates LDS is the bound of phase 2 and the first exchange of the

@@ -10,9 +10,10 @@
 // torus key words runs through the complex transform of fft.h, folded to C[X]/(X^1024 - i): the key
 // is split into three signed limbs, K = K_0 + 2^22 K_1 + 2^44 K_2 (mod 2^64, |K_b| <= 2^21), and every
 // limb's product is rounded to the nearest integer. Ten splittings leave a transform within 46 u of
-// its norm (u = 2^-53; 52 u with the turned constants below), the 16 accumulated products of a slot add 16 u
-// and the ten joinings 43 u, so the error of a coefficient is at most 165 u x 8 rows x 2^8 sqrt(2048) x 2^21 sqrt(2048) = 0.17 before
-// rounding: the integers are exact (below 2^43) and the torus words the schoolbook ones.
+// its norm (u = 2^-53; 52 u with the turned constants below), for the digits and for the key. The products
+// of a slot, 16 fused operations per part, add 16 sqrt(2) = 22.6 u of the sum of their magnitudes, and the ten
+// joinings 43 u. So the error of a coefficient is at most 170 u x 8 rows x 2^8 sqrt(2048) x 2^21 sqrt(2048) = 0.17
+// before rounding: the integers are exact (below 2^43) and the torus words the schoolbook ones.
 #include <algorithm>
 #include <vector>
 
@@ -218,9 +219,10 @@ __global__ __launch_bounds__(256) void k_cb_key(const u64* __restrict__ bk2, c64
 // every row has been read, the sums take the rows' place, waves 0-5 invert one each and leave its
 // integers, shifted by their limb, in its region, and all waves add the three of each output to ACC.
 // The rows and the accumulator fill the 160 KiB of LDS. The key, 786 KB a step, is read once per job,
-// two rows' entries (12 each per lane) ahead of use. A step takes 17.1 us: 12.2 without the key loads
-// (transforms and LDS in turn), the rest is the key's stream, 50 to 64 bytes a clock, past the two
-// rows that the registers hold. Those two are loaded beside the inverse transform; asked for among
+// two rows' entries (12 each per lane) ahead of use. A step of 255 jobs takes 17.0 us (of 24 jobs 17.8, of
+// three 19.7: fewer jobs share what comes from memory), 12.3 without the key loads (transforms and LDS in
+// turn: VALU issue is 40% busy, LDS 28%), the rest is the key's stream, 50 to 64 bytes a clock, past the
+// two rows that the registers hold. Those two are loaded beside the inverse transform; asked for among
 // the last products, where the stream is the bound, a step took 1 us more. The result is
 // SampleExtract_0 + 1/(2 Bg^j) as a TLWE2.
 constexpr size_t CB_LDS = (size_t)CB_ROWS * CB_REGION_C64 * 16 + 2 * CB_N2 * 8;

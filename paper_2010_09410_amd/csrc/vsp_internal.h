@@ -77,7 +77,9 @@ constexpr uint64_t kSplitAt[kSplitPts] = {1, 16, 64, 256, 512, 768, 1024, 1280, 
 //  * Blind rotation: a gate stays on one workgroup from start to end, so a batch of B gates takes
 //    ceil(B / br_cap[s]) rounds of br_round_ms[s] with shape s, where br_cap[s] is the number
 //    of gates the whole GPU holds at once (occupancy x compute units x gates per group) and
-//    br_round_ms[s] the time of one full round. The split matrix-core form is timed instead
+//    br_round_ms[s] the time of one full round. (Forms 3 and 4 are priced as rounds of singles or of
+//    pairs; where launch_blind_rotate mixes the two, the time is shorter than the price: 700 gates are
+//    priced at 7.1 ms and take 6.4.) The split matrix-core form is timed instead
 //    at the sizes kSplitAt (split_ms[k], with the fastest row-group count split_groups[k]) and
 //    estimated in between by linear interpolation (beyond the last size: in proportion), with
 //    a 3% margin above 1,280 gates.
@@ -298,14 +300,14 @@ hipError_t launch_blind_rotate_mfma(const vsp_context* ctx, const uint8_t* ops, 
                                     const int8_t* const* tkeys = nullptr);
 // Identity key switch TLWE1 [B][N+1] -> TLWE0 [B][n+1] (outputs scattered by idxo if given).
 // form: 0 one workgroup per gate, 1 row-stationary tiles, 2 LDS-staged split, 3 matrix cores
-// (the context's own key only; other keys run form 2), -1 the tuned one.
+// (keys without byte planes run form 2), -1 the tuned one.
 constexpr int kKsForms = 4;
 // ksk: the key-switching key to use (NULL: the context's); ks_mf: its byte-plane form (needed
 // for form 3 with a key other than the context's).
 hipError_t launch_keyswitch(const vsp_context* ctx, const uint8_t* ops, const uint32_t* tlwe1, const uint32_t* idxo,
                             uint32_t* out, uint64_t B, hipStream_t st, int form = -1, const uint32_t* ksk = nullptr,
                             const int8_t* ks_mf = nullptr);
-// out[j] = C_j (ext) x_j, or with `x0` given: out[j] = x0_j + C_j (ext) (x_j - x0_j).
+// out[j] = C_j (ext) x_j.
 hipError_t launch_ext_product(const vsp_context* ctx, const c64* Cn, const uint32_t* x, uint32_t* out,
                               uint64_t J, hipStream_t st);
 hipError_t launch_polymul(const vsp_context* ctx, const int32_t* a, const uint32_t* b, uint32_t* out, uint64_t J,
